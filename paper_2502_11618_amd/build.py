@@ -23,7 +23,7 @@ INCLUDE = os.path.join(ROOT, "include")
 BUILD = os.path.join(ROOT, "_build")
 LIB = os.path.join(PKG, "liblnr.so")
 
-SOURCES = ["api.cpp", "grid.hip", "render.hip", "filter.hip", "unet.hip"]
+SOURCES = ["api.cpp", "grid.hip", "render.hip", "filter.hip", "unet.hip", "conv16.hip"]
 
 FLAGS = [
     "-O3", "-std=c++17", "-fPIC", "--offload-arch=gfx950",

@@ -311,15 +311,21 @@ double host_e4m3_value(uint8_t v) {
 }
 
 
+// index of the (32 output channel, 16 input channel) block of output channel o
+// and input channel i in the packed weights of conv16.hip
+size_t unit_tile(const ConvLayer &l, int o, int i) {
+  const int g = channel_group(l.cout_pad), tiles = g / 32;
+  return ((size_t)(o / g) * (l.cin_pad / 16) + i / 16) * tiles + (o % g) / 32;
+}
+
 // ---------------------------------------------------------------------------
 // U-Net activation layout for a batch of B same-shape images, and its launches
 // ---------------------------------------------------------------------------
 struct UNetLayout {
   int H = 0, W = 0, B = 1;
-  size_t es = 4;  // bytes per activation element
-  size_t x0_off = 0, x0_bs = 0;
+  size_t es = 4;  // bytes per activation of a channel
   size_t t_off[6] = {}, s_off[6] = {}, p_off[6] = {}, d_off[6] = {};
-  size_t act_bs[6] = {}, pool_bs[6] = {};  // per-image elements at level l (w_l and w_{l-1} channels)
+  size_t act_bs[6] = {}, pool_bs[6] = {};  // bytes per image at level l (w_l and w_{l-1} channels)
   size_t bytes = 0;
 };
 
@@ -328,42 +334,38 @@ UNetLayout unet_layout(const lnr_unet *u, int H, int W, int B) {
   y.H = H;
   y.W = W;
   y.B = B;
-  y.es = prec_half(u->prec) ? 2 : 4;
+  switch (u->prec) {
+    case Prec::F32:
+    case Prec::BF16X3: y.es = 4; break;  // float32; bfloat16 hi + lo
+    case Prec::FP8: y.es = u->widths[0] <= 64 ? 1 : 2; break;  // e4m3 (an unfused head reads float16)
+    default: y.es = 2;  // 16-bit; e4m3 hi + lo
+  }
   auto al = [](size_t b) { return (b + 255) / 256 * 256; };
   size_t off = 0;
-  y.x0_bs = (size_t)H * W * u->cin0_pad;
-  y.x0_off = off;
-  off += al(y.x0_bs * B * y.es);
   for (int l = 0; l < u->L; ++l) {
     const size_t px = (size_t)(H >> l) * (W >> l);
-    y.act_bs[l] = px * u->widths[l];
-    y.pool_bs[l] = (l > 0) ? px * u->widths[l - 1] : 0;
+    y.act_bs[l] = px * u->widths[l] * y.es;
+    y.pool_bs[l] = (l > 0) ? px * u->widths[l - 1] * y.es : 0;
     y.t_off[l] = off;
-    off += al(y.act_bs[l] * B * y.es);
+    off += al(y.act_bs[l] * B);
     y.s_off[l] = off;
-    off += al(y.act_bs[l] * B * y.es);
+    off += al(y.act_bs[l] * B);
     y.d_off[l] = off;
-    off += al(y.act_bs[l] * B * y.es);
+    off += al(y.act_bs[l] * B);
     y.p_off[l] = off;
-    off += al(y.pool_bs[l] * B * y.es);
+    off += al(y.pool_bs[l] * B);
   }
   y.bytes = off;
   return y;
 }
 
-lnr_status unet_pack(lnr_context *ctx, Scratch &sc, const lnr_unet *u, const UNetLayout &y, int b, const float *depth,
-                     const uint32_t *rgba, hipStream_t s) {
-  char *x0 = static_cast<char *>(sc.act.p) + y.x0_off + (size_t)b * y.x0_bs * y.es;
-  LNR_LAUNCH(ctx, "pack", s, launch_pack_input(depth, rgba, y.H, y.W, u->cin0_pad, u->prec, x0, s));
-  return LNR_OK;
-}
-
 // All 3x3 convolutions of the network over the batch; the 1x1 head is fused
 // into the last one when widths[0] <= 64 (outputs: head_outs_dev[b] if given,
 // else rgb_out + b * 3*H*W), otherwise it runs as its own kernel per image.
+// The first convolution reads the RGBDA images (rgbda_bs pixels apart) itself.
 lnr_status unet_convs(lnr_context *ctx, Scratch &sc, const lnr_unet *u, const UNetLayout &y, float *rgb_out,
-                      float *const *head_outs_dev, hipStream_t s, const float *rgbda_depth = nullptr,
-                      const uint32_t *rgbda_rgba = nullptr) {
+                      float *const *head_outs_dev, hipStream_t s, const float *rgbda_depth,
+                      const uint32_t *rgbda_rgba, size_t rgbda_bs) {
   char *base = static_cast<char *>(sc.act.p);
   const int L = u->L, B = y.B;
   const bool fuse_head = u->widths[0] <= 64;
@@ -372,9 +374,9 @@ lnr_status unet_convs(lnr_context *ctx, Scratch &sc, const lnr_unet *u, const UN
   for (int l = 0; l < L; ++l) {
     const int Hl = y.H >> l, Wl = y.W >> l;
     ConvCall a{};
-    a.in0 = (l == 0) ? (const void *)(base + y.x0_off) : (const void *)(base + y.p_off[l]);
+    a.in0 = (l == 0) ? nullptr : (const void *)(base + y.p_off[l]);
     a.C0 = (l == 0) ? u->cin0_pad : u->widths[l - 1];
-    a.in0_bs = (l == 0) ? y.x0_bs : y.pool_bs[l];
+    a.in0_bs = y.pool_bs[l];
     a.in1 = nullptr;
     a.C1 = 0;
     a.H = Hl;
@@ -383,9 +385,10 @@ lnr_status unet_convs(lnr_context *ctx, Scratch &sc, const lnr_unet *u, const UN
     a.out = base + y.t_off[l];
     a.out_bs = y.act_bs[l];
     a.batch = B;
-    if (l == 0 && rgbda_depth) {
+    if (l == 0) {
       a.rgbda_depth = rgbda_depth;
       a.rgbda_rgba = rgbda_rgba;
+      a.rgbda_bs = rgbda_bs;
     }
     ConvCall c{};
     c.in0 = base + y.t_off[l];
@@ -405,10 +408,11 @@ lnr_status unet_convs(lnr_context *ctx, Scratch &sc, const lnr_unet *u, const UN
       c.head_out = rgb_out;
       c.head_outs = head_outs_dev;
     }
+    c.raw_out = L == 1 && !fuse_head;
     li += 2;
     if (l == 0 && L > 1 && enc0_fusable(*a.layer, *c.layer, u->prec)) {
       // both first-level convolutions in one launch; its time is reported as conv/enc0
-      LNR_LAUNCH(ctx, "conv/enc0", s, launch_enc0_fused(a, c, u->prec, s));
+      LNR_LAUNCH(ctx, "conv/enc0", s, launch_enc0(a, c, u->prec, s));
       continue;
     }
     LNR_LAUNCH(ctx, kConvNames[0][l][0], s, launch_conv3x3(a, u->prec, s));
@@ -446,13 +450,14 @@ lnr_status unet_convs(lnr_context *ctx, Scratch &sc, const lnr_unet *u, const UN
       c.head_out = rgb_out;
       c.head_outs = head_outs_dev;
     }
+    c.raw_out = l == 0 && !fuse_head;
     LNR_LAUNCH(ctx, kConvNames[1][l][1], s, launch_conv3x3(c, u->prec, s));
   }
   if (!fuse_head) {
     const size_t off = (L == 1) ? y.s_off[0] : y.d_off[0];
     for (int b = 0; b < B; ++b)
       LNR_LAUNCH(ctx, "head", s,
-                 launch_head(base + off + (size_t)b * y.act_bs[0] * y.es, u->widths[0], y.H, y.W, u->head, u->prec,
+                 launch_head(base + off + (size_t)b * y.act_bs[0], u->widths[0], y.H, y.W, u->head, u->prec,
                              rgb_out + (size_t)b * 3 * y.H * y.W, s));
   }
   return LNR_OK;
@@ -1198,17 +1203,14 @@ lnr_status lnr_unet_load(lnr_context *ctx, const void *blob_host, uint64_t bytes
           }
         if ((st = upload(wu.data(), 4 * wu.size(), &cl.wu)) != LNR_OK) return free_all(), st;
       }
-    } else if (u->prec == Prec::FP16) {
-      std::vector<uint16_t> h(np);
-      for (size_t i = 0; i < np; ++i) h[i] = host_f2h(packed[i]);
-      if ((st = upload(h.data(), 2 * np, &cl.w)) != LNR_OK) return free_all(), st;
     } else if (u->prec == Prec::FP8 || u->prec == Prec::FP8X3) {
       // one scale per output channel: its largest weight (of the float64,
-      // batch-norm-folded weights) maps to 448; the lo plane holds the e4m3 of
-      // what rounding the scaled weight to e4m3 left
-      std::vector<uint8_t> hi(np, 0), lo(np, 0);
+      // batch-norm-folded weights) maps to 448; lo holds the e4m3 of what
+      // rounding the scaled weight to e4m3 left.  Units: 16 channels, or
+      // 8 channels hi then lo.
+      const bool x3 = u->prec == Prec::FP8X3;
+      std::vector<uint8_t> units(x3 ? 2 * np : np, 0);
       std::vector<float> scale(cl.cout_pad, 1.f);
-      const size_t row = (size_t)9 * cl.cin_pad;
       for (int o = 0; o < (int)co; ++o) {
         double amax = 0;
         for (int i = 0; i < (int)ci; ++i)
@@ -1217,26 +1219,37 @@ lnr_status lnr_unet_load(lnr_context *ctx, const void *blob_host, uint64_t bytes
         scale[o] = (float)sc;
         for (int i = 0; i < (int)ci; ++i)
           for (int t = 0; t < 9; ++t) {
-            const size_t q = (size_t)o * row + (size_t)t * cl.cin_pad + i;
             const double v = Wd[((size_t)o * ci + i) * 9 + t] / (double)scale[o];
-            hi[q] = host_e4m3(v);
-            lo[q] = host_e4m3(v - host_e4m3_value(hi[q]));
+            const uint8_t hi = host_e4m3(v);
+            const size_t chunk = unit_tile(cl, o, i);
+            if (x3) {
+              uint8_t *q = &units[(((chunk * 9 + t) * 2 + (i % 16) / 8) * 32 + o % 32) * 16 + i % 8];
+              q[0] = hi;
+              q[8] = host_e4m3(v - host_e4m3_value(hi));
+            } else {
+              units[((chunk * 9 + t) * 32 + o % 32) * 16 + i % 16] = hi;
+            }
           }
       }
-      if ((st = upload(hi.data(), np, &cl.w)) != LNR_OK) return free_all(), st;
-      if (u->prec == Prec::FP8X3 && (st = upload(lo.data(), np, &cl.w_lo)) != LNR_OK) return free_all(), st;
+      if ((st = upload(units.data(), units.size(), &cl.w)) != LNR_OK) return free_all(), st;
       void *sp;
       if ((st = upload(scale.data(), 4 * scale.size(), &sp)) != LNR_OK) return free_all(), st;
       cl.wscale = static_cast<float *>(sp);
     } else {
-      std::vector<uint16_t> hi(np), lo(np);
-      for (size_t i = 0; i < np; ++i) {
-        hi[i] = host_f2bf(packed[i]);
-        lo[i] = host_f2bf(packed[i] - host_bf2f(hi[i]));
-      }
-      if ((st = upload(hi.data(), 2 * np, &cl.w)) != LNR_OK) return free_all(), st;
-      if (u->prec == Prec::BF16X3)
-        if ((st = upload(lo.data(), 2 * np, &cl.w_lo)) != LNR_OK) return free_all(), st;
+      // 16-bit units of 8 channels; split bfloat16: a chunk's hi plane, then its lo plane
+      const int planes = u->prec == Prec::BF16X3 ? 2 : 1;
+      std::vector<uint16_t> units(np * planes, 0);
+      for (int o = 0; o < cl.cout_pad; ++o)
+        for (int t = 0; t < 9; ++t)
+          for (int i = 0; i < cl.cin_pad; ++i) {
+            const float v = packed[((size_t)o * 9 + t) * cl.cin_pad + i];
+            const size_t chunk = unit_tile(cl, o, i);
+            const uint16_t hi = u->prec == Prec::FP16 ? host_f2h(v) : host_f2bf(v);
+            uint16_t *q = &units[(((chunk * planes * 9 + t) * 2 + (i % 16) / 8) * 32 + o % 32) * 8 + i % 8];
+            q[0] = hi;
+            if (planes == 2) q[9 * 512] = host_f2bf(v - host_bf2f(hi));
+          }
+      if ((st = upload(units.data(), 2 * units.size(), &cl.w)) != LNR_OK) return free_all(), st;
     }
     u->convs.push_back(cl);
   }
@@ -1275,10 +1288,8 @@ lnr_status lnr_reconstruct(lnr_context *ctx, const lnr_unet *u, const lnr_image 
   const UNetLayout lay = unet_layout(u, H, W, 1);
   if ((st = ensure(ctx, ctx->sc.act, lay.bytes)) != LNR_OK) return st;
   hipStream_t s = static_cast<hipStream_t>(hip_stream);
-  // one image: the first convolution reads the RGBDA image itself (batches
-  // from the serving loop go through the input pack into one batched tensor)
   if ((st = unet_convs(ctx, ctx->sc, u, lay, rgb_out, nullptr, s, in->depth,
-                       reinterpret_cast<const uint32_t *>(in->rgba))) != LNR_OK)
+                       reinterpret_cast<const uint32_t *>(in->rgba), 0)) != LNR_OK)
     return st;
   ctx->last_stream = s;
   return LNR_OK;
@@ -1358,7 +1369,7 @@ struct ServerLane {
   float **head_outs_host = nullptr;  // pinned host staging of the same
   DevCam *cams_dev = nullptr;        // the batch's cameras, device array [max_batch]
   DevCam *cams_host = nullptr;       // pinned host staging of the same
-  // the RGBDA image of each batch slot (rendered, filtered, packed), at the
+  // the RGBDA image of each batch slot (rendered, filtered), at the
   // largest session size: a key plane, a depth plane and an rgba plane of
   // max_batch slots each, slot b at pixel b * slot_px of every plane
   void *slot_buf = nullptr;
@@ -1664,8 +1675,8 @@ lnr_status lnr_server_step(lnr_server *srv, int32_t *launched) {
     lane->outs.push_back(o);
   }
   // Every launch of the batch: per slot render (camera read from cams_dev),
-  // depth filter and input pack, then the batched U-Net writing through
-  // head_outs_dev.  Nothing in it depends on the batch's cameras or sessions
+  // and depth filter, then the batched U-Net reading the slots' images and
+  // writing through head_outs_dev.  Nothing in it depends on the batch's cameras or sessions
   // beyond those two device arrays, so one capture per (size, batch) serves
   // every later batch of that shape.
   char *slots = static_cast<char *>(lane->slot_buf);
@@ -1680,11 +1691,11 @@ lnr_status lnr_server_step(lnr_server *srv, int32_t *launched) {
                                  srv->cfg.soft_eps, s, lane->cams_dev + b);
       if (r == LNR_OK && srv->cfg.n_levels > 0)
         r = depth_filter_impl(ctx, lane->sc, &img, srv->cfg.n_levels, srv->cfg.filter_strength, s);
-      if (r == LNR_OK)
-        r = unet_pack(ctx, lane->sc, srv->unet, lay, b, img.depth, reinterpret_cast<const uint32_t *>(img.rgba), s);
       if (r != LNR_OK) return r;
     }
-    return unet_convs(ctx, lane->sc, srv->unet, lay, nullptr, lane->head_outs_dev, s);
+    return unet_convs(ctx, lane->sc, srv->unet, lay, nullptr, lane->head_outs_dev, s,
+                      reinterpret_cast<const float *>(slots + 8 * sp * mb),
+                      reinterpret_cast<const uint32_t *>(slots + 12 * sp * mb), sp);
   };
   LNR_HIP(ctx, hipEventRecord(lane->ev_start, s));
   LNR_HIP(ctx, hipMemcpyAsync(lane->head_outs_dev, lane->head_outs_host, 8ull * B, hipMemcpyHostToDevice, s));

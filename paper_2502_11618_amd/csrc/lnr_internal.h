@@ -189,52 +189,61 @@ hipError_t launch_upsample_fused(int n, const float *const *D, const int *Hs, co
 // unet.hip
 // values equal the public lnr_precision ones
 enum class Prec { F32 = 0, BF16 = 1, FP8 = 2, BF16X3 = 3, FP16 = 4, FP8X3 = 5 };
-// 16-bit activations in HBM (the e4m3 modes keep float16 activations)
-inline bool prec_half(Prec p) { return p == Prec::BF16 || p == Prec::FP16 || p == Prec::FP8 || p == Prec::FP8X3; }
-
 struct ConvLayer {
   int cout = 0, cin = 0, k = 3;  // logical sizes
   int cout_pad = 0;              // multiple of 32 (MFMA block rows)
-  int cin_pad = 0;               // multiple of 8 (fp32) / 16 (bf16)
-  void *w = nullptr;             // packed weights [cout_pad][k*k][cin_pad] (f32 or bf16 hi)
-  void *w_lo = nullptr;          // bf16 low parts (BF16X3)
+  int cin_pad = 0;               // multiple of 8 (fp32) / 16
+  // packed weights: float32 [cout_pad][9][cin_pad]; else the operand units of
+  // conv16.hip, [group][cin_pad / 16][tile][plane][tap][half][32 channels]:
+  // groups of channel_group(cout_pad) output channels, tiles of 32
+  void *w = nullptr;
   float *bias = nullptr;         // [cout_pad]
   void *wu = nullptr;            // float32 only: Winograd F(2x2,3x3) weights G g G^T [cout_pad][16][cin_pad]
   float *wscale = nullptr;       // e4m3 modes: weight scale per output channel [cout_pad]
 };
 
+inline int channel_group(int cout_pad) { return cout_pad % 64 == 0 ? 64 : 32; }
+
+// Tensors: float32 NHWC, or the channel-block operands of conv16.hip; in0 has
+// C0 channels at H x W, in1 C1 channels at (H/2) x (W/2), read nearest-
+// upsampled (decoder), or null.
 struct ConvCall {
-  const void *in0;   // NHWC, C0 channels, H x W
-  const void *in1;   // NHWC, C1 channels, (H/2) x (W/2), read nearest-upsampled (decoder), or null
+  const void *in0;
+  const void *in1;
   int C0, C1;
   int H, W;
   const ConvLayer *layer;
-  void *out;         // NHWC, layer->cout channels
-  void *out_pool;    // NHWC, (H/2) x (W/2), 2x2 max of out, or null
+  void *out;         // layer->cout channels
+  void *out_pool;    // (H/2) x (W/2), 2x2 max of out, or null
   // optional fused 1x1 head (c_out <= 64): when head_out is set, the ReLU output
   // is not stored; head_out[o][y][x] = head_b[o] + sum_c head_w[o][c] * out[c]
   const float *head_w = nullptr;  // [3][cout]
   const float *head_b = nullptr;  // [3]
   float *head_out = nullptr;      // planar float [3][H][W]
-  // batch of same-shape images (per-image element strides; head_outs: device
+  // batch of same-shape images (per-image strides in bytes; head_outs: device
   // array of per-image head outputs, or null for head_out + image * 3*H*W)
   int batch = 1;
   size_t in0_bs = 0, in1_bs = 0, out_bs = 0, pool_bs = 0;
   float *const *head_outs = nullptr;
-  // first layer of a single image only: stage the network input straight from
-  // the RGBDA image (the same values the input pack writes) instead of in0
+  // first layer: the network input is read from the RGBDA images, rgbda_bs
+  // pixels apart, instead of in0
   const float *rgbda_depth = nullptr;
   const uint32_t *rgbda_rgba = nullptr;
+  size_t rgbda_bs = 0;
+  bool raw_out = false;  // the output is launch_head's input
 };
 
-hipError_t launch_pack_input(const float *depth, const uint32_t *rgba, int H, int W, int cpad, Prec p, void *x,
-                             hipStream_t s);
-// the first two convolutions in one launch (bf16 and fp16, first level of 16 or
-// 32 channels, at least two levels): the same outputs as two launch_conv3x3
-// calls, without the first one's output in HBM
-bool enc0_fusable(const ConvLayer &l0, const ConvLayer &l1, Prec p);
-hipError_t launch_enc0_fused(const ConvCall &c0, const ConvCall &c1, Prec p, hipStream_t s);
 hipError_t launch_conv3x3(const ConvCall &c, Prec p, hipStream_t s);
 hipError_t launch_head(const void *x, int C, int H, int W, const ConvLayer &head, Prec p, float *out, hipStream_t s);
+
+// conv16.hip: the same for every precision but float32, and the first two
+// convolutions in one launch (first level of 16 or 32 channels, at least two
+// levels) with the outputs of two launch_conv16 calls, without the first one's
+// output in memory
+bool enc0_fusable(const ConvLayer &l0, const ConvLayer &l1, Prec p);
+hipError_t launch_enc0(const ConvCall &c0, const ConvCall &c1, Prec p, hipStream_t s);
+hipError_t launch_conv16(const ConvCall &c, Prec p, hipStream_t s);
+hipError_t launch_head16(const void *x, int C, int H, int W, const ConvLayer &head, Prec p, float *out,
+                         hipStream_t s);
 
 }  // namespace lnr
