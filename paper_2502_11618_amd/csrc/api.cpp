@@ -656,12 +656,15 @@ static lnr_status cloud_build(lnr_context *ctx, lnr_cloud *cl, const float *xyz_
   LNR_HIP(ctx, launch_cell_aabb(c->d.x, c->d.y, c->d.z, c->d.cell_start, (uint32_t)C, c->d.aabb, s));
   uint32_t *d_total;
   if ((st = tmp.get(&d_total, 256)) != LNR_OK) return st;
-  LNR_HIP(ctx, hipMemsetAsync(d_total, 0, 4, s));
+  LNR_HIP(ctx, hipMemsetAsync(d_total, 0, 8, s));
   LNR_HIP(ctx, launch_chunk_count(c->d.cell_start, (uint32_t)C, d_total, s));
-  uint32_t total = 0;
-  LNR_HIP(ctx, hipMemcpy(&total, d_total, 4, hipMemcpyDeviceToHost));
+  uint32_t total[2] = {0, 0};
+  LNR_HIP(ctx, hipMemcpy(total, d_total, 8, hipMemcpyDeviceToHost));
   LNR_HIP(ctx, hipDeviceSynchronize());
-  c->d.max_chunks = total;
+  c->d.max_chunks = total[0];
+  const bool dense = (uint64_t)N >= (uint64_t)total[1] * kDenseItem;
+  c->d.item_points = dense ? kBinDense : kSplatChunk;
+  c->d.max_items = dense ? total[1] : total[0];
   return LNR_OK;
 }
 
@@ -792,25 +795,27 @@ static lnr_status render_impl(lnr_context *ctx, Scratch &scr, const lnr_cloud *c
              launch_clear(out->key, atomic ? npix : 0u, counters, tb.tile_nseg, atomic ? 0u : 2 * tg.n_tiles, s));
   LNR_LAUNCH(ctx, "cull", s,
              launch_cull(c->d, prm, dev ? &dev->cull : nullptr, static_cast<uint8_t *>(scr.flags.p),
-                         static_cast<uint2 *>(scr.chunks.p), counters, s));
+                         static_cast<uint2 *>(scr.chunks.p), atomic ? kSplatChunk : c->d.item_points, counters,
+                         s));
   const uint2 *chunks = static_cast<const uint2 *>(scr.chunks.p);
   uint32_t *rgba32 = reinterpret_cast<uint32_t *>(out->rgba);
   if (atomic) {
     LNR_LAUNCH(ctx, "splat", s, launch_splat(c->d, chunks, counters, sc, out->key, count, s));
     if (!soft) LNR_LAUNCH(ctx, "resolve", s, launch_resolve(out->key, c->d.rgbx, out->depth, rgba32, npix, s));
   } else {
-    static const char *const names[5] = {"bin", "tilescan", "segsort", "tile", "tileres"};
+    static const char *const names[6] = {"bin", "tilescan", "segsort", "tile", "soft", "tileres"};
     const bool merged = tiled_scan_merged(tg);  // the scan runs inside the segment sort
-    for (int stage = 0; stage < 5; ++stage)
-      if (!(merged && stage == 1))
+    for (int stage = 0; stage < 6; ++stage)
+      if (!(merged && stage == 1) && !(!soft && stage == 4))
         LNR_LAUNCH(ctx, names[stage], s,
-                 launch_tiled_splat(c->d, chunks, counters, sc, dev ? &dev->splat : nullptr, (uint32_t)cam->height,
-                                    tb, out->key, out->depth, rgba32, stage, s));
+                   launch_tiled_splat(c->d, chunks, counters, sc, dev ? &dev->splat : nullptr, (uint32_t)cam->height,
+                                      tb, out->key, out->depth, rgba32, soft ? scr.soft_acc.p : nullptr,
+                                      1.0f + soft_eps, stage, s));
   }
-  if (soft)
+  if (soft && atomic)
     LNR_LAUNCH(ctx, "soft", s,
-               launch_soft(c->d, chunks, counters, sc, dev ? &dev->splat : nullptr, out->key, 1.0f + soft_eps,
-                           static_cast<uint32_t *>(scr.soft_acc.p), out->depth, rgba32, npix, s));
+               launch_soft(c->d, chunks, counters, sc, out->key, 1.0f + soft_eps, scr.soft_acc.p, out->depth, rgba32,
+                           npix, s));
   ctx->last_stream = s;
   ctx->rendered = true;
   ctx->counted = count;

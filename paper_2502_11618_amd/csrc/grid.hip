@@ -250,10 +250,20 @@ __global__ __launch_bounds__(kThreads) void cell_aabb_kernel(const float *__rest
 __global__ __launch_bounds__(kThreads) void chunk_count_kernel(const uint32_t *__restrict__ cell_start,
                                                                uint32_t n_cells, uint32_t *__restrict__ total) {
   const uint32_t c = blockIdx.x * kThreads + threadIdx.x;
-  uint32_t v = 0;
-  if (c < n_cells) v = (cell_start[c + 1] - cell_start[c] + kSplatChunk - 1) / kSplatChunk;
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-  if ((threadIdx.x & 63) == 0 && v) atomicAdd(total, v);
+  uint32_t v = 0, d = 0;
+  if (c < n_cells) {
+    const uint32_t cnt = cell_start[c + 1] - cell_start[c];
+    v = cnt / kSplatChunk + (cnt % kSplatChunk ? 1u : 0u);
+    d = cnt / kBinDense + (cnt % kBinDense ? 1u : 0u);
+  }
+  for (int off = 32; off > 0; off >>= 1) {
+    v += __shfl_xor(v, off, 64);
+    d += __shfl_xor(d, off, 64);
+  }
+  if ((threadIdx.x & 63) == 0 && v) {
+    atomicAdd(&total[0], v);
+    atomicAdd(&total[1], d);
+  }
 }
 
 inline uint32_t div_up(uint64_t a, uint64_t b) { return (uint32_t)((a + b - 1) / b); }

@@ -22,6 +22,8 @@ struct CloudDev {
   float origin[3] = {0, 0, 0};
   float cell_size = 0;
   uint32_t max_chunks = 0;    // sum over cells of ceil(count / kSplatChunk)
+  uint32_t item_points = 0;   // points of a tiled splat's work item: kSplatChunk or kBinDense
+  uint32_t max_items = 0;     // sum over cells of ceil(count / item_points)
   float *x = nullptr, *y = nullptr, *z = nullptr;  // sorted SoA coordinates
   uint32_t *rgbx = nullptr;   // sorted colours, bytes r, g, b, 0
   uint32_t *perm = nullptr;   // sorted position -> input index
@@ -31,6 +33,9 @@ struct CloudDev {
 
 constexpr uint32_t kSplatChunk = 4096;   // points per splat work item
 constexpr int kSplatThreads = 256;
+// The tiled splat's work items have kBinDense points where the cloud's cells
+// fill them with kDenseItem points or more on average.
+constexpr uint32_t kBinDense = 8192, kDenseItem = 3072;
 
 // frustum-cull parameters, formed on the host in double precision
 struct CullParams {
@@ -110,6 +115,7 @@ hipError_t launch_gather_points(const float *xyz, const uint8_t *rgb, const uint
                                 float *y, float *z, uint32_t *rgbx, hipStream_t s);
 hipError_t launch_cell_aabb(const float *x, const float *y, const float *z, const uint32_t *cell_start,
                             uint32_t n_cells, float *aabb, hipStream_t s);
+// sums over cells of ceil(count / kSplatChunk) and ceil(count / kBinDense) into total[0..1] (zeroed by the caller)
 hipError_t launch_chunk_count(const uint32_t *cell_start, uint32_t n_cells, uint32_t *total, hipStream_t s);
 
 // render.hip
@@ -117,9 +123,10 @@ hipError_t launch_chunk_count(const uint32_t *cell_start, uint32_t n_cells, uint
 // splat's per-tile segment counts (n_tiles words)
 hipError_t launch_clear(uint64_t *key, uint32_t npix, uint32_t *counters, uint32_t *tile_nseg, uint32_t n_tiles,
                         hipStream_t s);
-// Screen-tiled splat (32 x 32 pixel tiles), in up to five launches (stage
-// 0..4: bin, tilescan, segsort, tile, tileres; stage 1 launches nothing when
-// tiled_scan_merged(), the segment sort then taking the scan).  Scratch per
+// Screen-tiled splat (32 x 32 pixel tiles), in up to six launches (stage
+// 0..5: bin, tilescan, segsort, tile, soft, tileres; stage 1 launches nothing
+// when tiled_scan_merged(), the segment sort then taking the scan; stage 4
+// only for the soft z-buffer).  Scratch per
 // render for a cloud of n points: recs u64[n] (a work item's records at its
 // points' positions), segs uint4[n] and sorted u32[n] (at most one segment
 // per record), tile_nseg u32[2 n_tiles] (the counts, then the merged sort's
@@ -143,13 +150,15 @@ struct TiledSplatBufs {
   uint32_t *tile_units;
   uint2 *units;
 };
+// acc (nullptr: the hard z-buffer): 16 bytes of colour sums per pixel.
 // cam_dev / prm_dev (may be nullptr): the same camera in device memory, read by
 // the kernels instead of the by-value copy (graph replays with new cameras)
 hipError_t launch_tiled_splat(const CloudDev &c, const uint2 *chunks, uint32_t *counters, const SplatCam &cam,
                               const SplatCam *cam_dev, uint32_t H, const TiledSplatBufs &b, uint64_t *key,
-                              float *depth, uint32_t *rgba, int stage, hipStream_t s);
+                              float *depth, uint32_t *rgba, void *acc, float one_plus_eps, int stage,
+                              hipStream_t s);
 hipError_t launch_cull(const CloudDev &c, const CullParams &prm, const CullParams *prm_dev, uint8_t *flags,
-                       uint2 *chunks, uint32_t *counters, hipStream_t s);
+                       uint2 *chunks, uint32_t chunk, uint32_t *counters, hipStream_t s);
 // the atomic splat (global z-buffer); count_atomics: also add the number of
 // z-buffer atomics issued to counters[kAtomicWord]
 hipError_t launch_splat(const CloudDev &c, const uint2 *chunks, uint32_t *counters, const SplatCam &cam,
@@ -169,10 +178,10 @@ hipError_t launch_atomic_probe(uint64_t *buf, uint32_t n_slots, int pattern, uin
                                hipStream_t s);
 hipError_t launch_resolve(const uint64_t *key, const uint32_t *rgbx, float *depth, uint32_t *rgba, uint32_t npix,
                           hipStream_t s);
-// soft z-buffer: clear the colour sums, accumulate, resolve (acc = 4 x u32 per pixel)
+// soft z-buffer after launch_splat: clear the colour sums (acc, 16 bytes per pixel), accumulate, resolve
 hipError_t launch_soft(const CloudDev &c, const uint2 *chunks, const uint32_t *counters, const SplatCam &cam,
-                       const SplatCam *cam_dev, const uint64_t *key, float one_plus_eps, uint32_t *acc, float *depth,
-                       uint32_t *rgba, uint32_t npix, hipStream_t s);
+                       const uint64_t *key, float one_plus_eps, void *acc, float *depth, uint32_t *rgba, uint32_t npix,
+                       hipStream_t s);
 
 // filter.hip
 hipError_t launch_pyramid(const float *depth, const uint32_t *rgba, int H, int W, int n, float *const *levels,

@@ -142,7 +142,7 @@ __device__ __attribute__((always_inline)) inline void add_totals(bool vis, uint3
 }
 
 // One lane per cell.  A visible non-empty cell is cut into splat work items
-// of at most kSplatChunk points, queued in the depth bucket of the cell's
+// of at most `chunk` points, queued in the depth bucket of the cell's
 // centre.  DEV: the camera's parameters are read from device memory (prm_dev)
 // instead of the kernel arguments, so that a captured graph can be replayed
 // for new cameras.
@@ -151,7 +151,7 @@ __global__ __launch_bounds__(kThreads) void cull_kernel(const float *__restrict_
                                                         const uint32_t *__restrict__ cell_start, uint32_t n_cells,
                                                         CullParams prm_val, const CullParams *__restrict__ prm_dev,
                                                         uint8_t *__restrict__ flags, uint2 *__restrict__ chunks,
-                                                        uint32_t cap, uint32_t *__restrict__ counters) {
+                                                        uint32_t cap, uint32_t chunk, uint32_t *__restrict__ counters) {
   const CullParams &prm = DEV ? *prm_dev : prm_val;
   const uint32_t c = blockIdx.x * kThreads + threadIdx.x;
   uint32_t start = 0, cnt = 0;
@@ -165,11 +165,11 @@ __global__ __launch_bounds__(kThreads) void cull_kernel(const float *__restrict_
                          aabb[6ull * c + 4], aabb[6ull * c + 5], &bucket);
     flags[c] = vis ? 1 : 0;
   }
-  const uint32_t nch = vis ? (cnt + kSplatChunk - 1) / kSplatChunk : 0u;
+  const uint32_t nch = vis ? (cnt + chunk - 1) / chunk : 0u;
   const uint32_t pos = reserve_places(nch, bucket, counters);
   for (uint32_t k = 0; k < nch; ++k) {
-    const uint32_t off = k * kSplatChunk;
-    chunks[(size_t)bucket * cap + pos + k] = make_uint2(start + off, min(kSplatChunk, cnt - off));
+    const uint32_t off = k * chunk;
+    chunks[(size_t)bucket * cap + pos + k] = make_uint2(start + off, min(chunk, cnt - off));
   }
   add_totals(vis, nch, cnt, counters);
 }
@@ -283,6 +283,32 @@ __device__ __attribute__((always_inline)) inline bool project_point(float x, flo
     }
   }
   return false;
+}
+
+// floor(RN(a / w)) for w > 0 and whether it lies in [0, lim): the quotient by the
+// reciprocal decides unless it is within its error (below 2^-22 of its size, and
+// rounding a / w moves it by half an ulp) of an integer, where the correctly
+// rounded division does.  Non-finite values take the division too.
+__device__ __attribute__((always_inline)) inline bool pixel_coord(float a, float w, float rw, float lim, uint32_t *p) {
+  const float q = a * rw;
+  float f = floorf(q);
+  const float r = q - f, m = fmaxf(fabsf(q), 1.0f) * 0x1p-21f;
+  if (!(r > m && r < 1.0f - m)) f = a / w;
+  *p = (uint32_t)f;
+  return f >= 0.f && f < lim;
+}
+// As project_point: the depth's bits and the pixel of a drawn point.
+__device__ __attribute__((always_inline)) inline bool project_pixel(float x, float y, float z, const SplatCam &cam,
+                                                                    uint32_t *wbits, uint32_t *px, uint32_t *py) {
+  const float *P = cam.P;
+  const float a = ((P[0] * x + P[1] * y) + P[2] * z) + P[3];
+  const float b = ((P[4] * x + P[5] * y) + P[6] * z) + P[7];
+  const float w = ((P[8] * x + P[9] * y) + P[10] * z) + P[11];
+  *wbits = __float_as_uint(w);
+  const bool in = w >= cam.z_near && w <= cam.z_far;
+  const float rw = __builtin_amdgcn_rcpf(w);
+  const bool inx = pixel_coord(a, w, rw, cam.Wf, px), iny = pixel_coord(b, w, rw, cam.Hf, py);
+  return in & inx & iny;
 }
 
 // The block-wide rectangle of the lanes' rectangles [x0, x1] x [y0, y1]
@@ -464,11 +490,10 @@ __global__ __launch_bounds__(kThreads) void splat_views_kernel(const float *__re
 // Screen-tiled splat (the default): no global atomic per point or pixel.
 //
 //   bin       one workgroup per work item: project the points; if they fall
-//             in a screen rectangle of at most kDedupPx pixels, keep only the
-//             nearest of each pixel (LDS z-buffer); counting-sort the rest by
-//             32 x 32 screen tile in LDS and write them, grouped by tile, as
-//             8-byte records at the work item's own place in the record
-//             array.  Each (work item, tile) group is a segment.
+//             in few enough 8 x 8 pixel blocks, keep only the nearest of each
+//             pixel (LDS z-buffer); write the entries, grouped by 32 x 32
+//             screen tile, as 8-byte records at the work item's own place in
+//             the record array.  Each (work item, tile) group is a segment.
 //   tilescan  one workgroup: per-tile segment offsets, and the units of work
 //             of the tile kernel: up to kSegsPerUnit segments of one tile.
 //   segsort   groups the segment ids by tile, and empties the keys of the
@@ -482,7 +507,11 @@ __global__ __launch_bounds__(kThreads) void splat_views_kernel(const float *__re
 //             atomicMin (one per pixel and unit), and
 //   tileres   resolves those tiles afterwards.
 //
-// A record is (float32 depth bits << 32) | (pixel within the tile << 12) |
+// The soft z-buffer takes the same launches with every drawn point an entry:
+// the tile kernel sums the colours of a tile of one unit too, and
+//   soft      sums those of the busier tiles once their nearest depths have met.
+//
+// A record is (float32 depth bits << 32) | (pixel within the tile << 14) |
 // (point index - work item start); the tile kernel rebuilds the key
 // (depth bits << 32) | sorted index, so the image equals the atomic splat's.
 // ---------------------------------------------------------------------------
@@ -491,7 +520,8 @@ constexpr int kTileSide = 1 << kTileShift;
 constexpr int kTilePx = kTileSide * kTileSide;
 constexpr int kHistBins = 1024;  // tiles one binning pass can address
 constexpr int kSegsPerUnit = 32;
-static_assert(kSplatChunk <= 4096, "a record keeps 12 bits of point offset");
+constexpr int kRecOffsetBits = 14;  // of a record: the point's offset in its work item
+static_assert(kBinDense <= 1u << kRecOffsetBits, "a record keeps the point offset within its work item");
 
 // exclusive prefix over the block (blockDim.x = NT): each thread passes its
 // value and gets the sum of the values of lower threads; *total receives the
@@ -523,72 +553,156 @@ struct TileGrid {
   uint32_t tiles_x, tiles_y, n_tiles;
 };
 
-template <bool DEV>  // DEV: the camera comes from device memory (cam_dev), as in cull_kernel
-__global__ __launch_bounds__(kThreads) void bin_kernel(const float *__restrict__ xs, const float *__restrict__ ys,
-                                                       const float *__restrict__ zs, const uint2 *__restrict__ chunks,
-                                                       uint32_t cap, uint32_t *__restrict__ counters, SplatCam cam_val,
-                                                       const SplatCam *__restrict__ cam_dev, TileGrid tg,
-                                                       uint64_t *__restrict__ recs, uint4 *__restrict__ segs,
-                                                       uint32_t *__restrict__ tile_nseg) {
+// A frame's work items.  Clouds with dense cells (kDenseItem points per item or
+// more) take items of up to 8 K points in workgroups of 512 threads: one on-chip
+// z-buffer then meets twice the points of a cell, over twice the pixels, so
+// fewer entries and segments leave it; others 4 K points and 256 threads.
+template <int NT>
+struct BinItem {
+  static constexpr int kPoints = NT * 16;                 // per item
+  static constexpr int kBlocks = NT >= 512 ? 128 : 64;   // 8 x 8 pixel blocks of the on-chip z-buffer
+};
+
+// DEV: the camera comes from device memory (cam_dev), as in cull_kernel.  ALL:
+// every drawn point is an entry (the soft z-buffer sums them all).
+template <int NT, bool DEV, bool ALL>
+__global__ __launch_bounds__(NT, 4) void bin_kernel(
+    const float *__restrict__ xs, const float *__restrict__ ys, const float *__restrict__ zs,
+    const uint2 *__restrict__ chunks, uint32_t cap, uint32_t *__restrict__ counters, SplatCam cam_val,
+    const SplatCam *__restrict__ cam_dev, TileGrid tg, uint64_t *__restrict__ recs, uint4 *__restrict__ segs,
+    uint32_t *__restrict__ tile_nseg) {
   const SplatCam &cam = DEV ? *cam_dev : cam_val;
-  // The work item's entries live in LDS, one u64 per slot (~0 = none).  With
-  // the on-chip z-buffer, slot = pixel of the rectangle (row order) and the
-  // entry its nearest key (depth bits << 32 | point index); otherwise slot =
-  // point (index - work item start) and the entry (depth bits << 32 |
-  // py << 16 | px).
-  __shared__ unsigned long long s_ent[kDedupPx];
-  __shared__ uint32_t s_hist[kHistBins];
-  __shared__ uint32_t s_tmp[kThreads / 64];
+  constexpr int kBlocks = BinItem<NT>::kBlocks, kWaves = NT / 64, kPts = 16;
+  constexpr int kZb = ALL ? kHistBins / 2 : kBlocks * 64;
+  __shared__ unsigned long long s_zb[kZb];  // z-buffer; or the tile histogram
+  __shared__ uint32_t s_off[kBlocks + 1];
+  __shared__ uint32_t s_tmp[kWaves];
   __shared__ uint32_t s_bb[4];
   __shared__ uint32_t s_seg_base;
+  uint32_t *s_hist = reinterpret_cast<uint32_t *>(s_zb);
+  static_assert(kHistBins * 4 <= (int)sizeof(s_zb), "the histogram lies where the z-buffer is");
   uint2 ch;
   if (!work_item(blockIdx.x, counters, chunks, cap, &ch)) return;
-  const int tid = threadIdx.x;
-  uint32_t x0, y0, x1, y1, bw, nslots;
-  bool dedup;
-  {
-    uint64_t kk[kPtsPerThread];
-    uint32_t px[kPtsPerThread], py[kPtsPerThread];
-    project_work_item(xs, ys, zs, ch, cam, kk, px, py, s_bb, &x0, &y0, &x1, &y1);
-    if (x0 > x1) return;  // nothing drawn (the same for the whole block)
-    bw = x1 - x0 + 1;
-    const uint64_t a64 = (uint64_t)bw * (uint64_t)(y1 - y0 + 1);
-    dedup = a64 <= (uint64_t)kDedupPx;
-    if (dedup) {
-      nslots = (uint32_t)a64;
-      for (uint32_t p = tid; p < nslots; p += kThreads) s_ent[p] = ~0ull;
-      __syncthreads();
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  ch.x = (uint32_t)__builtin_amdgcn_readfirstlane((int)ch.x);
+  ch.y = (uint32_t)__builtin_amdgcn_readfirstlane((int)ch.y);
+  const float *xb = xs + ch.x, *yb = ys + ch.x, *zb = zs + ch.x;
+  // thread t holds points t, t + NT, ...: depth bits and packed pixel (y << 16 | x; ~0 = not drawn)
+  uint32_t wb[kPts], pix[kPts];
+  uint32_t x0 = ~0u, y0 = ~0u, x1 = 0, y1 = 0;
+  // (groups of four points, so that the loads of all sixteen are not held at once)
 #pragma unroll
-      for (int q = 0; q < kPtsPerThread; ++q)
-        if (px[q] != ~0u) atomicMin(&s_ent[(py[q] - y0) * bw + (px[q] - x0)], (unsigned long long)kk[q]);
-    } else {
-      nslots = ch.y;
+  for (int g = 0; g < kPts; g += 4) {
+    float x[4], y[4], z[4];
 #pragma unroll
-      for (int q = 0; q < kPtsPerThread; ++q) {
-        const uint32_t i = tid + q * kThreads;
-        if (i < ch.y)
-          s_ent[i] = px[q] == ~0u ? ~0ull : ((kk[q] & 0xFFFFFFFF00000000ull) | (py[q] << 16) | px[q]);
-      }
+    for (int q = 0; q < 4; ++q) {
+      const uint32_t i = min((uint32_t)(tid + (g + q) * NT), ch.y - 1u);
+      x[q] = xb[i];
+      y[q] = yb[i];
+      z[q] = zb[i];
     }
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      uint32_t px = 0, py = 0;
+      const bool drawn = project_pixel(x[q], y[q], z[q], cam, &wb[g + q], &px, &py) &&
+                         (uint32_t)(tid + (g + q) * NT) < ch.y;
+      pix[g + q] = drawn ? (py << 16) | px : ~0u;
+      x0 = min(x0, drawn ? px : ~0u);
+      x1 = max(x1, drawn ? px : 0u);
+      y0 = min(y0, drawn ? py : ~0u);
+      y1 = max(y1, drawn ? py : 0u);
+    }
+    __builtin_amdgcn_sched_barrier(0);
   }
-  __syncthreads();
-  // pixel and key of an entry in slot p
-  const float inv_bw = 1.0f / (float)bw;
-  auto decode = [&](uint32_t p, uint64_t e, uint32_t *gx, uint32_t *gy) -> uint64_t {
-    if (dedup) {
-      const uint32_t ry = small_div(p, inv_bw);
-      *gy = y0 + ry;
-      *gx = x0 + (p - ry * bw);
-      return e;
-    }
-    *gy = ((uint32_t)e >> 16) & 0xFFFFu;
-    *gx = (uint32_t)e & 0xFFFFu;
-    return (e & 0xFFFFFFFF00000000ull) | (uint64_t)(ch.x + p);
-  };
-  // counting sort of the entries by tile, in rounds of tile rows so that one
-  // round addresses at most kHistBins tiles
+  block_rect(x0, y0, x1, y1, s_bb, &x0, &y0, &x1, &y1);
+  if (x0 > x1) return;  // nothing drawn (the same for the whole block)
   const uint32_t tx0 = x0 >> kTileShift, ty0 = y0 >> kTileShift;
   const uint32_t tbw = (x1 >> kTileShift) - tx0 + 1, ty1 = y1 >> kTileShift;
+  const uint32_t bx0 = x0 >> 3, by0 = y0 >> 3, nbx = (x1 >> 3) - bx0 + 1, nby = (y1 >> 3) - by0 + 1;
+  if (!ALL && nbx <= (uint32_t)kBlocks && nby <= (uint32_t)kBlocks && nbx * nby <= (uint32_t)kBlocks) {
+    // ---- the points meet in a z-buffer of 8 x 8 pixel blocks (row order), one
+    // wave reads a block at a time, and the blocks' entries are written in
+    // tile order
+    const uint32_t nblk = nbx * nby;
+    for (uint32_t p = tid; p < nblk * 64; p += NT) s_zb[p] = ~0ull;
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < kPts; ++q) {
+      uint32_t p = pix[q];
+      asm volatile("" : "+v"(p));  // (nothing of it is held in registers beyond its turn)
+      if (p != ~0u) {
+        const uint32_t px = p & 0xFFFFu, py = p >> 16;
+        const uint32_t slot = (((py >> 3) - by0) * nbx + ((px >> 3) - bx0)) * 64 + (py & 7) * 8 + (px & 7);
+        atomicMin(&s_zb[slot], ((unsigned long long)wb[q] << 32) | (uint32_t)(tid + q * NT));
+      }
+    }
+    __syncthreads();
+    // place of block (bx, by) among the blocks in tile order
+    auto place = [&](uint32_t bx, uint32_t by) {
+      const uint32_t ty = (by0 + by) >> 2, tx = (bx0 + bx) >> 2;
+      const uint32_t ys = max(by0, ty << 2) - by0, ye = min(by0 + nby, (ty + 1) << 2) - by0;
+      const uint32_t xs_ = max(bx0, tx << 2) - bx0, xe = min(bx0 + nbx, (tx + 1) << 2) - bx0;
+      return ys * nbx + (ye - ys) * xs_ + (by - ys) * (xe - xs_) + (bx - xs_);
+    };
+    const float inv_nbx = 1.0f / (float)nbx;
+    for (uint32_t b = wave; b < nblk; b += kWaves) {
+      const uint64_t m = __ballot(s_zb[b * 64 + lane] != ~0ull);
+      const uint32_t by = small_div(b, inv_nbx);
+      if (lane == 0) s_off[place(b - by * nbx, by)] = (uint32_t)__popcll(m);
+    }
+    __syncthreads();
+    if (wave == 0) {
+      // exclusive prefix over the blocks in tile order, two per lane
+      const uint32_t i0 = 2 * lane, i1 = 2 * lane + 1;
+      const uint32_t c0 = i0 < nblk ? s_off[i0] : 0u, c1 = i1 < nblk ? s_off[i1] : 0u;
+      uint32_t incl = c0 + c1;
+#pragma unroll
+      for (int off = 1; off < 64; off <<= 1) {
+        const uint32_t o = __shfl_up(incl, off, 64);
+        if (lane >= off) incl += o;
+      }
+      if (i0 < nblk) s_off[i0] = incl - c0 - c1;
+      if (i1 < nblk) s_off[i1] = incl - c1;
+      if (lane == 63) s_off[nblk] = incl;
+    }
+    __syncthreads();
+    if (wave == 0) {
+      // the segments: one lane per tile (at most 34 of them)
+      const uint32_t nty = ty1 - ty0 + 1, nt = tbw * nty;
+      uint32_t first = 0, cnt = 0, tile = 0;
+      if ((uint32_t)lane < nt) {
+        const uint32_t tr = lane / tbw, tc = lane - tr * tbw;
+        const uint32_t bx = max(bx0, (tx0 + tc) << 2) - bx0, by = max(by0, (ty0 + tr) << 2) - by0;
+        const uint32_t ye = min(by0 + nby, (ty0 + tr + 1) << 2) - by0, xe = min(bx0 + nbx, (tx0 + tc + 1) << 2) - bx0;
+        const uint32_t r = place(bx, by);
+        first = s_off[r];
+        cnt = s_off[r + (ye - by) * (xe - bx)] - first;
+        tile = (ty0 + tr) * tg.tiles_x + tx0 + tc;
+      }
+      const uint64_t m = __ballot(cnt != 0);
+      uint32_t base = 0;
+      if (lane == 0) base = atomicAdd(&counters[kSegTopWord], (uint32_t)__popcll(m));
+      base = __shfl(base, 0, 64);
+      if (cnt) {
+        segs[base + (uint32_t)__popcll(m & ((1ull << lane) - 1ull))] = make_uint4(tile, ch.x + first, cnt, ch.x);
+        atomicAdd(&tile_nseg[tile], 1u);
+      }
+    }
+    for (uint32_t b = wave; b < nblk; b += kWaves) {
+      const uint64_t k = s_zb[b * 64 + lane];
+      const uint64_t m = __ballot(k != ~0ull);
+      const uint32_t by = small_div(b, inv_nbx), bx = b - by * nbx;
+      if (k != ~0ull) {
+        const uint32_t pos = s_off[place(bx, by)] + (uint32_t)__popcll(m & ((1ull << lane) - 1ull));
+        const uint32_t local = ((((by0 + by) & 3) * 8 + (lane >> 3)) << kTileShift) | (((bx0 + bx) & 3) * 8 + (lane & 7));
+        recs[ch.x + pos] = (k & 0xFFFFFFFF00000000ull) | ((uint64_t)local << kRecOffsetBits) | (uint64_t)(uint32_t)k;
+      }
+    }
+    return;
+  }
+  // ---- a larger rectangle (a near surface), or ALL: every point is an entry.  Counting
+  // sort by tile, in rounds of tile rows so that one round addresses at most
+  // kHistBins tiles
   const uint32_t rows_per_round = max(1u, (uint32_t)kHistBins / tbw);
   uint32_t rec_next = 0;  // records written by earlier rounds
   for (uint32_t r0 = ty0; r0 <= ty1; r0 += rows_per_round) {
@@ -597,60 +711,62 @@ __global__ __launch_bounds__(kThreads) void bin_kernel(const float *__restrict__
     // a row wider than the histogram is split into column ranges
     for (uint32_t c0 = 0; c0 < tbins; c0 += kHistBins) {
       const uint32_t nbins = min((uint32_t)kHistBins, tbins - c0);
-      for (uint32_t b = tid; b < nbins; b += kThreads) s_hist[b] = 0;
+      // bin of a drawn point in this round (nbins or more: another round's)
+      // (the empty asm keeps the compiler from holding every point's tile across the rounds)
+      auto bin_of = [&](uint32_t p) {
+        asm volatile("" : "+v"(p));
+        const uint32_t ty = (p >> 16) >> kTileShift, tx = (p & 0xFFFFu) >> kTileShift;
+        return p == ~0u || ty < r0 || ty >= r1 ? ~0u : (ty - r0) * tbw + (tx - tx0) - c0;
+      };
+      for (uint32_t b = tid; b < nbins; b += NT) s_hist[b] = 0;
       __syncthreads();
-      for (uint32_t p = tid; p < nslots; p += kThreads) {
-        const uint64_t e = s_ent[p];
-        if (e == ~0ull) continue;
-        uint32_t gx, gy;
-        decode(p, e, &gx, &gy);
-        const uint32_t ty = gy >> kTileShift;
-        const uint32_t bin = (ty - r0) * tbw + ((gx >> kTileShift) - tx0) - c0;
-        if (ty >= r0 && ty < r1 && bin < nbins) atomicAdd(&s_hist[bin], 1u);
+#pragma unroll
+      for (int q = 0; q < kPts; ++q) {
+        const uint32_t bin = bin_of(pix[q]);
+        if (bin < nbins) atomicAdd(&s_hist[bin], 1u);
       }
       __syncthreads();
       // exclusive prefix over the bins of record counts and non-empty flags
-      // at once (16-bit halves: at most 4096 of each); a thread owns kPer bins
-      constexpr int kPer = kHistBins / kThreads;
-      uint32_t sum = 0;
+      // at once (16-bit halves: at most 8192 of each); a thread owns kPer bins
+      constexpr int kPer = kHistBins / NT;
+      uint32_t cnt[kPer], sum = 0;
+#pragma unroll
       for (int q = 0; q < kPer; ++q) {
         const uint32_t b = tid * kPer + q;
-        const uint32_t c = b < nbins ? s_hist[b] : 0u;
-        sum += (c << 16) | (c ? 1u : 0u);
+        cnt[q] = b < nbins ? s_hist[b] : 0u;
+        sum += (cnt[q] << 16) | (cnt[q] ? 1u : 0u);
       }
       uint32_t total;
-      uint32_t run = block_exclusive_scan<kThreads>(sum, s_tmp, &total);
+      uint32_t run = block_exclusive_scan<NT>(sum, s_tmp, &total);
       const uint32_t n_rec = total >> 16, n_seg = total & 0xFFFFu;
       if (n_rec == 0) continue;  // uniform: nothing in these bins
       if (tid == 0) s_seg_base = atomicAdd(&counters[kSegTopWord], n_seg);
       __syncthreads();
       const uint32_t seg_base = s_seg_base;
+#pragma unroll
       for (int q = 0; q < kPer; ++q) {
         const uint32_t b = tid * kPer + q;
-        if (b >= nbins) break;
-        const uint32_t c = s_hist[b];
-        const uint32_t first = rec_next + (run >> 16);
-        if (c) {
-          const uint32_t tb = c0 + b;
-          const uint32_t tile = (r0 + tb / tbw) * tg.tiles_x + (tx0 + tb % tbw);
-          segs[seg_base + (run & 0xFFFFu)] = make_uint4(tile, ch.x + first, c, ch.x);
-          atomicAdd(&tile_nseg[tile], 1u);
+        if (b < nbins) {
+          const uint32_t first = rec_next + (run >> 16);
+          if (cnt[q]) {
+            const uint32_t tb = c0 + b;
+            const uint32_t tile = (r0 + tb / tbw) * tg.tiles_x + (tx0 + tb % tbw);
+            segs[seg_base + (run & 0xFFFFu)] = make_uint4(tile, ch.x + first, cnt[q], ch.x);
+            atomicAdd(&tile_nseg[tile], 1u);
+          }
+          s_hist[b] = first;  // bin -> cursor at its first record
+          run += (cnt[q] << 16) | (cnt[q] ? 1u : 0u);
         }
-        s_hist[b] = first;  // bin -> cursor at its first record
-        run += (c << 16) | (c ? 1u : 0u);
       }
       __syncthreads();
-      for (uint32_t p = tid; p < nslots; p += kThreads) {
-        const uint64_t e = s_ent[p];
-        if (e == ~0ull) continue;
-        uint32_t gx, gy;
-        const uint64_t k = decode(p, e, &gx, &gy);
-        const uint32_t ty = gy >> kTileShift;
-        const uint32_t bin = (ty - r0) * tbw + ((gx >> kTileShift) - tx0) - c0;
-        if (ty < r0 || ty >= r1 || bin >= nbins) continue;
+#pragma unroll
+      for (int q = 0; q < kPts; ++q) {
+        const uint32_t bin = bin_of(pix[q]);
+        if (bin >= nbins) continue;
         const uint32_t pos = atomicAdd(&s_hist[bin], 1u);
-        const uint32_t local = ((gy & (kTileSide - 1)) << kTileShift) | (gx & (kTileSide - 1));
-        recs[ch.x + pos] = (k & 0xFFFFFFFF00000000ull) | ((uint64_t)local << 12) | (uint64_t)((uint32_t)k - ch.x);
+        const uint32_t px = pix[q] & 0xFFFFu, py = pix[q] >> 16;
+        const uint32_t local = ((py & (kTileSide - 1)) << kTileShift) | (px & (kTileSide - 1));
+        recs[ch.x + pos] = ((uint64_t)wb[q] << 32) | ((uint64_t)local << kRecOffsetBits) | (uint64_t)(uint32_t)(tid + q * NT);
       }
       rec_next += n_rec;
       __syncthreads();
@@ -697,14 +813,16 @@ __global__ __launch_bounds__(kScanThreads) void tilescan_kernel(const uint32_t *
 // [tile_off[t], tile_off[t + 1]) (their order is irrelevant: the tile kernel
 // takes a minimum).  Counts tile_nseg back down to zero.  Also empties the
 // key buffer over the tiles of more than one unit, whose units merge into it
-// with atomicMin (the tile kernel writes every other tile's keys whole).
+// with atomicMin (the tile kernel writes every other tile's keys whole), and
+// zeroes their colour sums (acc, the soft z-buffer).
 __global__ __launch_bounds__(kThreads) void segsort_kernel(const uint4 *__restrict__ segs,
                                                            const uint32_t *__restrict__ counters,
                                                            const uint32_t *__restrict__ tile_off,
                                                            uint32_t *__restrict__ tile_nseg,
                                                            uint32_t *__restrict__ sorted,
                                                            const uint32_t *__restrict__ tile_units, TileGrid tg,
-                                                           uint32_t W, uint32_t H, uint64_t *__restrict__ key) {
+                                                           uint32_t W, uint32_t H, uint64_t *__restrict__ key,
+                                                           uint4 *__restrict__ acc) {
   const uint32_t n = counters[kSegTopWord];
   for (uint32_t i = blockIdx.x * kThreads + threadIdx.x; i < n; i += gridDim.x * kThreads) {
     const uint32_t t = segs[i].x;
@@ -716,7 +834,10 @@ __global__ __launch_bounds__(kThreads) void segsort_kernel(const uint4 *__restri
     for (int p = threadIdx.x; p < kTilePx; p += kThreads) {
       const uint32_t gx = (tx << kTileShift) + (p & (kTileSide - 1));
       const uint32_t gy = (ty << kTileShift) + (p >> kTileShift);
-      if (gx < W && gy < H) key[(size_t)gy * W + gx] = ~0ull;
+      if (gx < W && gy < H) {
+        key[(size_t)gy * W + gx] = ~0ull;
+        if (acc) acc[(size_t)gy * W + gx] = make_uint4(0u, 0u, 0u, 0u);
+      }
     }
   }
 }
@@ -740,7 +861,8 @@ __global__ __launch_bounds__(kThreads) void segscan_kernel(const uint4 *__restri
                                                            uint32_t *__restrict__ tile_units,
                                                            uint2 *__restrict__ units, uint32_t unit_cap,
                                                            uint32_t *__restrict__ sorted, TileGrid tg, uint32_t W,
-                                                           uint32_t H, uint64_t *__restrict__ key) {
+                                                           uint32_t H, uint64_t *__restrict__ key,
+                                                           uint4 *__restrict__ acc) {
   __shared__ uint32_t s_off[kMaxScanTiles + 1];
   __shared__ uint32_t s_tmp[kThreads / 64];
   const int tid = threadIdx.x;
@@ -790,7 +912,10 @@ __global__ __launch_bounds__(kThreads) void segscan_kernel(const uint4 *__restri
     for (int p = tid; p < kTilePx; p += kThreads) {
       const uint32_t gx = (tx << kTileShift) + (p & (kTileSide - 1));
       const uint32_t gy = (ty << kTileShift) + (p >> kTileShift);
-      if (gx < W && gy < H) key[(size_t)gy * W + gx] = ~0ull;
+      if (gx < W && gy < H) {
+        key[(size_t)gy * W + gx] = ~0ull;
+        if (acc) acc[(size_t)gy * W + gx] = make_uint4(0u, 0u, 0u, 0u);
+      }
     }
   }
 }
@@ -806,21 +931,99 @@ __device__ inline void resolve_px(uint64_t k, const uint32_t *__restrict__ rgbx,
   }
 }
 
+// The records of a unit: up to kSegsPerUnit segments of one tile, NT threads.
+struct UnitSegs {
+  uint32_t pref[kSegsPerUnit + 1];  // prefix of the segments' record counts
+  uint2 seg[kSegsPerUnit];          // first record, work item start
+};
+// Segments [beg, end) of the sorted list into u (called by every thread; a
+// barrier follows before u is read).
+__device__ inline void load_unit(UnitSegs &u, const uint4 *__restrict__ segs, const uint32_t *__restrict__ sorted,
+                                 uint32_t beg, uint32_t nb) {
+  const int tid = threadIdx.x;
+  if (tid >= 64) return;
+  uint32_t c = 0;
+  if ((uint32_t)tid < nb) {
+    const uint4 sg = segs[sorted[beg + tid]];
+    u.seg[tid] = make_uint2(sg.y, sg.w);
+    c = sg.z;
+  }
+  uint32_t incl = c;
+#pragma unroll
+  for (int off = 1; off < 64; off <<= 1) {
+    const uint32_t o = __shfl_up(incl, off, 64);
+    if (tid >= off) incl += o;
+  }
+  if (tid <= kSegsPerUnit) u.pref[tid] = incl - c;  // pref[nb] = total
+}
+// f(depth bits, pixel of the tile, point index) for every record of the unit.
+// kInFlight records per thread: their loads are issued before the first is
+// used, so their latencies overlap.
+template <int NT, typename F>
+__device__ inline void for_records(const UnitSegs &u, uint32_t nb, const uint64_t *__restrict__ recs, F f) {
+  constexpr int kInFlight = 4;
+  const uint32_t total = u.pref[nb];
+  for (uint32_t r0 = threadIdx.x; r0 < total; r0 += kInFlight * NT) {
+    uint64_t rc[kInFlight];
+    uint32_t base[kInFlight];
+#pragma unroll
+    for (int m = 0; m < kInFlight; ++m) {
+      const uint32_t r = r0 + m * NT;
+      rc[m] = ~0ull;
+      base[m] = 0;
+      if (r < total) {
+        uint32_t lo = 0, hi = nb;  // the last segment whose prefix is <= r
+        while (hi - lo > 1) {
+          const uint32_t mid = (lo + hi) >> 1;
+          if (u.pref[mid] <= r) lo = mid;
+          else hi = mid;
+        }
+        const uint2 sg = u.seg[lo];
+        rc[m] = recs[sg.x + (r - u.pref[lo])];
+        base[m] = sg.y;
+      }
+    }
+#pragma unroll
+    for (int m = 0; m < kInFlight; ++m) {
+      if (rc[m] == ~0ull) continue;
+      const uint32_t lo = (uint32_t)rc[m];
+      f((uint32_t)(rc[m] >> 32), (lo >> kRecOffsetBits) & (kTilePx - 1), base[m] + (lo & ((1u << kRecOffsetBits) - 1u)));
+    }
+  }
+}
+
+// Colour sums of the soft z-buffer: two words of two 32-bit sums each (red |
+// green << 32, blue | points << 32), added to without carries between them.
+__device__ inline void add_colour(unsigned long long *sum, uint32_t c) {
+  atomicAdd(&sum[0], (unsigned long long)(c & 255u) | ((unsigned long long)((c >> 8) & 255u) << 32));
+  atomicAdd(&sum[1], (unsigned long long)((c >> 16) & 255u) | (1ull << 32));
+}
+// mean of the summed colours, rounded half up, with the fill mask
+__device__ inline uint32_t mean_colour(uint64_t rg, uint64_t bn) {
+  const uint64_t n = bn >> 32, n2 = 2ull * n;
+  const uint32_t r = (uint32_t)((2ull * (uint32_t)rg + n) / n2);
+  const uint32_t g = (uint32_t)((2ull * (rg >> 32) + n) / n2);
+  const uint32_t b = (uint32_t)((2ull * (uint32_t)bn + n) / n2);
+  return r | (g << 8) | (b << 16) | (1u << 24);
+}
+
 // Units of work, grid-stride: the LDS z-buffer of one tile over the records
-// of up to kSegsPerUnit of its segments.
-__global__ __launch_bounds__(kThreads) void tile_kernel(const uint64_t *__restrict__ recs,
-                                                        const uint4 *__restrict__ segs,
-                                                        const uint32_t *__restrict__ sorted,
-                                                        const uint32_t *__restrict__ tile_off,
-                                                        const uint32_t *__restrict__ tile_units,
-                                                        const uint2 *__restrict__ units,
-                                                        const uint32_t *__restrict__ counters, TileGrid tg,
-                                                        const uint32_t *__restrict__ rgbx, uint32_t W, uint32_t H,
-                                                        uint64_t *__restrict__ key, float *__restrict__ depth,
-                                                        uint32_t *__restrict__ rgba) {
+// of up to kSegsPerUnit of its segments.  SOFT: a tile of one unit then goes
+// over its records again and sums the colours of the points within one_plus_eps
+// of their pixel's nearest depth (in LDS: the sums never go to memory).
+template <int NT, bool SOFT>
+__global__ __launch_bounds__(NT) void tile_kernel(const uint64_t *__restrict__ recs, const uint4 *__restrict__ segs,
+                                                  const uint32_t *__restrict__ sorted,
+                                                  const uint32_t *__restrict__ tile_off,
+                                                  const uint32_t *__restrict__ tile_units,
+                                                  const uint2 *__restrict__ units,
+                                                  const uint32_t *__restrict__ counters, TileGrid tg,
+                                                  const uint32_t *__restrict__ rgbx, uint32_t W, uint32_t H,
+                                                  uint64_t *__restrict__ key, float *__restrict__ depth,
+                                                  uint32_t *__restrict__ rgba, float one_plus_eps) {
   __shared__ unsigned long long zb[kTilePx];
-  __shared__ uint32_t s_pref[kSegsPerUnit + 1];
-  __shared__ uint2 s_seg[kSegsPerUnit];  // first record, work item start
+  __shared__ unsigned long long sums[SOFT ? 2 * kTilePx : 1];
+  __shared__ UnitSegs us;
   const int tid = threadIdx.x;
   const uint32_t n_units = counters[kUnitsWord];
   for (uint32_t u = blockIdx.x; u < n_units; u += gridDim.x) {
@@ -828,58 +1031,27 @@ __global__ __launch_bounds__(kThreads) void tile_kernel(const uint64_t *__restri
     const uint32_t t = un.x;
     const uint32_t beg = tile_off[t] + un.y, end = min(tile_off[t + 1], beg + kSegsPerUnit);
     const uint32_t nb = end > beg ? end - beg : 0u;
-    for (int p = tid; p < kTilePx; p += kThreads) zb[p] = ~0ull;
-    if (tid < 64) {  // the unit's segments and the prefix of their record counts (one wave)
-      uint32_t c = 0;
-      if ((uint32_t)tid < nb) {
-        const uint4 sg = segs[sorted[beg + tid]];
-        s_seg[tid] = make_uint2(sg.y, sg.w);
-        c = sg.z;
-      }
-      uint32_t incl = c;
-#pragma unroll
-      for (int off = 1; off < 64; off <<= 1) {
-        const uint32_t o = __shfl_up(incl, off, 64);
-        if (tid >= off) incl += o;
-      }
-      if (tid <= kSegsPerUnit) s_pref[tid] = incl - c;  // s_pref[nb] = total
-    }
-    __syncthreads();
-    const uint32_t total = s_pref[nb];
-    // kInFlight records per thread: their loads are issued before the first
-    // LDS atomic, so their latencies overlap
-    constexpr int kInFlight = 4;
-    for (uint32_t r0 = tid; r0 < total; r0 += kInFlight * kThreads) {
-      uint64_t rc[kInFlight];
-      uint32_t base[kInFlight];
-#pragma unroll
-      for (int m = 0; m < kInFlight; ++m) {
-        const uint32_t r = r0 + m * kThreads;
-        rc[m] = ~0ull;
-        base[m] = 0;
-        if (r < total) {
-          uint32_t lo = 0, hi = nb;  // the last segment whose prefix is <= r
-          while (hi - lo > 1) {
-            const uint32_t mid = (lo + hi) >> 1;
-            if (s_pref[mid] <= r) lo = mid;
-            else hi = mid;
-          }
-          const uint2 sg = s_seg[lo];
-          rc[m] = recs[sg.x + (r - s_pref[lo])];
-          base[m] = sg.y;
-        }
-      }
-#pragma unroll
-      for (int m = 0; m < kInFlight; ++m) {
-        if (rc[m] == ~0ull) continue;
-        const uint64_t k = (rc[m] & 0xFFFFFFFF00000000ull) | (uint64_t)(base[m] + (uint32_t)(rc[m] & 0xFFFu));
-        atomicMin(&zb[(rc[m] >> 12) & (kTilePx - 1)], (unsigned long long)k);
-      }
-    }
-    __syncthreads();
     const bool alone = tile_units[t] == 1;
+    for (int p = tid; p < kTilePx; p += NT) zb[p] = ~0ull;
+    if constexpr (SOFT)
+      for (int p = tid; p < 2 * kTilePx; p += NT) sums[p] = 0ull;
+    load_unit(us, segs, sorted, beg, nb);
+    __syncthreads();
+    for_records<NT>(us, nb, recs, [&](uint32_t w, uint32_t px, uint32_t j) {
+      atomicMin(&zb[px], ((unsigned long long)w << 32) | j);
+    });
+    __syncthreads();
+    if constexpr (SOFT) {
+      if (alone) {
+        for_records<NT>(us, nb, recs, [&](uint32_t w, uint32_t px, uint32_t j) {
+          const float zmin = __uint_as_float((uint32_t)(zb[px] >> 32));
+          if (__uint_as_float(w) <= zmin * one_plus_eps) add_colour(&sums[2 * px], rgbx[j]);
+        });
+        __syncthreads();
+      }
+    }
     const uint32_t tx = t % tg.tiles_x, ty = t / tg.tiles_x;
-    for (int p = tid; p < kTilePx; p += kThreads) {
+    for (int p = tid; p < kTilePx; p += NT) {
       const uint32_t gx = (tx << kTileShift) + (p & (kTileSide - 1));
       const uint32_t gy = (ty << kTileShift) + (p >> kTileShift);
       if (gx >= W || gy >= H) continue;
@@ -887,7 +1059,12 @@ __global__ __launch_bounds__(kThreads) void tile_kernel(const uint64_t *__restri
       const uint64_t k = zb[p];
       if (alone) {
         key[i] = k;
-        resolve_px(k, rgbx, i, depth, rgba);
+        if constexpr (SOFT) {
+          depth[i] = k == ~0ull ? 0.f : __uint_as_float((uint32_t)(k >> 32));
+          rgba[i] = k == ~0ull ? 0u : mean_colour(sums[2 * p], sums[2 * p + 1]);
+        } else {
+          resolve_px(k, rgbx, i, depth, rgba);
+        }
       } else if (k != ~0ull) {
         atomicMin(reinterpret_cast<unsigned long long *>(key + i), (unsigned long long)k);
       }
@@ -896,10 +1073,66 @@ __global__ __launch_bounds__(kThreads) void tile_kernel(const uint64_t *__restri
   }
 }
 
-// Resolve of the tiles whose units merged through the key buffer.
+// Soft z-buffer of the tiles of more than one unit, once their nearest depths
+// have met in the key buffer: each unit sums its colours in LDS and adds them
+// to the pixels' sums in memory (two 64-bit atomics per pixel and unit).
+template <int NT>
+__global__ __launch_bounds__(NT) void soft_units_kernel(const uint64_t *__restrict__ recs,
+                                                        const uint4 *__restrict__ segs,
+                                                        const uint32_t *__restrict__ sorted,
+                                                        const uint32_t *__restrict__ tile_off,
+                                                        const uint32_t *__restrict__ tile_units,
+                                                        const uint2 *__restrict__ units,
+                                                        const uint32_t *__restrict__ counters, TileGrid tg,
+                                                        const uint32_t *__restrict__ rgbx, uint32_t W, uint32_t H,
+                                                        const uint64_t *__restrict__ key, float one_plus_eps,
+                                                        unsigned long long *__restrict__ acc) {
+  __shared__ unsigned long long sums[2 * kTilePx];
+  __shared__ float zmin[kTilePx];
+  __shared__ UnitSegs us;
+  const int tid = threadIdx.x;
+  const uint32_t n_units = counters[kUnitsWord];
+  for (uint32_t u = blockIdx.x; u < n_units; u += gridDim.x) {
+    const uint2 un = units[u];
+    const uint32_t t = un.x;
+    if (tile_units[t] == 1) continue;  // (the same for the whole block)
+    const uint32_t beg = tile_off[t] + un.y, end = min(tile_off[t + 1], beg + kSegsPerUnit);
+    const uint32_t nb = end > beg ? end - beg : 0u;
+    const uint32_t tx = t % tg.tiles_x, ty = t / tg.tiles_x;
+    auto pixel = [&](int p, size_t *i) {
+      const uint32_t gx = (tx << kTileShift) + (p & (kTileSide - 1));
+      const uint32_t gy = (ty << kTileShift) + (p >> kTileShift);
+      *i = (size_t)gy * W + gx;
+      return gx < W && gy < H;
+    };
+    for (int p = tid; p < kTilePx; p += NT) {
+      size_t i;
+      zmin[p] = pixel(p, &i) ? __uint_as_float((uint32_t)(key[i] >> 32)) : 0.f;
+      sums[2 * p] = sums[2 * p + 1] = 0ull;
+    }
+    load_unit(us, segs, sorted, beg, nb);
+    __syncthreads();
+    for_records<NT>(us, nb, recs, [&](uint32_t w, uint32_t px, uint32_t j) {
+      if (__uint_as_float(w) <= zmin[px] * one_plus_eps) add_colour(&sums[2 * px], rgbx[j]);
+    });
+    __syncthreads();
+    for (int p = tid; p < kTilePx; p += NT) {
+      size_t i;
+      if (pixel(p, &i) && sums[2 * p + 1]) {
+        atomicAdd(&acc[2 * i], sums[2 * p]);
+        atomicAdd(&acc[2 * i + 1], sums[2 * p + 1]);
+      }
+    }
+    __syncthreads();
+  }
+}
+
+// Resolve of the tiles whose units merged through the key buffer (and, with
+// acc, through the colour sums).
 __global__ __launch_bounds__(kThreads) void tileres_kernel(const uint32_t *__restrict__ tile_units, TileGrid tg,
                                                            const uint32_t *__restrict__ rgbx, uint32_t W, uint32_t H,
-                                                           const uint64_t *__restrict__ key, float *__restrict__ depth,
+                                                           const uint64_t *__restrict__ key,
+                                                           const uint64_t *__restrict__ acc, float *__restrict__ depth,
                                                            uint32_t *__restrict__ rgba) {
   const uint32_t t = blockIdx.x;
   if (tile_units[t] == 1) return;
@@ -909,7 +1142,13 @@ __global__ __launch_bounds__(kThreads) void tileres_kernel(const uint32_t *__res
     const uint32_t gy = (ty << kTileShift) + (p >> kTileShift);
     if (gx >= W || gy >= H) continue;
     const size_t i = (size_t)gy * W + gx;
-    resolve_px(key[i], rgbx, i, depth, rgba);
+    const uint64_t k = key[i];
+    if (acc && k != ~0ull) {
+      depth[i] = __uint_as_float((uint32_t)(k >> 32));
+      rgba[i] = mean_colour(acc[2 * i], acc[2 * i + 1]);
+    } else {
+      resolve_px(k, rgbx, i, depth, rgba);
+    }
   }
 }
 
@@ -941,62 +1180,39 @@ __global__ __launch_bounds__(kThreads) void atomic_probe_kernel(uint64_t *__rest
 }
 
 // Soft z-buffer (Method, "Point Cloud Projection": colours of points at similar
-// depths are averaged).  A second pass over the same work items adds the colour
-// of every point whose depth is within (1 + eps) of its pixel's nearest depth
-// into integer sums; integer atomics make the result order independent.
-template <bool DEV>  // DEV: the camera comes from device memory (cam_dev), as in cull_kernel
+// depths are averaged) behind the atomic splat.  A second pass over the same
+// work items adds the colour of every point whose depth is within (1 + eps) of
+// its pixel's nearest depth into integer sums; integer atomics make the result
+// order independent.
 __global__ __launch_bounds__(kThreads) void soft_accum_kernel(const float *__restrict__ xs, const float *__restrict__ ys,
                                                               const float *__restrict__ zs,
                                                               const uint32_t *__restrict__ rgbx,
                                                               const uint2 *__restrict__ chunks, uint32_t cap,
-                                                              const uint32_t *__restrict__ counters, SplatCam cam_val,
-                                                              const SplatCam *__restrict__ cam_dev,
+                                                              const uint32_t *__restrict__ counters, SplatCam cam,
                                                               const uint64_t *__restrict__ key, float one_plus_eps,
-                                                              uint32_t *__restrict__ acc) {
-  const SplatCam &cam = DEV ? *cam_dev : cam_val;
+                                                              unsigned long long *__restrict__ acc) {
   uint2 ch;
   if (!work_item(blockIdx.x, counters, chunks, cap, &ch)) return;
-  const float *P = cam.P;
   for (uint32_t i = threadIdx.x; i < ch.y; i += kThreads) {
     const uint32_t j = ch.x + i;
-    const float x = xs[j], y = ys[j], z = zs[j];
-    const float a = ((P[0] * x + P[1] * y) + P[2] * z) + P[3];
-    const float b = ((P[4] * x + P[5] * y) + P[6] * z) + P[7];
-    const float w = ((P[8] * x + P[9] * y) + P[10] * z) + P[11];
-    if (!(w >= cam.z_near && w <= cam.z_far)) continue;
-    const float u = a / w;
-    const float v = b / w;
-    if (!(u >= 0.f && u < cam.Wf && v >= 0.f && v < cam.Hf)) continue;
-    const size_t p = (size_t)(uint32_t)v * cam.W + (uint32_t)u;
+    uint64_t k;
+    uint32_t px, py;
+    if (!project_point(xs[j], ys[j], zs[j], j, cam, k, px, py)) continue;
+    const size_t p = (size_t)py * cam.W + px;
     const float zmin = __uint_as_float((uint32_t)(key[p] >> 32));
-    if (!(w <= zmin * one_plus_eps)) continue;
-    const uint32_t c = rgbx[j];
-    atomicAdd(&acc[4 * p + 0], c & 255u);
-    atomicAdd(&acc[4 * p + 1], (c >> 8) & 255u);
-    atomicAdd(&acc[4 * p + 2], (c >> 16) & 255u);
-    atomicAdd(&acc[4 * p + 3], 1u);
+    if (__uint_as_float((uint32_t)(k >> 32)) <= zmin * one_plus_eps) add_colour(acc + 2 * p, rgbx[j]);
   }
 }
 
 __global__ __launch_bounds__(kThreads) void resolve_soft_kernel(const uint64_t *__restrict__ key,
-                                                                const uint32_t *__restrict__ acc,
+                                                                const uint64_t *__restrict__ acc,
                                                                 float *__restrict__ depth, uint32_t *__restrict__ rgba,
                                                                 uint32_t npix) {
   const uint32_t stride = gridDim.x * kThreads;
   for (uint32_t i = blockIdx.x * kThreads + threadIdx.x; i < npix; i += stride) {
     const uint64_t k = key[i];
-    if (k == ~0ull) {
-      depth[i] = 0.f;
-      rgba[i] = 0u;
-    } else {
-      depth[i] = __uint_as_float((uint32_t)(k >> 32));
-      const uint4 s = *reinterpret_cast<const uint4 *>(acc + 4ull * i);
-      const uint64_t n2 = 2ull * s.w;
-      const uint32_t r = (uint32_t)((2ull * s.x + s.w) / n2);
-      const uint32_t g = (uint32_t)((2ull * s.y + s.w) / n2);
-      const uint32_t b = (uint32_t)((2ull * s.z + s.w) / n2);
-      rgba[i] = r | (g << 8) | (b << 16) | (1u << 24);
-    }
+    depth[i] = k == ~0ull ? 0.f : __uint_as_float((uint32_t)(k >> 32));
+    rgba[i] = k == ~0ull ? 0u : mean_colour(acc[2ull * i], acc[2ull * i + 1]);
   }
 }
 
@@ -1020,6 +1236,9 @@ __global__ __launch_bounds__(kThreads) void resolve_kernel(const uint64_t *__res
     }
   }
 }
+
+// threads per tile of the soft splat: its records are every drawn point
+constexpr int kSoftThreads = 512;
 
 inline uint32_t grid_for(uint32_t n) {
   uint32_t b = (n + kThreads - 1) / kThreads;
@@ -1050,18 +1269,27 @@ TiledSplatGrid tiled_splat_grid(uint32_t W, uint32_t H, uint32_t n_points) {
 
 hipError_t launch_tiled_splat(const CloudDev &c, const uint2 *chunks, uint32_t *counters, const SplatCam &cam,
                               const SplatCam *cam_dev, uint32_t H, const TiledSplatBufs &b, uint64_t *key,
-                              float *depth, uint32_t *rgba, int stage, hipStream_t s) {
+                              float *depth, uint32_t *rgba, void *acc, float one_plus_eps, int stage,
+                              hipStream_t s) {
   if (c.max_chunks == 0) return hipErrorInvalidValue;  // a loaded cloud has at least one point
   const TiledSplatGrid g = tiled_splat_grid(cam.W, H, c.n);
   const TileGrid tg{g.tiles_x, g.tiles_y, g.n_tiles};
+  const bool soft = acc != nullptr;
+  const uint32_t tile_grid = (uint32_t)std::min<uint64_t>(g.unit_cap, std::max<uint64_t>(2ull * g.n_tiles, 4096));
   switch (stage) {
     case 0:
-      if (cam_dev)
-        bin_kernel<true><<<c.max_chunks, kThreads, 0, s>>>(c.x, c.y, c.z, chunks, c.max_chunks, counters, cam, cam_dev,
-                                                          tg, b.recs, b.segs, b.tile_nseg);
-      else
-        bin_kernel<false><<<c.max_chunks, kThreads, 0, s>>>(c.x, c.y, c.z, chunks, c.max_chunks, counters, cam,
-                                                           nullptr, tg, b.recs, b.segs, b.tile_nseg);
+#define LNR_BIN(NT, DEV, ALL)                                                                                         \
+  bin_kernel<NT, DEV, ALL><<<c.max_items, NT, 0, s>>>(c.x, c.y, c.z, chunks, c.max_chunks, counters, cam, cam_dev,   \
+                                                      tg, b.recs, b.segs, b.tile_nseg)
+#define LNR_BIN_NT(NT)                                                                                                \
+  do {                                                                                                                \
+    if (soft) { if (cam_dev) LNR_BIN(NT, true, true); else LNR_BIN(NT, false, true); }                                \
+    else { if (cam_dev) LNR_BIN(NT, true, false); else LNR_BIN(NT, false, false); }                                   \
+  } while (0)
+      if (c.item_points == kBinDense) LNR_BIN_NT(512);
+      else LNR_BIN_NT(256);
+#undef LNR_BIN_NT
+#undef LNR_BIN
       break;
     case 1:
       if (tiled_scan_merged(g)) return hipSuccess;  // taken by the segment sort
@@ -1072,19 +1300,30 @@ hipError_t launch_tiled_splat(const CloudDev &c, const uint2 *chunks, uint32_t *
       if (tiled_scan_merged(g))
         segscan_kernel<<<256, kThreads, 0, s>>>(b.segs, counters, b.tile_nseg, b.tile_nseg + g.n_tiles, b.tile_off,
                                                 b.tile_units, b.units, (uint32_t)g.unit_cap, b.sorted, tg, cam.W, H,
-                                                key);
+                                                key, static_cast<uint4 *>(acc));
       else
         segsort_kernel<<<1024, kThreads, 0, s>>>(b.segs, counters, b.tile_off, b.tile_nseg, b.sorted, b.tile_units,
-                                                  tg, cam.W, H, key);
+                                                  tg, cam.W, H, key, static_cast<uint4 *>(acc));
       break;
-    case 3: {
-      const uint64_t grid = std::min<uint64_t>(g.unit_cap, std::max<uint64_t>(2ull * g.n_tiles, 4096));
-      tile_kernel<<<(uint32_t)grid, kThreads, 0, s>>>(b.recs, b.segs, b.sorted, b.tile_off, b.tile_units, b.units,
-                                                      counters, tg, c.rgbx, cam.W, H, key, depth, rgba);
+    case 3:
+      if (soft)
+        tile_kernel<kSoftThreads, true><<<tile_grid, kSoftThreads, 0, s>>>(b.recs, b.segs, b.sorted, b.tile_off,
+                                                                           b.tile_units, b.units, counters, tg, c.rgbx,
+                                                                           cam.W, H, key, depth, rgba, one_plus_eps);
+      else
+        tile_kernel<kThreads, false><<<tile_grid, kThreads, 0, s>>>(b.recs, b.segs, b.sorted, b.tile_off, b.tile_units,
+                                                                    b.units, counters, tg, c.rgbx, cam.W, H, key, depth,
+                                                                    rgba, 1.f);
       break;
-    }
     case 4:
-      tileres_kernel<<<g.n_tiles, kThreads, 0, s>>>(b.tile_units, tg, c.rgbx, cam.W, H, key, depth, rgba);
+      if (soft)
+        soft_units_kernel<kSoftThreads><<<tile_grid, kSoftThreads, 0, s>>>(
+            b.recs, b.segs, b.sorted, b.tile_off, b.tile_units, b.units, counters, tg, c.rgbx, cam.W, H, key,
+            one_plus_eps, static_cast<unsigned long long *>(acc));
+      break;
+    case 5:
+      tileres_kernel<<<g.n_tiles, kThreads, 0, s>>>(b.tile_units, tg, c.rgbx, cam.W, H, key,
+                                                    static_cast<const uint64_t *>(acc), depth, rgba);
       break;
     default:
       return hipErrorInvalidValue;
@@ -1093,14 +1332,14 @@ hipError_t launch_tiled_splat(const CloudDev &c, const uint2 *chunks, uint32_t *
 }
 
 hipError_t launch_cull(const CloudDev &c, const CullParams &prm, const CullParams *prm_dev, uint8_t *flags,
-                       uint2 *chunks, uint32_t *counters, hipStream_t s) {
+                       uint2 *chunks, uint32_t chunk, uint32_t *counters, hipStream_t s) {
   const uint32_t nb = (c.n_cells + kThreads - 1) / kThreads;
   if (prm_dev)
     cull_kernel<true><<<nb, kThreads, 0, s>>>(c.aabb, c.cell_start, c.n_cells, prm, prm_dev, flags, chunks,
-                                              c.max_chunks, counters);
+                                              c.max_chunks, chunk, counters);
   else
     cull_kernel<false><<<nb, kThreads, 0, s>>>(c.aabb, c.cell_start, c.n_cells, prm, nullptr, flags, chunks,
-                                               c.max_chunks, counters);
+                                               c.max_chunks, chunk, counters);
   return hipGetLastError();
 }
 
@@ -1146,19 +1385,13 @@ hipError_t launch_resolve(const uint64_t *key, const uint32_t *rgbx, float *dept
 }
 
 hipError_t launch_soft(const CloudDev &c, const uint2 *chunks, const uint32_t *counters, const SplatCam &cam,
-                       const SplatCam *cam_dev, const uint64_t *key, float one_plus_eps, uint32_t *acc, float *depth,
-                       uint32_t *rgba, uint32_t npix, hipStream_t s) {
-  clear_acc_kernel<<<grid_for(npix), kThreads, 0, s>>>(reinterpret_cast<uint4 *>(acc), npix);
+                       const uint64_t *key, float one_plus_eps, void *acc, float *depth, uint32_t *rgba, uint32_t npix,
+                       hipStream_t s) {
+  clear_acc_kernel<<<grid_for(npix), kThreads, 0, s>>>(static_cast<uint4 *>(acc), npix);
   if (c.max_chunks)
-  {
-    if (cam_dev)
-      soft_accum_kernel<true><<<c.max_chunks, kThreads, 0, s>>>(c.x, c.y, c.z, c.rgbx, chunks, c.max_chunks, counters,
-                                                               cam, cam_dev, key, one_plus_eps, acc);
-    else
-      soft_accum_kernel<false><<<c.max_chunks, kThreads, 0, s>>>(c.x, c.y, c.z, c.rgbx, chunks, c.max_chunks,
-                                                                counters, cam, nullptr, key, one_plus_eps, acc);
-  }
-  resolve_soft_kernel<<<grid_for(npix), kThreads, 0, s>>>(key, acc, depth, rgba, npix);
+    soft_accum_kernel<<<c.max_chunks, kThreads, 0, s>>>(c.x, c.y, c.z, c.rgbx, chunks, c.max_chunks, counters, cam, key,
+                                                       one_plus_eps, static_cast<unsigned long long *>(acc));
+  resolve_soft_kernel<<<grid_for(npix), kThreads, 0, s>>>(key, static_cast<const uint64_t *>(acc), depth, rgba, npix);
   return hipGetLastError();
 }
 
