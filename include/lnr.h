@@ -168,8 +168,8 @@ void lnr_cloud_destroy(lnr_cloud *c);
  * culling never changes the image.  out->key, depth and rgba must all be
  * non-NULL with out->width/height equal to the camera's.  flags: 0 or any of
  * LNR_RENDER_NO_CULL, LNR_RENDER_ATOMIC_SPLAT, LNR_RENDER_COUNT_ATOMICS (see
- * above; the image is the same).  The tiled splat takes 28 bytes of context
- * scratch per point of the cloud. */
+ * above; the image is the same).  The tiled splat takes up to 28 bytes of
+ * context scratch per point of the cloud. */
 lnr_status lnr_render(lnr_context *ctx, const lnr_cloud *c, const lnr_camera *cam, lnr_image *out, uint32_t flags,
                       void *hip_stream);
 /* Render with the soft z-buffer of Method, "Point Cloud Projection" (colours of
@@ -193,14 +193,17 @@ lnr_status lnr_render_soft(lnr_context *ctx, const lnr_cloud *c, const lnr_camer
  *                may overlap (LNR_E_INVALID_ARG).
  *   n_views    : 1..1024.  The views go in passes of up to 8: a pass culls
  *                every grid cell against each of its views' frustums, and
- *                the points of a cell visible in any of them are loaded once
- *                and drawn into each view whose frustum the cell meets.
- *   flags      : 0 or LNR_RENDER_NO_CULL.  The z-buffers are the images' key
- *                buffers, lowered with 64-bit atomicMin after an on-chip
- *                z-buffer per work item (LNR_RENDER_ATOMIC_SPLAT's method):
- *                the screen-tiled splat would need its per-point scratch
- *                once per view.
- * Uses 16 bytes of context scratch per work item and depth bucket.
+ *                the points of a cell visible in any of them are drawn into
+ *                each view whose frustum the cell meets.
+ *   flags      : 0 or LNR_RENDER_NO_CULL.
+ * A pass is the screen-tiled splat of all its views in the same launches.  Its
+ * scratch is lnr_render's once per view, so a pass takes as many views as fit
+ * in 6 GiB of scratch, the context's budget and a quarter of the free device
+ * memory.  Where the budget does not hold even one view's, the z-buffers are
+ * the images' key buffers, lowered with 64-bit atomicMin after an on-chip
+ * z-buffer per work item (LNR_RENDER_ATOMIC_SPLAT's method), and a pass loads
+ * each point once.  Uses 16 bytes of context scratch per work item and depth
+ * bucket besides.
  * lnr_render_stats then reports the last pass: cells visible in at least one
  * of its views, and the points of those cells, each read once.  Errors as
  * lnr_render, checked for every view before anything is enqueued. */

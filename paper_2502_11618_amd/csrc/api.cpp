@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <array>
 #include <deque>
 #include <map>
 #include <tuple>
@@ -711,24 +712,71 @@ void lnr_cloud_destroy(lnr_cloud *c) {
 // ---------------------------------------------------------------------------
 // render
 // ---------------------------------------------------------------------------
-// scratch of the tiled splat for a cloud of n_points points and grid g (see TiledSplatGrid)
-static lnr_status ensure_tiled(lnr_context *ctx, Scratch &scr, const TiledSplatGrid &g, uint32_t n_points) {
-  const size_t n = std::max<uint32_t>(1, n_points);
-  lnr_status st;
-  if ((st = ensure(ctx, scr.recs, 8 * n)) != LNR_OK || (st = ensure(ctx, scr.segs, 16 * n)) != LNR_OK ||
-      (st = ensure(ctx, scr.sorted, 4 * n)) != LNR_OK || (st = ensure(ctx, scr.tile_nseg, 8ull * g.n_tiles)) != LNR_OK ||
-      (st = ensure(ctx, scr.tile_off, 4ull * g.n_tiles + 4)) != LNR_OK ||
-      (st = ensure(ctx, scr.tile_units, 4ull * g.n_tiles)) != LNR_OK ||
-      (st = ensure(ctx, scr.units, 8ull * g.unit_cap)) != LNR_OK)
-    return st;
+// Scratch of the tiled splat for n_views views at once of a cloud of n_points
+// points, sized for grid g (the largest view's, see TiledSplatGrid): bytes of
+// each buffer, in the order below.
+static std::array<Buf *, 7> tiled_scratch(Scratch &scr) {
+  return {&scr.recs, &scr.segs, &scr.sorted, &scr.tile_nseg, &scr.tile_off, &scr.tile_units, &scr.units};
+}
+static std::array<size_t, 7> tiled_bytes(const TiledSplatGrid &g, uint32_t n_points, int n_views) {
+  const size_t n = std::max<uint32_t>(1, n_points), v = (size_t)n_views;
+  return {8 * n * v, 16 * g.seg_cap * v, 4 * g.seg_cap * v, 8ull * g.n_tiles * v, (4ull * g.n_tiles + 4) * v, 4ull * g.n_tiles * v,
+          8ull * g.unit_cap * v};
+}
+static lnr_status ensure_tiled(lnr_context *ctx, Scratch &scr, const TiledSplatGrid &g, uint32_t n_points,
+                               int n_views = 1) {
+  const auto bufs = tiled_scratch(scr);
+  const auto need = tiled_bytes(g, n_points, n_views);
+  for (size_t i = 0; i < bufs.size(); ++i) {
+    const lnr_status st = ensure(ctx, *bufs[i], need[i]);
+    if (st != LNR_OK) return st;
+  }
   return LNR_OK;
 }
+// the part of view v
+static TiledSplatBufs tiled_bufs(Scratch &scr, const TiledSplatGrid &g, uint32_t n_points, size_t v = 0) {
+  const size_t n = std::max<uint32_t>(1, n_points);
+  return TiledSplatBufs{static_cast<uint64_t *>(scr.recs.p) + v * n,
+                        static_cast<uint4 *>(scr.segs.p) + v * g.seg_cap,
+                        static_cast<uint32_t *>(scr.sorted.p) + v * g.seg_cap,
+                        static_cast<uint32_t *>(scr.tile_nseg.p) + v * 2 * g.n_tiles,
+                        static_cast<uint32_t *>(scr.tile_off.p) + v * (g.n_tiles + 1),
+                        static_cast<uint32_t *>(scr.tile_units.p) + v * g.n_tiles,
+                        static_cast<uint2 *>(scr.units.p) + v * g.unit_cap};
+}
 
-static TiledSplatBufs tiled_bufs(Scratch &scr) {
-  return TiledSplatBufs{static_cast<uint64_t *>(scr.recs.p),       static_cast<uint4 *>(scr.segs.p),
-                        static_cast<uint32_t *>(scr.sorted.p),     static_cast<uint32_t *>(scr.tile_nseg.p),
-                        static_cast<uint32_t *>(scr.tile_off.p),   static_cast<uint32_t *>(scr.tile_units.p),
-                        static_cast<uint2 *>(scr.units.p)};
+// How many of n views the tiled splat takes at once: all of them while their
+// scratch stays within kViewsScratch (more per launch fills the chip better,
+// but the scratch is 28 bytes per point and view), the budget, and a quarter of
+// the device memory still free; shared out evenly over the passes.  0: not even
+// one view's scratch fits the budget.
+constexpr size_t kViewsScratch = 6ull << 30;
+static int tiled_views_at_once(lnr_context *ctx, Scratch &scr, const TiledSplatGrid &g, uint32_t n_points, int n) {
+  const auto bufs = tiled_scratch(scr);
+  size_t held = 0;
+  for (Buf *b : bufs) held += b->p ? b->cap : 0;
+  size_t free_bytes = 0, total_bytes = 0;
+  bool asked = false;
+  for (int v = std::min(n, kViewsPerPass); v >= 1; --v) {
+    const auto need = tiled_bytes(g, n_points, v);
+    size_t sum = 0, more = 0;
+    for (size_t i = 0; i < bufs.size(); ++i) {
+      sum += need[i];
+      if (!bufs[i]->p || bufs[i]->cap < need[i]) more += need[i];
+    }
+    if (more) {
+      if (ctx->budget && ctx->allocated - std::min<uint64_t>(ctx->allocated, held) + sum > ctx->budget) continue;
+      if (v > 1) {
+        if (sum > kViewsScratch) continue;
+        if (!asked && hipMemGetInfo(&free_bytes, &total_bytes) != hipSuccess) free_bytes = 0;
+        asked = true;
+        if (more > free_bytes / 4) continue;
+      }
+    }
+    const int passes = (n + v - 1) / v;
+    return (n + passes - 1) / passes;
+  }
+  return 0;
 }
 
 static SplatCam make_splat_cam(const lnr_camera *cam) {
@@ -783,16 +831,16 @@ static lnr_status render_impl(lnr_context *ctx, Scratch &scr, const lnr_cloud *c
   const SplatCam sc = make_splat_cam(cam);
   const bool count = (flags & LNR_RENDER_COUNT_ATOMICS) != 0;
   const bool atomic = count || (flags & LNR_RENDER_ATOMIC_SPLAT) != 0;
-  const TiledSplatGrid tg = tiled_splat_grid((uint32_t)cam->width, (uint32_t)cam->height, c->d.n);
+  const TiledSplatGrid tg = tiled_splat_grid((uint32_t)cam->width, (uint32_t)cam->height, c->d);
   // every allocation comes before the first launch: a failure leaves the image untouched
   if (!atomic && (st = ensure_tiled(ctx, scr, tg, c->d.n)) != LNR_OK) return st;
   if (soft && (st = ensure(ctx, scr.soft_acc, 16ull * npix)) != LNR_OK) return st;
-  const TiledSplatBufs tb = tiled_bufs(scr);
   if (dev && atomic) return fail(ctx, LNR_E_INVALID_ARG, "a camera in device memory needs the tiled splat");
   // (the tiled splat writes every key itself: its segment sort empties the
   // keys of the tiles that merge through atomics, so only the counters here)
   LNR_LAUNCH(ctx, "clear", s,
-             launch_clear(out->key, atomic ? npix : 0u, counters, tb.tile_nseg, atomic ? 0u : 2 * tg.n_tiles, s));
+             launch_clear(out->key, atomic ? npix : 0u, counters, kCounterWords,
+                          static_cast<uint32_t *>(scr.tile_nseg.p), atomic ? 0u : 2 * tg.n_tiles, s));
   LNR_LAUNCH(ctx, "cull", s,
              launch_cull(c->d, prm, dev ? &dev->cull : nullptr, static_cast<uint8_t *>(scr.flags.p),
                          static_cast<uint2 *>(scr.chunks.p), atomic ? kSplatChunk : c->d.item_points, counters,
@@ -804,13 +852,13 @@ static lnr_status render_impl(lnr_context *ctx, Scratch &scr, const lnr_cloud *c
     if (!soft) LNR_LAUNCH(ctx, "resolve", s, launch_resolve(out->key, c->d.rgbx, out->depth, rgba32, npix, s));
   } else {
     static const char *const names[6] = {"bin", "tilescan", "segsort", "tile", "soft", "tileres"};
-    const bool merged = tiled_scan_merged(tg);  // the scan runs inside the segment sort
+    const TiledSplatView view{sc, dev ? &dev->splat : nullptr, (uint32_t)cam->height, tiled_bufs(scr, tg, c->d.n),
+                              counters, out->key, out->depth, rgba32, soft ? scr.soft_acc.p : nullptr};
+    const bool merged = tiled_scan_merged(&view, 1);  // the scan runs inside the segment sort
     for (int stage = 0; stage < 6; ++stage)
       if (!(merged && stage == 1) && !(!soft && stage == 4))
         LNR_LAUNCH(ctx, names[stage], s,
-                   launch_tiled_splat(c->d, chunks, counters, sc, dev ? &dev->splat : nullptr, (uint32_t)cam->height,
-                                      tb, out->key, out->depth, rgba32, soft ? scr.soft_acc.p : nullptr,
-                                      1.0f + soft_eps, stage, s));
+                   launch_tiled_splat(c->d, chunks, counters, view, 1.0f + soft_eps, stage, s));
   }
   if (soft && atomic)
     LNR_LAUNCH(ctx, "soft", s,
@@ -820,6 +868,47 @@ static lnr_status render_impl(lnr_context *ctx, Scratch &scr, const lnr_cloud *c
   ctx->rendered = true;
   ctx->counted = count;
   ctx->last_cells = c->d.n_cells;
+  return LNR_OK;
+}
+
+// the largest grid of n cameras
+static TiledSplatGrid largest_grid(const lnr_cloud *c, const lnr_camera *cams, int n) {
+  TiledSplatGrid g;
+  for (int v = 0; v < n; ++v) {
+    const TiledSplatGrid w = tiled_splat_grid((uint32_t)cams[v].width, (uint32_t)cams[v].height, c->d);
+    if (w.n_tiles > g.n_tiles) g = w;
+  }
+  return g;
+}
+
+// Up to kViewsPerPass views (n) in the same launches of the tiled splat, whose
+// scratch (flags, views, counters, and the tiled splat's for n views of grid g)
+// is there.  dev (may be nullptr): the views' cameras in device memory.
+static lnr_status render_tiled_views(lnr_context *ctx, Scratch &scr, const lnr_cloud *c, const lnr_camera *cams,
+                                     const lnr_image *outs, int n, const TiledSplatGrid &g, bool no_cull,
+                                     hipStream_t s, const DevCam *dev) {
+  uint32_t *counters = static_cast<uint32_t *>(scr.counters.p);
+  uint4 *items = static_cast<uint4 *>(scr.views.p);
+  ViewsCull vc{};
+  vc.n = n;
+  TiledSplatView views[kViewsPerPass];
+  for (int v = 0; v < n; ++v) {
+    if (!dev) vc.v[v] = make_cull_params(&cams[v], no_cull);
+    views[v] = TiledSplatView{make_splat_cam(&cams[v]), dev ? &dev[v].splat : nullptr, (uint32_t)cams[v].height,
+                              tiled_bufs(scr, g, c->d.n, (size_t)v), counters + (size_t)v * kViewCounterWords,
+                              outs[v].key, outs[v].depth, reinterpret_cast<uint32_t *>(outs[v].rgba), nullptr};
+  }
+  LNR_LAUNCH(ctx, "clear", s,
+             launch_clear(nullptr, 0u, counters, (uint32_t)(n * kViewCounterWords),
+                          static_cast<uint32_t *>(scr.tile_nseg.p), 2 * g.n_tiles * (uint32_t)n, s));
+  LNR_LAUNCH(ctx, "cull_views", s,
+             launch_cull_views(c->d, vc, dev, static_cast<uint8_t *>(scr.flags.p), items, c->d.item_points, counters,
+                               s));
+  static const char *const names[6] = {"bin", "tilescan", "segsort", "tile", "soft", "tileres"};
+  const bool merged = tiled_scan_merged(views, n);
+  for (int stage = 0; stage < 6; ++stage)
+    if (!(merged && stage == 1) && stage != 4)
+      LNR_LAUNCH(ctx, names[stage], s, launch_tiled_views(c->d, items, counters, views, n, stage, s));
   return LNR_OK;
 }
 
@@ -869,10 +958,25 @@ lnr_status lnr_render_views(lnr_context *ctx, const lnr_cloud *c, const lnr_came
   if ((st = ensure(ctx, scr.flags, c->d.n_cells)) != LNR_OK) return st;
   if ((st = ensure(ctx, scr.views, 16ull * kDepthBuckets * std::max<uint32_t>(1, c->d.max_chunks))) != LNR_OK)
     return st;
-  if ((st = ensure(ctx, scr.counters, 4 * kCounterWords)) != LNR_OK) return st;
+  if ((st = ensure(ctx, scr.counters, 4 * kViewCounterWords * kViewsPerPass)) != LNR_OK) return st;
   uint32_t *counters = static_cast<uint32_t *>(scr.counters.p);
   uint4 *items = static_cast<uint4 *>(scr.views.p);
   const bool no_cull = (flags & LNR_RENDER_NO_CULL) != 0;
+  const TiledSplatGrid grid = largest_grid(c, cams, n_views);
+  const int at_once = tiled_views_at_once(ctx, scr, grid, c->d.n, std::min(n_views, kViewsPerPass));
+  if (at_once > 0) {
+    if ((st = ensure_tiled(ctx, scr, grid, c->d.n, at_once)) != LNR_OK) return st;
+    for (int g = 0; g < n_views; g += at_once)
+      if ((st = render_tiled_views(ctx, scr, c, cams + g, outs + g, std::min(at_once, n_views - g), grid, no_cull, s,
+                                   nullptr)) != LNR_OK)
+        return st;
+    ctx->last_stream = s;
+    ctx->rendered = true;
+    ctx->counted = false;
+    ctx->last_cells = c->d.n_cells;
+    return LNR_OK;
+  }
+  // the tiled splat's scratch does not fit the budget: z-buffers in device memory
   for (int g = 0; g < n_views; g += kViewsPerPass) {
     const int n = std::min(kViewsPerPass, n_views - g);
     ViewsCull vc{};
@@ -885,10 +989,11 @@ lnr_status lnr_render_views(lnr_context *ctx, const lnr_cloud *c, const lnr_came
       vs.cam[v] = make_splat_cam(cam);
       vs.key[v] = o.key;
       LNR_LAUNCH(ctx, "clear", s,
-                 launch_clear(o.key, (uint32_t)o.width * (uint32_t)o.height, counters, nullptr, 0u, s));
+                 launch_clear(o.key, (uint32_t)o.width * (uint32_t)o.height, counters, kCounterWords, nullptr, 0u, s));
     }
     LNR_LAUNCH(ctx, "cull_views", s,
-               launch_cull_views(c->d, vc, static_cast<uint8_t *>(scr.flags.p), items, counters, s));
+               launch_cull_views(c->d, vc, nullptr, static_cast<uint8_t *>(scr.flags.p), items, kSplatChunk, counters,
+                                 s));
     LNR_LAUNCH(ctx, "splat_views", s, launch_splat_views(c->d, items, counters, vs, s));
     for (int v = 0; v < n; ++v) {
       const lnr_image &o = outs[g + v];
@@ -975,8 +1080,10 @@ lnr_status lnr_measure_atomic_min(lnr_context *ctx, uint64_t n_slots, int32_t pa
 // ---------------------------------------------------------------------------
 // fixed: the allocation-free entry point's per-device array (nullptr: the
 // context's grow-only scratch)
+// batch images of io's size, px_stride pixels apart, in the same launches
 static lnr_status depth_filter_impl(lnr_context *ctx, Scratch &scr, lnr_image *io, int32_t n_levels,
-                                    float filter_strength, void *hip_stream, float *fixed = nullptr);
+                                    float filter_strength, void *hip_stream, float *fixed = nullptr, int batch = 1,
+                                    size_t px_stride = 0);
 
 lnr_status lnr_depth_filter(lnr_context *ctx, lnr_image *io, int32_t n_levels, float filter_strength,
                             void *hip_stream) {
@@ -993,7 +1100,8 @@ lnr_status lnr_depth_filter_noalloc(lnr_context *ctx, lnr_image *io, int32_t n_l
 }
 
 static lnr_status depth_filter_impl(lnr_context *ctx, Scratch &scr, lnr_image *io, int32_t n_levels,
-                                    float filter_strength, void *hip_stream, float *fixed) {
+                                    float filter_strength, void *hip_stream, float *fixed, int batch,
+                                    size_t px_stride) {
   if (!ctx) return LNR_E_INVALID_ARG;
   if (!io || !io->depth || !io->rgba) return fail(ctx, LNR_E_INVALID_ARG, "NULL pointer argument");
   if (io->width < 1 || io->height < 1 || io->width > 16384 || io->height > 16384)
@@ -1030,7 +1138,7 @@ static lnr_status depth_filter_impl(lnr_context *ctx, Scratch &scr, lnr_image *i
                       " bytes of the allocation-free filter's scratch");
     base = reinterpret_cast<char *>(fixed);
   } else {
-    if ((st = ensure(ctx, scr.pyramid, total)) != LNR_OK) return st;
+    if ((st = ensure(ctx, scr.pyramid, total * (size_t)batch)) != LNR_OK) return st;
     base = static_cast<char *>(scr.pyramid.p);
   }
   float *D[32] = {nullptr};
@@ -1040,14 +1148,15 @@ static lnr_status depth_filter_impl(lnr_context *ctx, Scratch &scr, lnr_image *i
   if (fixed) {
     // no timing events either: nothing is created or allocated on this path
     (void)hipGetLastError();
-    LNR_HIP(ctx, launch_pyramid(io->depth, rgba, io->height, io->width, n_levels, D, s));
+    LNR_HIP(ctx, launch_pyramid(io->depth, rgba, io->height, io->width, n_levels, D, 1, 0, 0, s));
     LNR_HIP(ctx, launch_upsample_fused(n_levels, D, Hs, Ws, io->depth, rgba, filter_strength,
-                                       1.0f + filter_strength, s));
+                                       1.0f + filter_strength, 1, 0, 0, s));
   } else {
-    LNR_LAUNCH(ctx, "pyramid", s, launch_pyramid(io->depth, rgba, io->height, io->width, n_levels, D, s));
+    LNR_LAUNCH(ctx, "pyramid", s,
+               launch_pyramid(io->depth, rgba, io->height, io->width, n_levels, D, batch, px_stride, total / 4, s));
     LNR_LAUNCH(ctx, "upsample", s,
                launch_upsample_fused(n_levels, D, Hs, Ws, io->depth, rgba, filter_strength, 1.0f + filter_strength,
-                                     s));
+                                     batch, px_stride, total / 4, s));
   }
   ctx->last_stream = s;
   return LNR_OK;
@@ -1379,6 +1488,7 @@ struct ServerLane {
   // max_batch slots each, slot b at pixel b * slot_px of every plane
   void *slot_buf = nullptr;
   size_t slot_bytes = 0, slot_px = 0;
+  int views = 1;  // slots the (hard) tiled splat renders at once
   // one graph per (height, width, batch): every launch of a whole batch
   std::map<std::tuple<int, int, int>, hipGraphExec_t> graphs;
   std::vector<hipGraph_t> graph_defs;
@@ -1506,9 +1616,9 @@ lnr_status lnr_server_create(lnr_context *ctx, const lnr_cloud *c, const lnr_une
     }
     if ((st = ensure(ctx, l.sc.flags, c->d.n_cells)) != LNR_OK ||
         (st = ensure(ctx, l.sc.chunks, 8ull * kDepthBuckets * std::max<uint32_t>(1, c->d.max_chunks))) != LNR_OK ||
-        (st = ensure(ctx, l.sc.counters, 4 * kCounterWords)) != LNR_OK || (st = ensure(ctx, l.sc.pyramid, pyr)) != LNR_OK ||
-        (st = ensure(ctx, l.sc.act, act)) != LNR_OK ||
-        (st = ensure_tiled(ctx, l.sc, tiled_splat_grid((uint32_t)mW, (uint32_t)mH, c->d.n), c->d.n)) != LNR_OK ||
+        (st = ensure(ctx, l.sc.counters, 4 * kViewCounterWords * kViewsPerPass)) != LNR_OK ||
+        (st = ensure(ctx, l.sc.pyramid, pyr)) != LNR_OK || (st = ensure(ctx, l.sc.act, act)) != LNR_OK ||
+        (st = ensure_tiled(ctx, l.sc, tiled_splat_grid((uint32_t)mW, (uint32_t)mH, c->d), c->d.n)) != LNR_OK ||
         (cfg->soft && (st = ensure(ctx, l.sc.soft_acc, 16 * npix)) != LNR_OK) ||
         (st = dalloc(ctx, (void **)&l.head_outs_dev, 8ull * 16)) != LNR_OK ||
         (st = dalloc(ctx, (void **)&l.cams_dev, sizeof(DevCam) * 16)) != LNR_OK ||
@@ -1518,6 +1628,31 @@ lnr_status lnr_server_create(lnr_context *ctx, const lnr_cloud *c, const lnr_une
     }
     l.slot_bytes = slot_bytes;
     l.slot_px = slot_px;
+  }
+  // More scratch for several slots per launch.  A budget is for sessions: under
+  // one, a lane takes no more in all than 28 bytes per point and a 16-channel
+  // input tensor of the batch, so that this refuses no session.
+  if (!cfg->soft && cfg->max_batch > 1) {
+    const TiledSplatGrid g = tiled_splat_grid((uint32_t)mW, (uint32_t)mH, c->d);
+    const size_t most = 28ull * c->d.n + npix * (u->prec == Prec::F32 ? 32 : u->prec == Prec::BF16X3 ? 64 : 32) *
+                                             (size_t)cfg->max_batch;
+    for (auto &l : srv->lanes) {
+      int v = tiled_views_at_once(ctx, l.sc, g, c->d.n, std::min(cfg->max_batch, kViewsPerPass));
+      auto needs = [&](int n) {
+        size_t sum = 16ull * kDepthBuckets * std::max<uint32_t>(1, c->d.max_chunks) + pyr * (size_t)(n - 1);
+        for (size_t b : tiled_bytes(g, c->d.n, n)) sum += b;
+        return sum;
+      };
+      while (v > 1 && ctx->budget && needs(v) > most) --v;
+      if (v <= 1) continue;
+      if ((st = ensure(ctx, l.sc.views, 16ull * kDepthBuckets * std::max<uint32_t>(1, c->d.max_chunks))) != LNR_OK ||
+          (st = ensure(ctx, l.sc.pyramid, pyr * (size_t)v)) != LNR_OK ||
+          (st = ensure_tiled(ctx, l.sc, g, c->d.n, v)) != LNR_OK) {
+        server_release(srv.get());
+        return st;
+      }
+      l.views = v;
+    }
   }
   ++ctx->children;
   *out = srv.release();
@@ -1687,15 +1822,30 @@ lnr_status lnr_server_step(lnr_server *srv, int32_t *launched) {
   char *slots = static_cast<char *>(lane->slot_buf);
   const size_t sp = lane->slot_px, mb = (size_t)srv->cfg.max_batch;
   auto enqueue = [&]() -> lnr_status {
-    for (int b = 0; b < B; ++b) {
-      const ServerSession &ss = srv->sessions[batch[b]];
-      lnr_image img{reinterpret_cast<uint64_t *>(slots) + (size_t)b * sp,
-                    reinterpret_cast<float *>(slots + 8 * sp * mb) + (size_t)b * sp,
-                    reinterpret_cast<uint8_t *>(slots + 12 * sp * mb) + 4 * (size_t)b * sp, W, H};
-      lnr_status r = render_impl(ctx, lane->sc, srv->cloud, &ss.cam, &img, 0, srv->cfg.soft != 0,
-                                 srv->cfg.soft_eps, s, lane->cams_dev + b);
+    auto slot = [&](int b) {
+      return lnr_image{reinterpret_cast<uint64_t *>(slots) + (size_t)b * sp,
+                       reinterpret_cast<float *>(slots + 8 * sp * mb) + (size_t)b * sp,
+                       reinterpret_cast<uint8_t *>(slots + 12 * sp * mb) + 4 * (size_t)b * sp, W, H};
+    };
+    const int at_once = B > 1 ? lane->views : 1;
+    for (int b = 0; b < B; b += at_once) {
+      const int n = std::min(at_once, B - b);
+      lnr_image img[kViewsPerPass];
+      lnr_camera cams[kViewsPerPass];
+      for (int v = 0; v < n; ++v) {
+        img[v] = slot(b + v);
+        cams[v] = srv->sessions[batch[b + v]].cam;
+      }
+      lnr_status r;
+      if (n > 1) {
+        const TiledSplatGrid g = tiled_splat_grid((uint32_t)W, (uint32_t)H, srv->cloud->d);
+        r = render_tiled_views(ctx, lane->sc, srv->cloud, cams, img, n, g, false, s, lane->cams_dev + b);
+      } else {
+        r = render_impl(ctx, lane->sc, srv->cloud, &cams[0], &img[0], 0, srv->cfg.soft != 0, srv->cfg.soft_eps, s,
+                        lane->cams_dev + b);
+      }
       if (r == LNR_OK && srv->cfg.n_levels > 0)
-        r = depth_filter_impl(ctx, lane->sc, &img, srv->cfg.n_levels, srv->cfg.filter_strength, s);
+        r = depth_filter_impl(ctx, lane->sc, &img[0], srv->cfg.n_levels, srv->cfg.filter_strength, s, nullptr, n, sp);
       if (r != LNR_OK) return r;
     }
     return unet_convs(ctx, lane->sc, srv->unet, lay, nullptr, lane->head_outs_dev, s,

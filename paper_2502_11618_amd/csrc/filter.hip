@@ -33,8 +33,17 @@ __device__ inline float d0_at(const float *__restrict__ depth, const uint32_t *_
 template <bool FROM_IMAGE>
 __global__ __launch_bounds__(256) void pyramid_kernel(const float *__restrict__ src, const float *__restrict__ depth,
                                                       const uint32_t *__restrict__ rgba, int sH, int sW, int nl,
-                                                      float *o1, float *o2, float *o3, float *o4, float *o5) {
+                                                      float *o1, float *o2, float *o3, float *o4, float *o5,
+                                                      size_t px_stride, size_t level_stride) {
   __shared__ float t[16][17];
+  // image blockIdx.z of a batch: its pixels and its levels
+  if (FROM_IMAGE) {
+    depth += blockIdx.z * px_stride;
+    rgba += blockIdx.z * px_stride;
+  } else {
+    src += blockIdx.z * level_stride;
+  }
+  o1 += blockIdx.z * level_stride;
   const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
   int H = (sH + 1) >> 1, W = (sW + 1) >> 1;
   int X = blockIdx.x * 16 + tx, Y = blockIdx.y * 16 + ty;
@@ -64,7 +73,7 @@ __global__ __launch_bounds__(256) void pyramid_kernel(const float *__restrict__ 
       v = fminf(fminf(t[2 * ty][2 * tx], t[2 * ty][2 * tx + 1]), fminf(t[2 * ty + 1][2 * tx], t[2 * ty + 1][2 * tx + 1]));
       X = blockIdx.x * side + tx;
       Y = blockIdx.y * side + ty;
-      if (Y < H && X < W) outs[l - 1][(size_t)Y * W + X] = v;
+      if (Y < H && X < W) outs[l - 1][blockIdx.z * level_stride + (size_t)Y * W + X] = v;
     }
     __syncthreads();
     if (ty < side && tx < side) t[ty][tx] = v;
@@ -143,7 +152,11 @@ struct LevelPtrs {
 
 __global__ __launch_bounds__(kTileThreads) void upsample_fused_kernel(LevelPtrs lv, int n, float *__restrict__ depth,
                                                                       uint32_t *__restrict__ rgba, float fs,
-                                                                      float one_plus_fs) {
+                                                                      float one_plus_fs, size_t px_stride,
+                                                                      size_t level_stride) {
+  depth += blockIdx.z * px_stride;  // image blockIdx.z of a batch
+  rgba += blockIdx.z * px_stride;
+  const size_t lv0 = blockIdx.z * level_stride;
   __shared__ float sD[kPool], sU[kPool];
   // the chain of regions and their LDS offsets (in LDS: a private array
   // indexed by the level would live in scratch memory)
@@ -185,7 +198,7 @@ __global__ __launch_bounds__(kTileThreads) void upsample_fused_kernel(LevelPtrs 
     const int rw = g.c1 - g.c0, cnt = (g.r1 - g.r0) * rw, st = kSide[k];
     for (int i = t; i < cnt; i += kTileThreads) {
       const int y = i / rw, x = i - y * rw;
-      sD[off[k] + y * st + x] = lv.D[k][(size_t)(g.r0 + y) * lv.W[k] + g.c0 + x];
+      sD[off[k] + y * st + x] = lv.D[k][lv0 + (size_t)(g.r0 + y) * lv.W[k] + g.c0 + x];
     }
   }
   __syncthreads();
@@ -240,20 +253,21 @@ __global__ __launch_bounds__(kTileThreads) void upsample_fused_kernel(LevelPtrs 
 }  // namespace
 
 hipError_t launch_pyramid(const float *depth, const uint32_t *rgba, int H, int W, int n, float *const *levels,
-                          hipStream_t s) {
+                          int batch, size_t px_stride, size_t level_stride, hipStream_t s) {
   // levels[k] for k = 1..n are the min-pooled images; levels[0] is unused
   int sH = H, sW = W, k0 = 0;
   while (k0 < n) {
     const int nl = (n - k0) < 5 ? (n - k0) : 5;
     const int H1 = (sH + 1) >> 1, W1 = (sW + 1) >> 1;
-    dim3 grid((W1 + 15) / 16, (H1 + 15) / 16);
+    dim3 grid((W1 + 15) / 16, (H1 + 15) / 16, batch);
     float *o[5];
     for (int l = 0; l < 5; ++l) o[l] = (l < nl) ? levels[k0 + 1 + l] : nullptr;
     if (k0 == 0)
-      pyramid_kernel<true><<<grid, 256, 0, s>>>(nullptr, depth, rgba, sH, sW, nl, o[0], o[1], o[2], o[3], o[4]);
+      pyramid_kernel<true><<<grid, 256, 0, s>>>(nullptr, depth, rgba, sH, sW, nl, o[0], o[1], o[2], o[3], o[4],
+                                               px_stride, level_stride);
     else
       pyramid_kernel<false><<<grid, 256, 0, s>>>(levels[k0], nullptr, nullptr, sH, sW, nl, o[0], o[1], o[2], o[3],
-                                                 o[4]);
+                                                 o[4], px_stride, level_stride);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     for (int l = 0; l < nl; ++l) {
@@ -266,7 +280,8 @@ hipError_t launch_pyramid(const float *depth, const uint32_t *rgba, int H, int W
 }
 
 hipError_t launch_upsample_fused(int n, const float *const *D, const int *Hs, const int *Ws, float *depth,
-                                 uint32_t *rgba, float fs, float one_plus_fs, hipStream_t s) {
+                                 uint32_t *rgba, float fs, float one_plus_fs, int batch, size_t px_stride,
+                                 size_t level_stride, hipStream_t s) {
   if (n < 1 || n > kMaxLevels) return hipErrorInvalidValue;
   LevelPtrs lv{};
   for (int k = 0; k <= n; ++k) {
@@ -274,8 +289,8 @@ hipError_t launch_upsample_fused(int n, const float *const *D, const int *Hs, co
     lv.H[k] = Hs[k];
     lv.W[k] = Ws[k];
   }
-  dim3 grid((Ws[0] + kTile - 1) / kTile, (Hs[0] + kTile - 1) / kTile);
-  upsample_fused_kernel<<<grid, kTileThreads, 0, s>>>(lv, n, depth, rgba, fs, one_plus_fs);
+  dim3 grid((Ws[0] + kTile - 1) / kTile, (Hs[0] + kTile - 1) / kTile, batch);
+  upsample_fused_kernel<<<grid, kTileThreads, 0, s>>>(lv, n, depth, rgba, fs, one_plus_fs, px_stride, level_stride);
   return hipGetLastError();
 }
 

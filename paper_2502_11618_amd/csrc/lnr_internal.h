@@ -92,6 +92,8 @@ constexpr int kAtomicWord = 4 + kDepthBuckets;
 constexpr int kSegTopWord = kAtomicWord + 1;
 constexpr int kUnitsWord = kSegTopWord + 1;
 constexpr int kCounterWords = kUnitsWord + 1;
+constexpr int kViewCounterWords = 64;  // counters of view v of a multi-view render start at word 64 v
+static_assert(kCounterWords <= kViewCounterWords, "a view's counters");
 
 // ----------------------------------------------------------------------------
 // kernel launchers (each returns hipGetLastError() of its launches)
@@ -119,28 +121,24 @@ hipError_t launch_cell_aabb(const float *x, const float *y, const float *z, cons
 hipError_t launch_chunk_count(const uint32_t *cell_start, uint32_t n_cells, uint32_t *total, hipStream_t s);
 
 // render.hip
-// per-frame reset of the key buffer (npix words), the counters and the tiled
-// splat's per-tile segment counts (n_tiles words)
-hipError_t launch_clear(uint64_t *key, uint32_t npix, uint32_t *counters, uint32_t *tile_nseg, uint32_t n_tiles,
-                        hipStream_t s);
+// per-frame reset of the key buffer (npix words), n_counters words of the
+// counters and n_tiles words of the tiled splat's per-tile segment counts
+hipError_t launch_clear(uint64_t *key, uint32_t npix, uint32_t *counters, uint32_t n_counters, uint32_t *tile_nseg,
+                        uint32_t n_tiles, hipStream_t s);
 // Screen-tiled splat (32 x 32 pixel tiles), in up to six launches (stage
 // 0..5: bin, tilescan, segsort, tile, soft, tileres; stage 1 launches nothing
 // when tiled_scan_merged(), the segment sort then taking the scan; stage 4
 // only for the soft z-buffer).  Scratch per
 // render for a cloud of n points: recs u64[n] (a work item's records at its
-// points' positions), segs uint4[n] and sorted u32[n] (at most one segment
-// per record), tile_nseg u32[2 n_tiles] (the counts, then the merged sort's
+// points' positions), segs uint4[seg_cap] and sorted u32[seg_cap] (at most one
+// segment per record, and one per work item and tile), tile_nseg u32[2 n_tiles] (the counts, then the merged sort's
 // fill counters), tile_units u32[n_tiles], tile_off u32[n_tiles + 1], units
 // uint2[unit_cap].
 struct TiledSplatGrid {
   uint32_t tiles_x = 0, tiles_y = 0, n_tiles = 0;
-  uint64_t unit_cap = 0;
+  uint64_t seg_cap = 0, unit_cap = 0;
 };
-TiledSplatGrid tiled_splat_grid(uint32_t W, uint32_t H, uint32_t n_points);
-// true when the per-tile scan runs inside the segment sort (stage 1 then
-// launches nothing); tile_nseg then holds 2 n_tiles words: the counts, then
-// the fill counters of the sort, both zeroed by launch_clear
-bool tiled_scan_merged(const TiledSplatGrid &g);
+TiledSplatGrid tiled_splat_grid(uint32_t W, uint32_t H, const CloudDev &c);
 struct TiledSplatBufs {
   uint64_t *recs;
   uint4 *segs;
@@ -150,13 +148,32 @@ struct TiledSplatBufs {
   uint32_t *tile_units;
   uint2 *units;
 };
-// acc (nullptr: the hard z-buffer): 16 bytes of colour sums per pixel.
-// cam_dev / prm_dev (may be nullptr): the same camera in device memory, read by
-// the kernels instead of the by-value copy (graph replays with new cameras)
-hipError_t launch_tiled_splat(const CloudDev &c, const uint2 *chunks, uint32_t *counters, const SplatCam &cam,
-                              const SplatCam *cam_dev, uint32_t H, const TiledSplatBufs &b, uint64_t *key,
-                              float *depth, uint32_t *rgba, void *acc, float one_plus_eps, int stage,
-                              hipStream_t s);
+// One view of a tiled splat: its camera (cam_dev, may be nullptr: the same
+// camera in device memory, read by the kernels instead: graph replays with new
+// cameras), scratch, counters (kSegTopWord and kUnitsWord of this view) and
+// image.  acc (nullptr: the hard z-buffer): 16 bytes of colour sums per pixel.
+struct TiledSplatView {
+  SplatCam cam;
+  const SplatCam *cam_dev;
+  uint32_t H;
+  TiledSplatBufs b;
+  uint32_t *counters;
+  uint64_t *key;
+  float *depth;
+  uint32_t *rgba;
+  void *acc;
+};
+// true when the per-tile scan runs inside the segment sort (stage 1 then
+// launches nothing); tile_nseg then holds 2 n_tiles words: the counts, then
+// the fill counters of the sort, both zeroed by launch_clear
+bool tiled_scan_merged(const TiledSplatView *views, int n);
+// work: the counters of the culling pass
+hipError_t launch_tiled_splat(const CloudDev &c, const uint2 *chunks, const uint32_t *work, const TiledSplatView &view,
+                              float one_plus_eps, int stage, hipStream_t s);
+// up to kViewsPerPass views in the same launches (hard z-buffer); items as
+// launch_cull_views queues them
+hipError_t launch_tiled_views(const CloudDev &c, const uint4 *items, const uint32_t *work, const TiledSplatView *views,
+                              int n, int stage, hipStream_t s);
 hipError_t launch_cull(const CloudDev &c, const CullParams &prm, const CullParams *prm_dev, uint8_t *flags,
                        uint2 *chunks, uint32_t chunk, uint32_t *counters, hipStream_t s);
 // the atomic splat (global z-buffer); count_atomics: also add the number of
@@ -164,10 +181,11 @@ hipError_t launch_cull(const CloudDev &c, const CullParams &prm, const CullParam
 hipError_t launch_splat(const CloudDev &c, const uint2 *chunks, uint32_t *counters, const SplatCam &cam,
                         uint64_t *key, bool count_atomics, hipStream_t s);
 // several views in one pass: work items (start, count, view mask, 0) queued
-// as launch_cull queues its chunks, then one splat that reads each work
-// item's points once for all the views of its mask
-hipError_t launch_cull_views(const CloudDev &c, const ViewsCull &prm, uint8_t *flags, uint4 *items, uint32_t *counters,
-                             hipStream_t s);
+// as launch_cull queues its chunks (dev: the views' cameras in device memory,
+// or nullptr); and the atomic splat that reads each work item's points once
+// for all the views of its mask
+hipError_t launch_cull_views(const CloudDev &c, const ViewsCull &prm, const DevCam *dev, uint8_t *flags, uint4 *items,
+                             uint32_t chunk, uint32_t *counters, hipStream_t s);
 hipError_t launch_splat_views(const CloudDev &c, const uint4 *items, const uint32_t *counters, const ViewsSplat &vs,
                               hipStream_t s);
 // throughput probe: grid x 256 threads x iters 64-bit atomicMin on buf[n_slots]
@@ -183,9 +201,9 @@ hipError_t launch_soft(const CloudDev &c, const uint2 *chunks, const uint32_t *c
                        const uint64_t *key, float one_plus_eps, void *acc, float *depth, uint32_t *rgba, uint32_t npix,
                        hipStream_t s);
 
-// filter.hip
+// filter.hip: batch images px_stride pixels apart, their levels level_stride floats apart
 hipError_t launch_pyramid(const float *depth, const uint32_t *rgba, int H, int W, int n, float *const *levels,
-                          hipStream_t s);
+                          int batch, size_t px_stride, size_t level_stride, hipStream_t s);
 // allocation-free filter: floats in the per-device scratch array (16 MiB), and
 // its device address on the current device
 constexpr size_t kNoAllocScratchFloats = size_t(4) << 20;
@@ -193,7 +211,8 @@ hipError_t noalloc_scratch_address(float **ptr);
 // every upsampling level in one launch (1 <= n <= 15); D[1..n] min-pooled levels,
 // Hs/Ws[0..n] level sizes; removes the rejected pixels of depth/rgba in place
 hipError_t launch_upsample_fused(int n, const float *const *D, const int *Hs, const int *Ws, float *depth,
-                                 uint32_t *rgba, float fs, float one_plus_fs, hipStream_t s);
+                                 uint32_t *rgba, float fs, float one_plus_fs, int batch, size_t px_stride,
+                                 size_t level_stride, hipStream_t s);
 
 // unet.hip
 // values equal the public lnr_precision ones

@@ -23,15 +23,16 @@ namespace {
 
 constexpr int kThreads = 256;
 
-// Per-frame reset: the key buffer (npix words), the render counters and the
-// tiled splat's per-tile segment counts (n_tiles words, may be 0).
+// Per-frame reset: the key buffer (npix words), n_counters words of the render
+// counters and n_tiles words of per-tile segment counts (may be 0).
 __global__ __launch_bounds__(kThreads) void clear_kernel(uint64_t *__restrict__ key, uint32_t npix,
-                                                         uint32_t *__restrict__ counters,
+                                                         uint32_t *__restrict__ counters, uint32_t n_counters,
                                                          uint32_t *__restrict__ tile_nseg, uint32_t n_tiles) {
   const uint32_t stride = gridDim.x * kThreads;
   for (uint32_t i = blockIdx.x * kThreads + threadIdx.x; i < npix; i += stride) key[i] = ~0ull;
   for (uint32_t i = blockIdx.x * kThreads + threadIdx.x; i < n_tiles; i += stride) tile_nseg[i] = 0u;
-  if (blockIdx.x == 0 && threadIdx.x < kCounterWords) counters[threadIdx.x] = 0;
+  if (blockIdx.x == 0)
+    for (uint32_t i = threadIdx.x; i < n_counters; i += kThreads) counters[i] = 0;
 }
 
 // Conservative visibility of a cell's box [lo, hi] for one camera: the box is
@@ -174,14 +175,17 @@ __global__ __launch_bounds__(kThreads) void cull_kernel(const float *__restrict_
   add_totals(vis, nch, cnt, counters);
 }
 
-// Several views at once: a cell is tested against every view's frustum, and
+// Several views at once (dev: their cameras in device memory, or nullptr): a
+// cell is tested against every view's frustum, and
 // its work items carry the mask of the views that see it (bit v = view v) and
 // go to the queue of the nearest of those views' depth buckets.
 __global__ __launch_bounds__(kThreads) void cull_views_kernel(const float *__restrict__ aabb,
                                                               const uint32_t *__restrict__ cell_start,
                                                               uint32_t n_cells, ViewsCull prm,
+                                                              const DevCam *__restrict__ dev,
                                                               uint8_t *__restrict__ flags, uint4 *__restrict__ items,
-                                                              uint32_t cap, uint32_t *__restrict__ counters) {
+                                                              uint32_t cap, uint32_t chunk,
+                                                              uint32_t *__restrict__ counters) {
   const uint32_t c = blockIdx.x * kThreads + threadIdx.x;
   uint32_t start = 0, cnt = 0, mask = 0;
   int bucket = kDepthBuckets - 1;
@@ -193,7 +197,7 @@ __global__ __launch_bounds__(kThreads) void cull_views_kernel(const float *__res
       const double hi0 = aabb[6ull * c + 3], hi1 = aabb[6ull * c + 4], hi2 = aabb[6ull * c + 5];
       for (int v = 0; v < prm.n; ++v) {
         int b = 0;
-        if (cell_visible(prm.v[v], lo0, lo1, lo2, hi0, hi1, hi2, &b)) {
+        if (cell_visible(dev ? dev[v].cull : prm.v[v], lo0, lo1, lo2, hi0, hi1, hi2, &b)) {
           mask |= 1u << v;
           bucket = min(bucket, b);
         }
@@ -202,11 +206,11 @@ __global__ __launch_bounds__(kThreads) void cull_views_kernel(const float *__res
     flags[c] = mask ? 1 : 0;
   }
   const bool vis = mask != 0;
-  const uint32_t nch = vis ? (cnt + kSplatChunk - 1) / kSplatChunk : 0u;
+  const uint32_t nch = vis ? (cnt + chunk - 1) / chunk : 0u;
   const uint32_t pos = reserve_places(nch, bucket, counters);
   for (uint32_t k = 0; k < nch; ++k) {
-    const uint32_t off = k * kSplatChunk;
-    items[(size_t)bucket * cap + pos + k] = make_uint4(start + off, min(kSplatChunk, cnt - off), mask, 0u);
+    const uint32_t off = k * chunk;
+    items[(size_t)bucket * cap + pos + k] = make_uint4(start + off, min(chunk, cnt - off), mask, 0u);
   }
   add_totals(vis, nch, cnt, counters);
 }
@@ -553,6 +557,32 @@ struct TileGrid {
   uint32_t tiles_x, tiles_y, n_tiles;
 };
 
+// One view of a tiled render, and the NV views of a launch (blockIdx.y).
+struct TiledView {
+  SplatCam cam;
+  const SplatCam *cam_dev;  // the camera in device memory instead (graph replays with new cameras), or nullptr
+  uint32_t W, H, unit_cap;
+  TileGrid tg;
+  uint32_t *counters;  // kSegTopWord, kUnitsWord
+  uint64_t *recs;
+  uint4 *segs;
+  uint32_t *sorted, *tile_nseg, *tile_off, *tile_units;
+  uint2 *units;
+  uint64_t *key;
+  float *depth;
+  uint32_t *rgba;
+  uint4 *acc;  // colour sums of the soft z-buffer, or nullptr
+};
+template <int NV>
+struct TiledViews {
+  TiledView v[NV];
+};
+static_assert(sizeof(TiledViews<kViewsPerPass>) + 64 <= 4096, "kernel arguments stay within 4 KB");
+template <int NV>
+__device__ inline const TiledView &this_view(const TiledViews<NV> &vs) {
+  return vs.v[NV == 1 ? 0 : blockIdx.y];
+}
+
 // A frame's work items.  Clouds with dense cells (kDenseItem points per item or
 // more) take items of up to 8 K points in workgroups of 512 threads: one on-chip
 // z-buffer then meets twice the points of a cell, over twice the pixels, so
@@ -563,15 +593,21 @@ struct BinItem {
   static constexpr int kBlocks = NT >= 512 ? 128 : 64;   // 8 x 8 pixel blocks of the on-chip z-buffer
 };
 
-// DEV: the camera comes from device memory (cam_dev), as in cull_kernel.  ALL:
-// every drawn point is an entry (the soft z-buffer sums them all).
-template <int NT, bool DEV, bool ALL>
-__global__ __launch_bounds__(NT, 4) void bin_kernel(
-    const float *__restrict__ xs, const float *__restrict__ ys, const float *__restrict__ zs,
-    const uint2 *__restrict__ chunks, uint32_t cap, uint32_t *__restrict__ counters, SplatCam cam_val,
-    const SplatCam *__restrict__ cam_dev, TileGrid tg, uint64_t *__restrict__ recs, uint4 *__restrict__ segs,
-    uint32_t *__restrict__ tile_nseg) {
-  const SplatCam &cam = DEV ? *cam_dev : cam_val;
+// Item: uint2 (start, count); of several views uint4 (start, count, mask of the
+// views that see it).  ALL: every drawn point is an entry (the soft z-buffer
+// sums them all).  work: the culling counters.
+template <int NT, int NV, bool ALL>
+__global__ __launch_bounds__(NT, 4) void bin_kernel(const float *__restrict__ xs, const float *__restrict__ ys,
+                                                    const float *__restrict__ zs, const void *__restrict__ items,
+                                                    uint32_t cap, const uint32_t *__restrict__ work,
+                                                    TiledViews<NV> vs) {
+  const TiledView &a = this_view(vs);
+  const SplatCam cam = a.cam_dev ? *a.cam_dev : a.cam;
+  const TileGrid tg = a.tg;
+  uint32_t *__restrict__ counters = a.counters;
+  uint64_t *__restrict__ recs = a.recs;
+  uint4 *__restrict__ segs = a.segs;
+  uint32_t *__restrict__ tile_nseg = a.tile_nseg;
   constexpr int kBlocks = BinItem<NT>::kBlocks, kWaves = NT / 64, kPts = 16;
   constexpr int kZb = ALL ? kHistBins / 2 : kBlocks * 64;
   __shared__ unsigned long long s_zb[kZb];  // z-buffer; or the tile histogram
@@ -582,7 +618,14 @@ __global__ __launch_bounds__(NT, 4) void bin_kernel(
   uint32_t *s_hist = reinterpret_cast<uint32_t *>(s_zb);
   static_assert(kHistBins * 4 <= (int)sizeof(s_zb), "the histogram lies where the z-buffer is");
   uint2 ch;
-  if (!work_item(blockIdx.x, counters, chunks, cap, &ch)) return;
+  if constexpr (NV == 1) {
+    if (!work_item(blockIdx.x, work, static_cast<const uint2 *>(items), cap, &ch)) return;
+  } else {
+    uint4 it;
+    if (!work_item(blockIdx.x, work, static_cast<const uint4 *>(items), cap, &it)) return;
+    if (!((it.z >> blockIdx.y) & 1u)) return;
+    ch = make_uint2(it.x, it.y);
+  }
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   ch.x = (uint32_t)__builtin_amdgcn_readfirstlane((int)ch.x);
   ch.y = (uint32_t)__builtin_amdgcn_readfirstlane((int)ch.y);
@@ -593,6 +636,11 @@ __global__ __launch_bounds__(NT, 4) void bin_kernel(
   // (groups of four points, so that the loads of all sixteen are not held at once)
 #pragma unroll
   for (int g = 0; g < kPts; g += 4) {
+    if ((uint32_t)(g * NT) >= ch.y) {  // (the same for the whole block)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) wb[g + q] = 0u, pix[g + q] = ~0u;
+      continue;
+    }
     float x[4], y[4], z[4];
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
@@ -779,11 +827,15 @@ __global__ __launch_bounds__(NT, 4) void bin_kernel(
 // kSegsPerUnit)) units (tile_units[t]); units[u] = (tile, first segment of
 // the unit within the tile); counters[kUnitsWord] = number of units.
 constexpr int kScanThreads = 1024;
-__global__ __launch_bounds__(kScanThreads) void tilescan_kernel(const uint32_t *__restrict__ tile_nseg, TileGrid tg,
-                                                                uint32_t *__restrict__ tile_off,
-                                                                uint32_t *__restrict__ tile_units,
-                                                                uint2 *__restrict__ units, uint32_t unit_cap,
-                                                                uint32_t *__restrict__ counters) {
+template <int NV>
+__global__ __launch_bounds__(kScanThreads) void tilescan_kernel(TiledViews<NV> vs) {
+  const TiledView &a = this_view(vs);
+  const uint32_t *__restrict__ tile_nseg = a.tile_nseg;
+  const TileGrid tg = a.tg;
+  uint32_t *__restrict__ tile_off = a.tile_off, *__restrict__ tile_units = a.tile_units;
+  uint2 *__restrict__ units = a.units;
+  const uint32_t unit_cap = a.unit_cap;
+  uint32_t *__restrict__ counters = a.counters;
   __shared__ uint32_t s_tmp[kScanThreads / 64];
   const int tid = threadIdx.x;
   uint32_t seg_base = 0, unit_base = 0;
@@ -815,14 +867,17 @@ __global__ __launch_bounds__(kScanThreads) void tilescan_kernel(const uint32_t *
 // key buffer over the tiles of more than one unit, whose units merge into it
 // with atomicMin (the tile kernel writes every other tile's keys whole), and
 // zeroes their colour sums (acc, the soft z-buffer).
-__global__ __launch_bounds__(kThreads) void segsort_kernel(const uint4 *__restrict__ segs,
-                                                           const uint32_t *__restrict__ counters,
-                                                           const uint32_t *__restrict__ tile_off,
-                                                           uint32_t *__restrict__ tile_nseg,
-                                                           uint32_t *__restrict__ sorted,
-                                                           const uint32_t *__restrict__ tile_units, TileGrid tg,
-                                                           uint32_t W, uint32_t H, uint64_t *__restrict__ key,
-                                                           uint4 *__restrict__ acc) {
+template <int NV>
+__global__ __launch_bounds__(kThreads) void segsort_kernel(TiledViews<NV> vs) {
+  const TiledView &a = this_view(vs);
+  const uint4 *__restrict__ segs = a.segs;
+  const uint32_t *__restrict__ counters = a.counters, *__restrict__ tile_off = a.tile_off;
+  const uint32_t *__restrict__ tile_units = a.tile_units;
+  uint32_t *__restrict__ tile_nseg = a.tile_nseg, *__restrict__ sorted = a.sorted;
+  const TileGrid tg = a.tg;
+  const uint32_t W = a.W, H = a.H;
+  uint64_t *__restrict__ key = a.key;
+  uint4 *__restrict__ acc = a.acc;
   const uint32_t n = counters[kSegTopWord];
   for (uint32_t i = blockIdx.x * kThreads + threadIdx.x; i < n; i += gridDim.x * kThreads) {
     const uint32_t t = segs[i].x;
@@ -853,16 +908,19 @@ __global__ __launch_bounds__(kThreads) void segsort_kernel(const uint4 *__restri
 // workgroup's scan.  Then, as segsort_kernel: the segment ids grouped by tile,
 // and the keys of the tiles of more than one unit emptied.
 constexpr uint32_t kMaxScanTiles = 8192;
-__global__ __launch_bounds__(kThreads) void segscan_kernel(const uint4 *__restrict__ segs,
-                                                           uint32_t *__restrict__ counters,
-                                                           const uint32_t *__restrict__ tile_nseg,
-                                                           uint32_t *__restrict__ tile_fill,
-                                                           uint32_t *__restrict__ tile_off,
-                                                           uint32_t *__restrict__ tile_units,
-                                                           uint2 *__restrict__ units, uint32_t unit_cap,
-                                                           uint32_t *__restrict__ sorted, TileGrid tg, uint32_t W,
-                                                           uint32_t H, uint64_t *__restrict__ key,
-                                                           uint4 *__restrict__ acc) {
+template <int NV>
+__global__ __launch_bounds__(kThreads) void segscan_kernel(TiledViews<NV> vs) {
+  const TiledView &a = this_view(vs);
+  const uint4 *__restrict__ segs = a.segs;
+  uint32_t *__restrict__ counters = a.counters;
+  const TileGrid tg = a.tg;
+  const uint32_t *__restrict__ tile_nseg = a.tile_nseg;
+  uint32_t *__restrict__ tile_fill = a.tile_nseg + tg.n_tiles, *__restrict__ tile_off = a.tile_off;
+  uint32_t *__restrict__ tile_units = a.tile_units, *__restrict__ sorted = a.sorted;
+  uint2 *__restrict__ units = a.units;
+  const uint32_t unit_cap = a.unit_cap, W = a.W, H = a.H;
+  uint64_t *__restrict__ key = a.key;
+  uint4 *__restrict__ acc = a.acc;
   __shared__ uint32_t s_off[kMaxScanTiles + 1];
   __shared__ uint32_t s_tmp[kThreads / 64];
   const int tid = threadIdx.x;
@@ -1011,16 +1069,20 @@ __device__ inline uint32_t mean_colour(uint64_t rg, uint64_t bn) {
 // of up to kSegsPerUnit of its segments.  SOFT: a tile of one unit then goes
 // over its records again and sums the colours of the points within one_plus_eps
 // of their pixel's nearest depth (in LDS: the sums never go to memory).
-template <int NT, bool SOFT>
-__global__ __launch_bounds__(NT) void tile_kernel(const uint64_t *__restrict__ recs, const uint4 *__restrict__ segs,
-                                                  const uint32_t *__restrict__ sorted,
-                                                  const uint32_t *__restrict__ tile_off,
-                                                  const uint32_t *__restrict__ tile_units,
-                                                  const uint2 *__restrict__ units,
-                                                  const uint32_t *__restrict__ counters, TileGrid tg,
-                                                  const uint32_t *__restrict__ rgbx, uint32_t W, uint32_t H,
-                                                  uint64_t *__restrict__ key, float *__restrict__ depth,
-                                                  uint32_t *__restrict__ rgba, float one_plus_eps) {
+template <int NT, int NV, bool SOFT>
+__global__ __launch_bounds__(NT) void tile_kernel(TiledViews<NV> vs, const uint32_t *__restrict__ rgbx,
+                                                  float one_plus_eps) {
+  const TiledView &a = this_view(vs);
+  const uint64_t *__restrict__ recs = a.recs;
+  const uint4 *__restrict__ segs = a.segs;
+  const uint32_t *__restrict__ sorted = a.sorted, *__restrict__ tile_off = a.tile_off;
+  const uint32_t *__restrict__ tile_units = a.tile_units, *__restrict__ counters = a.counters;
+  const uint2 *__restrict__ units = a.units;
+  const TileGrid tg = a.tg;
+  const uint32_t W = a.W, H = a.H;
+  uint64_t *__restrict__ key = a.key;
+  float *__restrict__ depth = a.depth;
+  uint32_t *__restrict__ rgba = a.rgba;
   __shared__ unsigned long long zb[kTilePx];
   __shared__ unsigned long long sums[SOFT ? 2 * kTilePx : 1];
   __shared__ UnitSegs us;
@@ -1077,16 +1139,17 @@ __global__ __launch_bounds__(NT) void tile_kernel(const uint64_t *__restrict__ r
 // have met in the key buffer: each unit sums its colours in LDS and adds them
 // to the pixels' sums in memory (two 64-bit atomics per pixel and unit).
 template <int NT>
-__global__ __launch_bounds__(NT) void soft_units_kernel(const uint64_t *__restrict__ recs,
-                                                        const uint4 *__restrict__ segs,
-                                                        const uint32_t *__restrict__ sorted,
-                                                        const uint32_t *__restrict__ tile_off,
-                                                        const uint32_t *__restrict__ tile_units,
-                                                        const uint2 *__restrict__ units,
-                                                        const uint32_t *__restrict__ counters, TileGrid tg,
-                                                        const uint32_t *__restrict__ rgbx, uint32_t W, uint32_t H,
-                                                        const uint64_t *__restrict__ key, float one_plus_eps,
-                                                        unsigned long long *__restrict__ acc) {
+__global__ __launch_bounds__(NT) void soft_units_kernel(TiledViews<1> vs, const uint32_t *__restrict__ rgbx,
+                                                        float one_plus_eps) {
+  const TiledView &a = vs.v[0];
+  const uint64_t *__restrict__ recs = a.recs, *__restrict__ key = a.key;
+  const uint4 *__restrict__ segs = a.segs;
+  const uint32_t *__restrict__ sorted = a.sorted, *__restrict__ tile_off = a.tile_off;
+  const uint32_t *__restrict__ tile_units = a.tile_units, *__restrict__ counters = a.counters;
+  const uint2 *__restrict__ units = a.units;
+  const TileGrid tg = a.tg;
+  const uint32_t W = a.W, H = a.H;
+  unsigned long long *__restrict__ acc = reinterpret_cast<unsigned long long *>(a.acc);
   __shared__ unsigned long long sums[2 * kTilePx];
   __shared__ float zmin[kTilePx];
   __shared__ UnitSegs us;
@@ -1129,11 +1192,16 @@ __global__ __launch_bounds__(NT) void soft_units_kernel(const uint64_t *__restri
 
 // Resolve of the tiles whose units merged through the key buffer (and, with
 // acc, through the colour sums).
-__global__ __launch_bounds__(kThreads) void tileres_kernel(const uint32_t *__restrict__ tile_units, TileGrid tg,
-                                                           const uint32_t *__restrict__ rgbx, uint32_t W, uint32_t H,
-                                                           const uint64_t *__restrict__ key,
-                                                           const uint64_t *__restrict__ acc, float *__restrict__ depth,
-                                                           uint32_t *__restrict__ rgba) {
+template <int NV>
+__global__ __launch_bounds__(kThreads) void tileres_kernel(TiledViews<NV> vs, const uint32_t *__restrict__ rgbx) {
+  const TiledView &a = this_view(vs);
+  const uint32_t *__restrict__ tile_units = a.tile_units;
+  const TileGrid tg = a.tg;
+  const uint32_t W = a.W, H = a.H;
+  const uint64_t *__restrict__ key = a.key, *__restrict__ acc = reinterpret_cast<const uint64_t *>(a.acc);
+  float *__restrict__ depth = a.depth;
+  uint32_t *__restrict__ rgba = a.rgba;
+  if (NV > 1 && blockIdx.x >= tg.n_tiles) return;
   const uint32_t t = blockIdx.x;
   if (tile_units[t] == 1) return;
   const uint32_t tx = t % tg.tiles_x, ty = t / tg.tiles_x;
@@ -1247,88 +1315,109 @@ inline uint32_t grid_for(uint32_t n) {
 
 }  // namespace
 
-hipError_t launch_clear(uint64_t *key, uint32_t npix, uint32_t *counters, uint32_t *tile_nseg, uint32_t n_tiles,
-                        hipStream_t s) {
-  clear_kernel<<<grid_for(npix > n_tiles ? npix : n_tiles), kThreads, 0, s>>>(key, npix, counters, tile_nseg,
-                                                                             n_tiles);
+hipError_t launch_clear(uint64_t *key, uint32_t npix, uint32_t *counters, uint32_t n_counters, uint32_t *tile_nseg,
+                        uint32_t n_tiles, hipStream_t s) {
+  clear_kernel<<<grid_for(npix > n_tiles ? npix : n_tiles), kThreads, 0, s>>>(key, npix, counters, n_counters,
+                                                                             tile_nseg, n_tiles);
   return hipGetLastError();
 }
 
-bool tiled_scan_merged(const TiledSplatGrid &g) { return g.n_tiles <= kMaxScanTiles; }
-
-TiledSplatGrid tiled_splat_grid(uint32_t W, uint32_t H, uint32_t n_points) {
+TiledSplatGrid tiled_splat_grid(uint32_t W, uint32_t H, const CloudDev &c) {
   TiledSplatGrid g;
   g.tiles_x = (W + kTileSide - 1) >> kTileShift;
   g.tiles_y = (H + kTileSide - 1) >> kTileShift;
   g.n_tiles = g.tiles_x * g.tiles_y;
-  // a tile has max(1, ceil(s / kSegsPerUnit)) units, and there are at most
-  // n_points segments (one record at least each)
-  g.unit_cap = 2ull * g.n_tiles + n_points / kSegsPerUnit + 1;
+  g.seg_cap = std::max<uint64_t>(1, std::min<uint64_t>(c.n, (uint64_t)c.max_items * g.n_tiles));
+  // a tile with s segments has max(1, ceil(s / kSegsPerUnit)) units
+  g.unit_cap = 2ull * g.n_tiles + g.seg_cap / kSegsPerUnit + 1;
   return g;
 }
 
-hipError_t launch_tiled_splat(const CloudDev &c, const uint2 *chunks, uint32_t *counters, const SplatCam &cam,
-                              const SplatCam *cam_dev, uint32_t H, const TiledSplatBufs &b, uint64_t *key,
-                              float *depth, uint32_t *rgba, void *acc, float one_plus_eps, int stage,
-                              hipStream_t s) {
-  if (c.max_chunks == 0) return hipErrorInvalidValue;  // a loaded cloud has at least one point
-  const TiledSplatGrid g = tiled_splat_grid(cam.W, H, c.n);
-  const TileGrid tg{g.tiles_x, g.tiles_y, g.n_tiles};
-  const bool soft = acc != nullptr;
-  const uint32_t tile_grid = (uint32_t)std::min<uint64_t>(g.unit_cap, std::max<uint64_t>(2ull * g.n_tiles, 4096));
+namespace {
+template <int NV>
+hipError_t tiled_stage(const CloudDev &c, const void *items, const uint32_t *work, const TiledSplatView *views, int n,
+                       float one_plus_eps, int stage, hipStream_t s) {
+  TiledViews<NV> vs;
+  uint32_t most_tiles = 0, tile_grid = 0;
+  const bool merged = tiled_scan_merged(views, n);
+  for (int i = 0; i < NV; ++i) {
+    const TiledSplatView &w = views[i < n ? i : 0];
+    const TiledSplatGrid g = tiled_splat_grid(w.cam.W, w.H, c);
+    vs.v[i] = TiledView{w.cam, w.cam_dev, w.cam.W, w.H, (uint32_t)g.unit_cap,
+                        TileGrid{g.tiles_x, g.tiles_y, g.n_tiles}, w.counters, w.b.recs, w.b.segs, w.b.sorted,
+                        w.b.tile_nseg, w.b.tile_off, w.b.tile_units, w.b.units, w.key, w.depth, w.rgba,
+                        static_cast<uint4 *>(w.acc)};
+    most_tiles = std::max(most_tiles, g.n_tiles);
+    tile_grid = std::max(tile_grid,
+                         (uint32_t)std::min<uint64_t>(g.unit_cap, std::max<uint64_t>(2ull * g.n_tiles, 4096)));
+  }
+  const bool soft = views[0].acc != nullptr;
+  const uint32_t ny = (uint32_t)n;
   switch (stage) {
     case 0:
-#define LNR_BIN(NT, DEV, ALL)                                                                                         \
-  bin_kernel<NT, DEV, ALL><<<c.max_items, NT, 0, s>>>(c.x, c.y, c.z, chunks, c.max_chunks, counters, cam, cam_dev,   \
-                                                      tg, b.recs, b.segs, b.tile_nseg)
-#define LNR_BIN_NT(NT)                                                                                                \
-  do {                                                                                                                \
-    if (soft) { if (cam_dev) LNR_BIN(NT, true, true); else LNR_BIN(NT, false, true); }                                \
-    else { if (cam_dev) LNR_BIN(NT, true, false); else LNR_BIN(NT, false, false); }                                   \
-  } while (0)
-      if (c.item_points == kBinDense) LNR_BIN_NT(512);
-      else LNR_BIN_NT(256);
-#undef LNR_BIN_NT
+#define LNR_BIN(NT, ALL)                                                                                              \
+  bin_kernel<NT, NV, ALL><<<dim3(c.max_items, ny), NT, 0, s>>>(c.x, c.y, c.z, items, c.max_chunks, work, vs)
+      if (c.item_points == kBinDense) {
+        if (soft) LNR_BIN(512, true); else LNR_BIN(512, false);
+      } else {
+        if (soft) LNR_BIN(256, true); else LNR_BIN(256, false);
+      }
 #undef LNR_BIN
       break;
     case 1:
-      if (tiled_scan_merged(g)) return hipSuccess;  // taken by the segment sort
-      tilescan_kernel<<<1, kScanThreads, 0, s>>>(b.tile_nseg, tg, b.tile_off, b.tile_units, b.units,
-                                                 (uint32_t)g.unit_cap, counters);
+      if (merged) return hipSuccess;  // taken by the segment sort
+      tilescan_kernel<NV><<<dim3(1, ny), kScanThreads, 0, s>>>(vs);
       break;
     case 2:
-      if (tiled_scan_merged(g))
-        segscan_kernel<<<256, kThreads, 0, s>>>(b.segs, counters, b.tile_nseg, b.tile_nseg + g.n_tiles, b.tile_off,
-                                                b.tile_units, b.units, (uint32_t)g.unit_cap, b.sorted, tg, cam.W, H,
-                                                key, static_cast<uint4 *>(acc));
+      if (merged)
+        segscan_kernel<NV><<<dim3(256, ny), kThreads, 0, s>>>(vs);
       else
-        segsort_kernel<<<1024, kThreads, 0, s>>>(b.segs, counters, b.tile_off, b.tile_nseg, b.sorted, b.tile_units,
-                                                  tg, cam.W, H, key, static_cast<uint4 *>(acc));
+        segsort_kernel<NV><<<dim3(1024, ny), kThreads, 0, s>>>(vs);
       break;
     case 3:
-      if (soft)
-        tile_kernel<kSoftThreads, true><<<tile_grid, kSoftThreads, 0, s>>>(b.recs, b.segs, b.sorted, b.tile_off,
-                                                                           b.tile_units, b.units, counters, tg, c.rgbx,
-                                                                           cam.W, H, key, depth, rgba, one_plus_eps);
-      else
-        tile_kernel<kThreads, false><<<tile_grid, kThreads, 0, s>>>(b.recs, b.segs, b.sorted, b.tile_off, b.tile_units,
-                                                                    b.units, counters, tg, c.rgbx, cam.W, H, key, depth,
-                                                                    rgba, 1.f);
+      if constexpr (NV == 1) {
+        if (soft) {
+          tile_kernel<kSoftThreads, 1, true><<<tile_grid, kSoftThreads, 0, s>>>(vs, c.rgbx, one_plus_eps);
+          break;
+        }
+      }
+      tile_kernel<kThreads, NV, false><<<dim3(tile_grid, ny), kThreads, 0, s>>>(vs, c.rgbx, 1.f);
       break;
     case 4:
-      if (soft)
-        soft_units_kernel<kSoftThreads><<<tile_grid, kSoftThreads, 0, s>>>(
-            b.recs, b.segs, b.sorted, b.tile_off, b.tile_units, b.units, counters, tg, c.rgbx, cam.W, H, key,
-            one_plus_eps, static_cast<unsigned long long *>(acc));
+      if constexpr (NV == 1) {
+        if (soft) soft_units_kernel<kSoftThreads><<<tile_grid, kSoftThreads, 0, s>>>(vs, c.rgbx, one_plus_eps);
+      }
       break;
     case 5:
-      tileres_kernel<<<g.n_tiles, kThreads, 0, s>>>(b.tile_units, tg, c.rgbx, cam.W, H, key,
-                                                    static_cast<const uint64_t *>(acc), depth, rgba);
+      tileres_kernel<NV><<<dim3(most_tiles, ny), kThreads, 0, s>>>(vs, c.rgbx);
       break;
     default:
       return hipErrorInvalidValue;
   }
   return hipGetLastError();
+}
+}  // namespace
+
+bool tiled_scan_merged(const TiledSplatView *views, int n) {
+  for (int i = 0; i < n; ++i) {
+    const uint32_t tx = (views[i].cam.W + kTileSide - 1) >> kTileShift, ty = (views[i].H + kTileSide - 1) >> kTileShift;
+    if (tx * ty > kMaxScanTiles) return false;
+  }
+  return true;
+}
+
+hipError_t launch_tiled_splat(const CloudDev &c, const uint2 *chunks, const uint32_t *work, const TiledSplatView &view,
+                              float one_plus_eps, int stage, hipStream_t s) {
+  if (c.max_chunks == 0) return hipErrorInvalidValue;  // a loaded cloud has at least one point
+  return tiled_stage<1>(c, chunks, work, &view, 1, one_plus_eps, stage, s);
+}
+
+hipError_t launch_tiled_views(const CloudDev &c, const uint4 *items, const uint32_t *work, const TiledSplatView *views,
+                              int n, int stage, hipStream_t s) {
+  if (c.max_chunks == 0 || n < 1 || n > kViewsPerPass) return hipErrorInvalidValue;
+  for (int i = 0; i < n; ++i)
+    if (views[i].acc) return hipErrorInvalidValue;  // the soft z-buffer renders one view at a time
+  return tiled_stage<kViewsPerPass>(c, items, work, views, n, 1.f, stage, s);
 }
 
 hipError_t launch_cull(const CloudDev &c, const CullParams &prm, const CullParams *prm_dev, uint8_t *flags,
@@ -1354,12 +1443,12 @@ hipError_t launch_splat(const CloudDev &c, const uint2 *chunks, uint32_t *counte
   return hipGetLastError();
 }
 
-hipError_t launch_cull_views(const CloudDev &c, const ViewsCull &prm, uint8_t *flags, uint4 *items, uint32_t *counters,
-                             hipStream_t s) {
+hipError_t launch_cull_views(const CloudDev &c, const ViewsCull &prm, const DevCam *dev, uint8_t *flags, uint4 *items,
+                             uint32_t chunk, uint32_t *counters, hipStream_t s) {
   if (prm.n < 1 || prm.n > kViewsPerPass) return hipErrorInvalidValue;
   const uint32_t nb = (c.n_cells + kThreads - 1) / kThreads;
-  cull_views_kernel<<<nb, kThreads, 0, s>>>(c.aabb, c.cell_start, c.n_cells, prm, flags, items, c.max_chunks,
-                                            counters);
+  cull_views_kernel<<<nb, kThreads, 0, s>>>(c.aabb, c.cell_start, c.n_cells, prm, dev, flags, items, c.max_chunks,
+                                            chunk, counters);
   return hipGetLastError();
 }
 

@@ -51,3 +51,42 @@ def test_binning_rectangles(lnr, ctx, n, x0, y0, bw, bh):
     lnr.lnr_render_soft(ctx, cloud, cam, img, 0.3, flags=lnr.LNR_RENDER_ATOMIC_SPLAT)
     torch.cuda.synchronize()
     assert_images_equal(image_to_host(img), (want[0], want[1], soft), "soft, atomic splat")
+
+
+def _views(lnr, ctx, cloud, cams):
+    import torch
+    imgs = [lnr.Image(c.height, c.width) for c in cams]
+    lnr.lnr_render_views(ctx, cloud, cams, imgs)
+    torch.cuda.synchronize()
+    return imgs
+
+
+def test_views_under_a_budget(lnr, ctx, room_cloud, room_cams):
+    """lnr_render_views with scratch for all eight views, for some, and for none
+    (then without the tiled splat): the same images, never refused for it."""
+    cams = list(room_cams[:8])
+    want = [image_to_host(render_gpu(lnr, ctx, room_cloud, c)) for c in cams]
+    free = lnr.lnr_context_create(0)
+    for img, w in zip(_views(lnr, free, room_cloud, cams), want):
+        assert_images_equal(image_to_host(img), w, "no budget")
+    full = lnr.lnr_allocated_bytes(free)
+    one = lnr.lnr_context_create(0)
+    _views(lnr, one, room_cloud, cams[:1])
+    single = lnr.lnr_allocated_bytes(one)
+    assert single < full
+    for budget in (single, 3 * single, single // 2):
+        print("budget", budget, flush=True)
+        c = lnr.lnr_context_create(0, budget)
+        for img, w in zip(_views(lnr, c, room_cloud, cams), want):
+            assert_images_equal(image_to_host(img), w, f"budget {budget}")
+        assert lnr.lnr_allocated_bytes(c) <= budget
+
+
+def test_views_of_many_tiles(lnr, ctx, room_cloud, room_cams):
+    """One view of more than 8192 tiles (its scan is a launch of its own) among smaller ones."""
+    import dataclasses
+    big = dataclasses.replace(room_cams[1], width=4096, height=2112)
+    cams = [room_cams[0], big, room_cams[2]]
+    for cam, img in zip(cams, _views(lnr, ctx, room_cloud, cams)):
+        assert_images_equal(image_to_host(img), image_to_host(render_gpu(lnr, ctx, room_cloud, cam)),
+                            f"{cam.width}x{cam.height}")
