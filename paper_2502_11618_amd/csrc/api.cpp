@@ -1301,18 +1301,20 @@ lnr_status lnr_unet_load(lnr_context *ctx, const void *blob_host, uint64_t bytes
       if ((st = upload(packed.data(), 4 * np, &cl.w)) != LNR_OK) return free_all(), st;
       if (cl.cin_pad % 16 == 0) {
         // Winograd F(2x2, 3x3) filter transform U = G g G^T, rounded once from
-        // the float64 weights; U[o][4 xi + nu][i]
+        // the float64 weights, by pairs of input channels:
+        // [32-channel tile][chunk of 8][16-channel tile][position 4 xi + nu][pair][16][2]
         static const double G[4][3] = {{1, 0, 0}, {0.5, 0.5, 0.5}, {0.5, -0.5, 0.5}, {0, 0, 1}};
         std::vector<float> wu((size_t)cl.cout_pad * 16 * cl.cin_pad, 0.f);
         for (int o = 0; o < (int)co; ++o)
           for (int i = 0; i < (int)ci; ++i) {
             const double *g = &Wd[((size_t)o * ci + i) * 9];
+            const size_t chunk = (size_t)(o / 32) * (cl.cin_pad / 8) + i / 8;
             for (int xi = 0; xi < 4; ++xi)
               for (int nu = 0; nu < 4; ++nu) {
                 double acc = 0;
                 for (int dy = 0; dy < 3; ++dy)
                   for (int dx = 0; dx < 3; ++dx) acc += G[xi][dy] * g[dy * 3 + dx] * G[nu][dx];
-                wu[((size_t)o * 16 + 4 * xi + nu) * cl.cin_pad + i] = (float)acc;
+                wu[((((chunk * 2 + o % 32 / 16) * 16 + 4 * xi + nu) * 4 + i % 8 / 2) * 16 + o % 16) * 2 + i % 2] = (float)acc;
               }
           }
         if ((st = upload(wu.data(), 4 * wu.size(), &cl.wu)) != LNR_OK) return free_all(), st;

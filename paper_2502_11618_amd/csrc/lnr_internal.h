@@ -226,13 +226,14 @@ struct ConvLayer {
   // groups of channel_group(cout_pad) output channels, tiles of 32
   void *w = nullptr;
   float *bias = nullptr;         // [cout_pad]
-  void *wu = nullptr;            // float32 only: Winograd F(2x2,3x3) weights G g G^T [cout_pad][16][cin_pad]
+  void *wu = nullptr;            // float32 only: Winograd F(2x2,3x3) weights G g G^T, in the order wino_kernel stages them
   float *wscale = nullptr;       // e4m3 modes: weight scale per output channel [cout_pad]
 };
 
 inline int channel_group(int cout_pad) { return cout_pad % 64 == 0 ? 64 : 32; }
 
-// Tensors: float32 NHWC, or the channel-block operands of conv16.hip; in0 has
+// Tensors: float32 in channel blocks of 4 (planes of 16-byte units, a unit the 4
+// channels of a pixel), or the channel-block operands of conv16.hip; in0 has
 // C0 channels at H x W, in1 C1 channels at (H/2) x (W/2), read nearest-
 // upsampled (decoder), or null.
 struct ConvCall {

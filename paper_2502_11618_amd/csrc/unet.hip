@@ -12,38 +12,10 @@
 // (The reduced-precision networks are in conv16.hip.)
 #include <hip/hip_runtime.h>
 
-#include <atomic>
-
-#include "lnr_internal.h"
+#include "conv_stage.h"
 
 namespace lnr {
 namespace {
-
-typedef float floatx16 __attribute__((ext_vector_type(16)));
-
-struct ConvArgs {
-  const void *in0;
-  const void *in1;
-  int C0, C1, H, W;
-  const void *w;
-  const float *bias;
-  int cout, cin_pad;
-  void *out;
-  void *out_pool;
-  const float *head_w;
-  const float *head_b;
-  float *head_out;
-  // batch of same-shape images: per-image strides of the tensors above in
-  // elements; head_outs (device array) gives each image's planar head output
-  // when set; the RGBDA images are rgbda_bs pixels apart
-  int batch;
-  size_t in0_bs, in1_bs, out_bs, pool_bs;
-  float *const *head_outs;
-  const float *rgbda_depth;
-  const uint32_t *rgbda_rgba;
-  size_t rgbda_bs;
-  const float *wu;  // Winograd-domain weights [cout_pad][16][cin_pad], or null
-};
 
 // The network's first 3x3 convolution as implicit GEMM (M = output channels,
 // N = pixels, K = 9 taps x 8 staged channels), one chunk, read from the RGBDA
@@ -55,7 +27,7 @@ struct ConvArgs {
 // input channels are staged as (x0, x1, x2, 0 | x3, x4, 0, 0): k-step s pairs
 // channel s with channel 4 + s, so the fourth step is zero and skipped.
 template <int BM, int R>
-__global__ __launch_bounds__(256) void first3x3_kernel(ConvArgs a) {
+__global__ __launch_bounds__(256) void first3x3_kernel(Args a) {
   constexpr int CK = 8, S = CK + 4;          // LDS floats per staged pixel / weight row
   constexpr int MB = BM / 32;
   constexpr int TH = 4 * R, TW = 32;
@@ -68,13 +40,13 @@ __global__ __launch_bounds__(256) void first3x3_kernel(ConvArgs a) {
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   const int n = lane & 31, h = lane >> 5;
   const int ty0 = blockIdx.y * TH, tx0 = blockIdx.x * TW;
-  const int nzc = gridDim.z / a.batch;
+  const int nzc = (a.cout + BM - 1) / BM;
   const int bimg = blockIdx.z / nzc;
   const int co0 = (blockIdx.z - bimg * nzc) * BM;
   const int H = a.H, W = a.W;
-  const float *depth = a.rgbda_depth + (size_t)bimg * a.rgbda_bs;
-  const uint32_t *rgba = a.rgbda_rgba + (size_t)bimg * a.rgbda_bs;
-  float *out = static_cast<float *>(a.out) + (size_t)bimg * a.out_bs;
+  const float *depth = a.depth + (size_t)bimg * a.rgbda_bs;
+  const uint32_t *rgba = a.rgba + (size_t)bimg * a.rgbda_bs;
+  char *out = a.out + (size_t)bimg * a.out_bs;
 
   uint32_t q[NIN];
   float dd[NIN];
@@ -88,7 +60,7 @@ __global__ __launch_bounds__(256) void first3x3_kernel(ConvArgs a) {
     q[k] = rgba[o];
     dd[k] = depth[o];
   }
-  const float *wsrc = static_cast<const float *>(a.w) + (size_t)co0 * 9 * CK;
+  const float *wsrc = reinterpret_cast<const float *>(a.w) + (size_t)co0 * 9 * CK;
   float4 pw[NWR];
 #pragma unroll
   for (int k = 0; k < NWR; ++k) {
@@ -160,7 +132,7 @@ __global__ __launch_bounds__(256) void first3x3_kernel(ConvArgs a) {
       for (int r = 0; r < R; ++r) {
         const int gy = ty0 + wv * R + r;
         if (gy < H && gx < W)
-          *reinterpret_cast<float4 *>(out + ((size_t)gy * W + gx) * a.cout + c) =
+          *reinterpret_cast<float4 *>(out + ((size_t)(c >> 2) * H * W + (size_t)gy * W + gx) * 16) =
               make_float4(fmaxf(acc[mb][r][4 * j + 0] + b.x, 0.f), fmaxf(acc[mb][r][4 * j + 1] + b.y, 0.f),
                           fmaxf(acc[mb][r][4 * j + 2] + b.z, 0.f), fmaxf(acc[mb][r][4 * j + 3] + b.w, 0.f));
       }
@@ -175,444 +147,422 @@ __global__ __launch_bounds__(256) void first3x3_kernel(ConvArgs a) {
 //   G   = [1 0 0; 1/2 1/2 1/2; 1/2 -1/2 1/2; 0 0 1],
 //   A^T = [1 1 1 0; 0 1 -1 -1].
 // The channel sum is, for each of the 16 transform positions (xi, nu), a GEMM
-// (output channels x blocks, K = input channels) on v_mfma_f32_32x32x2_f32:
+// (output channels x blocks, K = input channels) on v_mfma_f32_16x16x4_f32:
 // 16 multiplies per block and channel pair instead of 36 for the direct form.
-// A tile is 8 rows x 32 columns of output pixels (4 x 16 blocks) x 32 MB output
-// channels.  A workgroup has 8 waves; wave w owns transform row xi = w & 3 of
-// block rows 2 (w >> 2) and 2 (w >> 2) + 1 (32 blocks, one per lane column)
-// and holds the accumulators (xi, nu = 0..3) of MB blocks of 32 channels, so
-// with MB = 2 its input fragments feed two MFMA blocks.  Row xi of B^T d
-// combines two patch rows, so a wave reads 8 of the 16 patch pixels and
-// transforms in registers.  Workgroups are persistent (one per CU) and stream
-// the CK-channel chunks of their tiles through two LDS buffers, one barrier
-// per chunk.  Epilogue: each wave reduces its row by A (2 values per block and
-// channel) into LDS, and every thread then finishes 4 channels of one block:
-// the A^T row reduction, bias, ReLU, the 2x2 output block (which is also the
-// max-pool window) and the fused 1x1 head.
-template <bool HEAD, int MB, int CK>
-__global__ __launch_bounds__(512) void wino3x3_kernel(ConvArgs a, int ntx, int nty, int nzc, int ntiles) {
-  constexpr int NT = 512, TB = 2;                    // threads; tile blocks of 2 tile rows
-  constexpr int NCO = 32 * MB;                       // output channels per workgroup tile
-  constexpr int NV = CK / 4;                         // staged channels CK: 16-byte vectors per pixel
-  constexpr int TH = 4 * TB, TW = 32, LW = TW + 2, LPix = (TH + 2) * LW;
-  // input tile in LDS, in 16-byte units (4 channels): unit of (row, col, vector v)
-  // = v PX + (col & 1) PY + row HZ + (col >> 1).  Lanes read the pixels of 16
-  // consecutive blocks, 2 columns apart: with even and odd columns in separate
-  // planes those are 16 consecutive units, one per bank group.
-  constexpr int HZ = LW / 2, PY = (TH + 2) * HZ, PX = 2 * PY;
-  constexpr int CS = 16 * CK + 4;                    // LDS floats per output channel of U (+4: bank spread)
-  constexpr int INP = NV * PX * 4, BUF = INP + NCO * CS;
-  constexpr int PP = NT / NV;                        // pixels / U rows per staging pass
-  constexpr int NIN = (LPix + PP - 1) / PP, NWR = NCO * 16 / PP;
-  constexpr int ES = 2 * 32 + 4;                     // epilogue floats per tile: 2 columns x 32 channels (+4)
-  constexpr int EPL = TB * 4 * 32 * ES;
-  // LDS: [buffer 0][GAP][buffer 1]; the epilogue's EPL floats start at the
-  // buffer just finished (0 or BUF) and may run into the gap
-  constexpr int GAP = EPL > BUF ? EPL - BUF : 0, B1 = BUF + GAP;
-  static_assert(NCO * 16 % PP == 0, "U rows must fill whole staging passes");
-  __shared__ __attribute__((aligned(16))) float smem[2 * BUF + GAP];
-
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-  const int n = lane & 31, h = lane >> 5;
-  const int xi = wv & 3, tb = wv >> 2;
+//
+// Tensors lie in memory as channel blocks: planes of 16-byte units, a unit the
+// 4 channels of a pixel.  A workgroup of 4 waves takes tiles of 8 rows x 32
+// columns of output pixels x 16 M output channels; wave w owns row w of the 2x2
+// blocks (16 of them) and keeps all 16 positions of its blocks and the tile's
+// channels in accumulators, so the output transform, the 2x2 max-pool (the
+// block is its window) and the 1x1 head run in registers and no accumulator
+// goes through LDS.  Chunks of 8 input channels of all the workgroup's tiles
+// form one stream.  In step t a wave multiplies chunk t from registers (its
+// transform) and LDS (the filters); in the multiplications' shadow it reads and
+// transforms chunk t + 1 and starts the loads, straight into LDS, of step
+// t + 1's filters and step t + 3's input.  One barrier per step; two workgroups
+// per CU (three with M = 1) cover each other's.  The instructions of a step are
+// fixed in place (sched_barrier): left alone the compiler reads each filter
+// right before its use and gathers the transform in front, 8% slower.
+//
+// LDS of a step: input units [channel quad][halo row][even columns, odd
+// columns] (the lanes read columns two apart: 16 consecutive units), filters
+// [16-channel tile][position][channel pair][16 channels][2].  Lane (n, kq) =
+// (lane & 15, lane >> 4) multiplies channels 2 kq and 2 kq + 1 of a chunk:
+// channel n of the filters' tile, block n of the wave's row.
+//
+// Bound by the matrix cores and, in part, by the transform's 64 additions for
+// 32 M multiplications: the cores are busy 74% of 128 + 256 -> 128 channels at
+// 480 x 270 (437 us), 63% of 32 -> 32 at 1920 x 1080 (196 us), which also reads
+// and writes 600 MB.  With one transform per 512-thread workgroup, shared
+// through LDS, and the accumulators added up there: 538 and 272 us.
+typedef float floatx4 __attribute__((ext_vector_type(4)));
+template <int M, bool HEAD>
+struct WinoLds {
+  static constexpr int TH = 8, LW = 34, HW = 17, UB = (TH + 2) * LW;  // halo tile: units per channel quad
+  static constexpr int NL = (UB + 63) / 64;                           // in wave loads
+  static constexpr int INB = 2 * UB * 16, WB = M * 8192;              // bytes of a step's input and filters
+  static constexpr int kWeights = 3 * INB, kBias = kWeights + 2 * WB;
+  static constexpr int kHead = kBias + 2 * M * 16 * 4;                // two tiles' biases
+  static constexpr int kBytes = kHead + (HEAD ? (3 * 64 + 4) * 4 : 0);
+};
+template <int M, bool HEAD>
+__global__ __launch_bounds__(256, 2) void wino_kernel(Args a) {
+  using S = WinoLds<M, HEAD>;
+  constexpr int NW = 4, LW = S::LW, UB = S::UB, NK = (S::NL + NW - 1) / NW;
+  __shared__ __attribute__((aligned(16))) char sm[S::kBytes];
+  const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int n = lane & 15, kq = lane >> 4;
   const int H = a.H, W = a.W;
-  const int Cin = a.C0 + a.C1;
-
-  // Persistent workgroups walk a list of tiles (an 8 x 32 pixel block of one
-  // image and one block of NCO output channels).  Tile order: output-channel
-  // blocks of one pixel block are consecutive, then pixel blocks, then images;
-  // with a grid of 8k workgroups, workgroup w (on XCD w mod 8) walks every
-  // k-th tile of the w mod 8 -th eighth of the list, so tiles that share input
-  // pixels run on the same XCD at about the same time.
-  const int G = gridDim.x;
-  int t_first, t_end, t_step;
-  if (G % 8 == 0 && G < ntiles) {
-    const int x = blockIdx.x & 7, per = G >> 3;
-    t_first = (int)((long)x * ntiles / 8) + (blockIdx.x >> 3);
-    t_end = (int)((long)(x + 1) * ntiles / 8);
-    t_step = per;
-  } else {
-    t_first = blockIdx.x;
-    t_end = ntiles;
-    t_step = G;
+  const uint32_t sm0 = lds_address(sm);
+  const int nch = (a.C0 + a.C1) >> 3, nch0 = a.C0 >> 3;
+  const Walk walk = my_tiles(a);
+  if (walk.first >= walk.end) return;
+  const int steps = (walk.end - walk.first) * nch;
+  if constexpr (HEAD) {
+    float *sh = reinterpret_cast<float *>(sm + S::kHead);
+    for (int i = tid; i < 3 * 64; i += 64 * NW) {
+      const int o = i >> 6, c = i & 63;
+      sh[i] = c < a.cout ? a.head_w[o * a.cout + c] : 0.f;
+    }
+    if (tid < 3) sh[192 + tid] = a.head_b[tid];
   }
-  struct TileId { int ty0, tx0, co0, bimg; };
-  auto decode = [&](int T) {
-    TileId d;
-    const int cz = T % nzc, sp = T / nzc;
-    const int nsp = ntx * nty;
-    d.bimg = sp / nsp;
-    const int r = sp - d.bimg * nsp;
-    d.ty0 = (r / ntx) * TH;
-    d.tx0 = (r % ntx) * TW;
-    d.co0 = cz * NCO;
-    return d;
+
+  // ---- filters: 2 M loads per wave and step
+  const char *wptr = nullptr;
+  int wT = walk.first, wc = 0, wslot = 0, wtile = 0;
+  uint64_t wlanes = ~0ull;
+  auto begin_weights = [&]() {
+    if (wc != 0) return;
+    if (wT < walk.end) {
+      const int cz = __builtin_amdgcn_readfirstlane(wT % a.ncz);
+      wptr = uniform(a.w + ((size_t)(cz * M >> 1) * nch * 2 + (cz * M & 1)) * 8192 + wv * 1024);
+      if (wv == 0) load_lds4(a.bias + cz * M * 16, lane * 4, sm0 + S::kBias + (wtile & 1) * M * 64, (1ull << M * 16) - 1);
+    } else {
+      wlanes = 0;
+    }
+  };
+  auto issue_weights = [&](int k) {
+    load_lds16(wptr + k * NW * 1024, lane * 16, sm0 + S::kWeights + wslot * S::WB + wv * 1024 + k * NW * 1024, wlanes);
+  };
+  auto end_weights = [&]() {
+    wptr += 2 * 8192;
+    wslot ^= 1;
+    if (++wc == nch) {
+      wc = 0;
+      ++wtile;
+      ++wT;
+    }
   };
 
-  // staging plan: this thread moves float4 qv of pixels p0, p0 + PP, ... and of
-  // U rows p0, p0 + PP, ... (row r = 16 co + position)
-  const int qv = (tid % NV) * 4, p0 = tid / NV;
-  int lofs[NIN];
+  // ---- input: in every channel quad, wave load j = wv + NW k covers units j 64 + lane
+  int urow[NK], ucol[NK];
 #pragma unroll
-  for (int k = 0; k < NIN; ++k) {
-    const int pix = p0 + k * PP, row = pix / LW, col = pix % LW;
-    lofs[k] = 4 * ((qv / 4) * PX + (col & 1) * PY + row * HZ + (col >> 1));
+  for (int k = 0; k < NK; ++k) {
+    const int pos = (wv + NW * k) * 64 + lane;
+    urow[k] = pos / LW;
+    const int q = pos - urow[k] * LW;
+    ucol[k] = q < S::HW ? 2 * q : 2 * (q - S::HW) + 1;
   }
-  // fetch state: the tile whose chunks are being fetched
-  int off0[NIN], off1[NIN];
-  const float *fin0 = nullptr, *fin1 = nullptr, *wsrc = nullptr;
-  auto set_fetch_tile = [&](const TileId &d) {
+  int iT = walk.first, ic = 0, islot = 0;
+  int iy0 = 0, ix0 = 0, iimg = 0;
+  uint32_t voff[NK];
+  uint64_t lanes[NK];
+  uint32_t outside = 0;  // bit k: this lane's unit of load k lies outside the image
+  bool border = false;
+  const char *src = nullptr;  // the chunk's first channel quad, at the tile's first halo row
+  size_t blk = 0;             // bytes per channel quad of the current source
+  auto set_source = [&](bool second) {
+    const int sh = second ? 1 : 0, Ws = W >> sh, y0 = (iy0 - 1) >> sh;
+    const char *in = second ? a.in1 + (size_t)iimg * a.in1_bs : a.in0 + (size_t)iimg * a.in0_bs;
+    blk = (size_t)(H >> sh) * Ws * 16;
+    src = uniform(in + (ptrdiff_t)y0 * Ws * 16);
 #pragma unroll
-    for (int k = 0; k < NIN; ++k) {
-      const int pix = p0 + k * PP, row = pix / LW, col = pix % LW;
-      const int gy = d.ty0 - 1 + row, gx = d.tx0 - 1 + col;
-      const bool inside = pix < LPix && gy >= 0 && gy < H && gx >= 0 && gx < W;
-      off0[k] = inside ? gy * W + gx : -1;
-      off1[k] = inside ? (gy >> 1) * (W >> 1) + (gx >> 1) : -1;
+    for (int k = 0; k < NK; ++k)  // (unused outside the image)
+      voff[k] = (uint32_t)((((iy0 - 1 + urow[k]) >> sh) - y0) * Ws + ((ix0 - 1 + ucol[k]) >> sh)) * 16u;
+  };
+  auto begin_input = [&]() {
+    if (ic == 0 && iT >= walk.end) {
+#pragma unroll
+      for (int k = 0; k < NK; ++k) lanes[k] = 0;
+      border = false;
+    } else if (ic == 0) {
+      const Tile t = tile_at(a, iT);
+      iy0 = t.ty * S::TH;
+      ix0 = t.tx * 32;
+      iimg = t.img;
+      outside = 0;
+#pragma unroll
+      for (int k = 0; k < NK; ++k) {
+        const bool any = urow[k] < S::TH + 2;
+        const bool in = ((unsigned)(iy0 - 1 + urow[k]) < (unsigned)H) & ((unsigned)(ix0 - 1 + ucol[k]) < (unsigned)W);
+        lanes[k] = __ballot(any & in);
+        outside |= (any & !in) ? 1u << k : 0u;
+      }
+      border = __ballot(outside != 0) != 0;
     }
-    fin0 = static_cast<const float *>(a.in0) + (size_t)d.bimg * a.in0_bs;
-    fin1 = a.in1 ? static_cast<const float *>(a.in1) + (size_t)d.bimg * a.in1_bs : nullptr;
-    wsrc = a.wu + ((size_t)d.co0 * 16 + p0) * a.cin_pad + qv;
+    if (ic == 0 || ic == nch0) set_source(ic != 0);
   };
-  const size_t wstep = (size_t)PP * a.cin_pad;
-  auto fetch_in = [&](int ci, uint4 (&v)[NIN]) {
-    const bool from0 = ci < a.C0;
-    const size_t csrc = from0 ? a.C0 : a.C1;
-    const float *src = (from0 ? fin0 + ci : fin1 + (ci - a.C0)) + qv;
+  auto issue_input = [&](int j) {
+    const int b = j / NK, k = j % NK;
+    load_lds16(src + b * blk, voff[k], sm0 + islot * S::INB + wv * 1024 + b * UB * 16 + k * NW * 1024, lanes[k]);
+  };
+  auto end_input = [&]() {
+    if (border) {
 #pragma unroll
-    for (int k = 0; k < NIN; ++k) {
-      const int o = from0 ? off0[k] : off1[k];
-      const uint4 x = *reinterpret_cast<const uint4 *>(src + (size_t)(o < 0 ? 0 : o) * csrc);
-      v[k] = o < 0 ? make_uint4(0u, 0u, 0u, 0u) : x;
+      for (int k = 0; k < NK; ++k)
+        if ((outside >> k) & 1u) {
+#pragma unroll
+          for (int b = 0; b < 2; ++b)
+            *reinterpret_cast<uint4 *>(sm + islot * S::INB + wv * 1024 + b * UB * 16 + k * NW * 1024 + lane * 16) =
+                make_uint4(0u, 0u, 0u, 0u);
+        }
     }
-  };
-  auto fetch_w = [&](int ci, uint4 (&v)[NWR]) {
-#pragma unroll
-    for (int k = 0; k < NWR; ++k) v[k] = *reinterpret_cast<const uint4 *>(wsrc + k * wstep + ci);
-  };
-  auto store_in = [&](int buf, const uint4 (&v)[NIN]) {
-#pragma unroll
-    for (int k = 0; k < NIN; ++k) {
-      if (!((k + 1) * PP <= LPix || p0 + k * PP < LPix)) continue;
-      *reinterpret_cast<uint4 *>(&smem[buf + lofs[k]]) = v[k];
-    }
-  };
-  auto store_w = [&](int buf, const uint4 (&v)[NWR]) {
-#pragma unroll
-    for (int k = 0; k < NWR; ++k) {
-      const int r = p0 + k * PP;
-      *reinterpret_cast<uint4 *>(&smem[buf + INP + (r >> 4) * CS + (r & 15) * CK + qv]) = v[k];
+    src += 2 * blk;
+    islot = islot == 2 ? 0 : islot + 1;
+    if (++ic == nch) {
+      ic = 0;
+      ++iT;
     }
   };
 
-  // lane (n, h): block (tr, tc) of the tile, channels 8g + 4h + s of
-  // chunk group g at k-step s.  Row xi of B^T d is patch row ra + sg * patch row rb.
-  const int tr = 2 * tb + (n >> 4), tc = n & 15;
-  const int ra = xi == 0 ? 0 : (xi == 2 ? 2 : 1);
-  const int rb = xi == 0 ? 2 : (xi == 1 ? 2 : (xi == 2 ? 1 : 3));
-  const float sg = xi == 1 ? 1.f : -1.f;
-  const int ioa = 4 * (h * PX + (2 * tr + ra) * HZ + tc);
-  const int iob = 4 * (h * PX + (2 * tr + rb) * HZ + tc);
-  const int iow = INP + n * CS + 4 * xi * CK + 4 * h;
-  // acc[mb][nu]: positions (xi, nu) of output channels co0 + 32 mb + ... of 32 blocks
-  floatx16 acc[MB][4];
+  // acc[m][4 xi + nu]: channels 16 m + 4 kq + i of block n
+  floatx4 acc[M][16];
   auto zero_acc = [&]() {
 #pragma unroll
-    for (int mb = 0; mb < MB; ++mb)
+    for (int m = 0; m < M; ++m)
 #pragma unroll
-      for (int v = 0; v < 4; ++v)
-#pragma unroll
-        for (int q = 0; q < 16; ++q) acc[mb][v][q] = 0.f;
+      for (int p = 0; p < 16; ++p) acc[m][p] = floatx4{0.f, 0.f, 0.f, 0.f};
   };
-  auto compute = [&](int buf) {
-    const float *pa = smem + buf + ioa, *pb = smem + buf + iob, *pu = smem + buf + iow;
-#pragma unroll 1
-    for (int g = 0; g < CK / 8; ++g) {
-      float4 da[4], db[4], u[MB][4];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        // column 2 tc + j of vector 2 g + h
-        const int o = 4 * (2 * g * PX + (j & 1) * PY + (j >> 1));
-        da[j] = *reinterpret_cast<const float4 *>(pa + o);
-        db[j] = *reinterpret_cast<const float4 *>(pb + o);
-      }
-#pragma unroll
-      for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) u[mb][v] = *reinterpret_cast<const float4 *>(pu + mb * 32 * CS + v * CK + 8 * g);
-#pragma unroll
-      for (int s = 0; s < 4; ++s) {
-        auto comp = [s](const float4 &f) { return s == 0 ? f.x : (s == 1 ? f.y : (s == 2 ? f.z : f.w)); };
-        float r[4];
-#pragma unroll
-        for (int j = 0; j < 4; ++j) r[j] = fmaf(sg, comp(db[j]), comp(da[j]));
-        const float t[4] = {r[0] - r[2], r[1] + r[2], r[2] - r[1], r[1] - r[3]};
-#pragma unroll
-        for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-          for (int v = 0; v < 4; ++v)
-            acc[mb][v] = __builtin_amdgcn_mfma_f32_32x32x2f32(comp(u[mb][v]), t[v], acc[mb][v], 0, 0, 0);
-      }
-    }
-  };
+  zero_acc();
+  const char *D = sm + ((kq >> 1) * UB + 2 * wv * LW + n) * 16 + (kq & 1) * 8;
+  const char *U = sm + S::kWeights + lane * 8;
+  float hs[2][2][3];  // head sums of the pixel tile's channels so far
 
-  // ---- epilogue of one tile into E (EPL floats of LDS nobody reads any
-  // more), one block of 32 output channels at a time.  Accumulator register
-  // 4j + i of acc[mb][nu] holds position (xi, nu) of channel co0 + 32 mb +
-  // 8j + 4h + i for block n; each wave reduces nu by A into E, then thread
-  // (block et, quad q) reduces xi by A^T for channels c .. c + 3.
-  const int q = tid & 7, et = tid >> 3, etb = et >> 5, en = et & 31;
-  auto epilogue = [&](float *E, const TileId &d) {
-    const int gy0 = d.ty0 + 2 * (2 * etb + (en >> 4)), gx0 = d.tx0 + 2 * (en & 15);
-    float *out = a.out ? static_cast<float *>(a.out) + (size_t)d.bimg * a.out_bs : nullptr;
-    float *out_pool = a.out_pool ? static_cast<float *>(a.out_pool) + (size_t)d.bimg * a.pool_bs : nullptr;
-    float hs[2][2][3];  // head partial sums of this thread's channels
+  // B^T d B of a lane's channels 2 kq, 2 kq + 1, in three parts: the patch's
+  // column j, B^T over its rows, B over the columns of row x
+  float2 d[4][4], v[16];
+  auto read_d = [&](int slot, int j) {
 #pragma unroll
-    for (int r = 0; r < 2; ++r)
+    for (int r = 0; r < 4; ++r)
+      d[r][j] = *reinterpret_cast<const float2 *>(D + slot * S::INB + (r * LW + (j & 1) * S::HW + (j >> 1)) * 16);
+  };
+  auto rows = [&](int j) {
+    const float2 d0 = d[0][j], d1 = d[1][j], d2 = d[2][j], d3 = d[3][j];
+    d[0][j] = make_float2(d0.x - d2.x, d0.y - d2.y);
+    d[1][j] = make_float2(d1.x + d2.x, d1.y + d2.y);
+    d[2][j] = make_float2(d2.x - d1.x, d2.y - d1.y);
+    d[3][j] = make_float2(d1.x - d3.x, d1.y - d3.y);
+    // (keeps the compiler from moving the sums out of the multiplications' shadow)
 #pragma unroll
-      for (int col = 0; col < 2; ++col) hs[r][col][0] = hs[r][col][1] = hs[r][col][2] = 0.f;
+    for (int r = 0; r < 4; ++r) asm volatile("" : "+v"(d[r][j].x), "+v"(d[r][j].y));
+  };
+  auto columns = [&](int x) {
+    v[4 * x + 0] = make_float2(d[x][0].x - d[x][2].x, d[x][0].y - d[x][2].y);
+    v[4 * x + 1] = make_float2(d[x][1].x + d[x][2].x, d[x][1].y + d[x][2].y);
+    v[4 * x + 2] = make_float2(d[x][2].x - d[x][1].x, d[x][2].y - d[x][1].y);
+    v[4 * x + 3] = make_float2(d[x][1].x - d[x][3].x, d[x][1].y - d[x][3].y);
 #pragma unroll
-    for (int mb = 0; mb < MB; ++mb) {
-      if (mb > 0) __syncthreads();  // the previous block's readers are done with E
+    for (int nu = 0; nu < 4; ++nu) asm volatile("" : "+v"(v[4 * x + nu].x), "+v"(v[4 * x + nu].y));
+  };
+  begin_weights();
+  for (int k = 0; k < 2 * M; ++k) issue_weights(k);
+  end_weights();
+  for (int t = 0; t < 3; ++t) {
+    begin_input();
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        float4 p0v, p1v;
-        p0v.x = acc[mb][0][4 * j + 0] + acc[mb][1][4 * j + 0] + acc[mb][2][4 * j + 0];
-        p0v.y = acc[mb][0][4 * j + 1] + acc[mb][1][4 * j + 1] + acc[mb][2][4 * j + 1];
-        p0v.z = acc[mb][0][4 * j + 2] + acc[mb][1][4 * j + 2] + acc[mb][2][4 * j + 2];
-        p0v.w = acc[mb][0][4 * j + 3] + acc[mb][1][4 * j + 3] + acc[mb][2][4 * j + 3];
-        p1v.x = acc[mb][1][4 * j + 0] - acc[mb][2][4 * j + 0] - acc[mb][3][4 * j + 0];
-        p1v.y = acc[mb][1][4 * j + 1] - acc[mb][2][4 * j + 1] - acc[mb][3][4 * j + 1];
-        p1v.z = acc[mb][1][4 * j + 2] - acc[mb][2][4 * j + 2] - acc[mb][3][4 * j + 2];
-        p1v.w = acc[mb][1][4 * j + 3] - acc[mb][2][4 * j + 3] - acc[mb][3][4 * j + 3];
-        float *e = E + ((tb * 4 + xi) * 32 + n) * ES + 8 * j + 4 * h;
-        *reinterpret_cast<float4 *>(e) = p0v;
-        *reinterpret_cast<float4 *>(e + 32) = p1v;
-      }
-      __syncthreads();
-      const int c = d.co0 + 32 * mb + 4 * q;
-      float y[2][2][4];  // [row][column][channel]
+    for (int j = 0; j < 2 * NK; ++j) issue_input(j);
+    end_input();
+  }
+  wait_loads<0>();
+  __syncthreads();
 #pragma unroll
-      for (int col = 0; col < 2; ++col) {
-        float4 P[4];
+  for (int j = 0; j < 4; ++j) {
+    read_d(0, j);
+    rows(j);
+  }
 #pragma unroll
-        for (int x = 0; x < 4; ++x)
-          P[x] = *reinterpret_cast<const float4 *>(E + ((etb * 4 + x) * 32 + en) * ES + col * 32 + 4 * q);
-        y[0][col][0] = P[0].x + P[1].x + P[2].x;
-        y[0][col][1] = P[0].y + P[1].y + P[2].y;
-        y[0][col][2] = P[0].z + P[1].z + P[2].z;
-        y[0][col][3] = P[0].w + P[1].w + P[2].w;
-        y[1][col][0] = P[1].x - P[2].x - P[3].x;
-        y[1][col][1] = P[1].y - P[2].y - P[3].y;
-        y[1][col][2] = P[1].z - P[2].z - P[3].z;
-        y[1][col][3] = P[1].w - P[2].w - P[3].w;
-      }
-      const bool live = c < a.cout;
-      float4 b = make_float4(0.f, 0.f, 0.f, 0.f);
-      if (live) b = *reinterpret_cast<const float4 *>(a.bias + c);
-      const float bb[4] = {b.x, b.y, b.z, b.w};
+  for (int x = 0; x < 4; ++x) columns(x);
+  __syncthreads();  // slot 0 is free
+  int T = walk.first, tile = 0, c = 0, slot = 1;
+  for (int t = 0; t < steps; ++t) {
+    // step t's filters and step t + 1's input lie in LDS, step t's transform in v
+    const char *Ut = U + (t & 1) * S::WB;
+    float2 u[3][M];
+    auto read_u = [&](int p) {
 #pragma unroll
-      for (int r = 0; r < 2; ++r)
+      for (int m = 0; m < M; ++m) u[p % 3][m] = *reinterpret_cast<const float2 *>(Ut + m * 8192 + p * 512);
+    };
+    read_u(0);
+    read_u(1);
+    begin_weights();
+    begin_input();
+    // In the multiplications' shadow: the loads of step t + 1's filters and step
+    // t + 3's input (masked off past the last), the filters of two positions on, and step
+    // t + 1's transform, into v as its values are used up.  (Past the last step
+    // it reads a slot of earlier values, and nobody its results.)
 #pragma unroll
-        for (int col = 0; col < 2; ++col)
+    for (int p = 0; p < 16; ++p) {
+      __builtin_amdgcn_sched_barrier(0);
+      if (p + 2 < 16) read_u(p + 2);
+      if (p < 4) read_d(slot, p);
+      __builtin_amdgcn_sched_barrier(0);
+      const float2(&f)[M] = u[p % 3];
 #pragma unroll
-          for (int i = 0; i < 4; ++i) y[r][col][i] = fmaxf(y[r][col][i] + bb[i], 0.f);
+      for (int m = 0; m < M; ++m) acc[m][p] = __builtin_amdgcn_mfma_f32_16x16x4f32(f[m].x, v[p].x, acc[m][p], 0, 0, 0);
+#pragma unroll
+      for (int m = 0; m < M; ++m) acc[m][p] = __builtin_amdgcn_mfma_f32_16x16x4f32(f[m].y, v[p].y, acc[m][p], 0, 0, 0);
+      if (p % 2 && p / 2 < 2 * M) issue_weights(p / 2);
+      if (p % 2 == 0 && p >= 8) issue_input(p / 2 - 4);
+      if (p >= 2 && p < 6) rows(p - 2);
+      if (p == 7) columns(0);
+      if (p == 9) columns(1);
+      if (p == 12) columns(2);
+      if (p == 15) columns(3);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    end_weights();
+    end_input();
+    // the input of step t + 3, the newest loads, may stay in flight
+    wait_loads<2 * NK>();
+    __syncthreads();
+    slot = slot == 2 ? 0 : slot + 1;
+    if (++c == nch) {
+      // ---- epilogue: A^T M A, bias, ReLU; stores, pool or head
+      const Tile tl = tile_at(a, T);
+      const int gy0 = tl.ty * S::TH + 2 * wv, gx0 = tl.tx * 32 + 2 * n;
+      const size_t HWp = (size_t)H * W;
+      const float *sb = reinterpret_cast<const float *>(sm + S::kBias) + (tile & 1) * M * 16;
       if constexpr (HEAD) {
-        if (live) {
+        if (tl.cz == 0) {
+#pragma unroll
+          for (int i = 0; i < 12; ++i) (&hs[0][0][0])[i] = 0.f;
+        }
+      }
+#pragma unroll
+      for (int m = 0; m < M; ++m) {
+        const int c0 = (tl.cz * M + m) * 16;
+        if (c0 >= a.cout) continue;  // (cout is a multiple of 16)
+        const float4 b4 = *reinterpret_cast<const float4 *>(sb + 16 * m + 4 * kq);
+        const floatx4 bias = {b4.x, b4.y, b4.z, b4.w};
+        floatx4 y[2][2];
+        {
+          floatx4 P[4];
+#pragma unroll
+          for (int x = 0; x < 4; ++x) P[x] = acc[m][4 * x] + acc[m][4 * x + 1] + acc[m][4 * x + 2];
+          y[0][0] = P[0] + P[1] + P[2] + bias;
+          y[1][0] = P[1] - P[2] - P[3] + bias;
+#pragma unroll
+          for (int x = 0; x < 4; ++x) P[x] = acc[m][4 * x + 1] - acc[m][4 * x + 2] - acc[m][4 * x + 3];
+          y[0][1] = P[0] + P[1] + P[2] + bias;
+          y[1][1] = P[1] - P[2] - P[3] + bias;
+        }
+#pragma unroll
+        for (int r = 0; r < 2; ++r)
+#pragma unroll
+          for (int col = 0; col < 2; ++col)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) y[r][col][i] = fmaxf(y[r][col][i], 0.f);
+        if constexpr (HEAD) {
+          const float *sh = reinterpret_cast<const float *>(sm + S::kHead) + c0 + 4 * kq;
+#pragma unroll
+          for (int k = 0; k < 3; ++k) {
+            const float4 w4 = *reinterpret_cast<const float4 *>(sh + 64 * k);
+            const float w[4] = {w4.x, w4.y, w4.z, w4.w};
+#pragma unroll
+            for (int r = 0; r < 2; ++r)
+#pragma unroll
+              for (int col = 0; col < 2; ++col)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) hs[r][col][k] = fmaf(w[i], y[r][col][i], hs[r][col][k]);
+          }
+        } else {
+          const size_t cb = (size_t)(c0 / 4 + kq);  // channel quad
+          char *out = a.out + (size_t)tl.img * a.out_bs + cb * HWp * 16;
 #pragma unroll
           for (int r = 0; r < 2; ++r)
 #pragma unroll
             for (int col = 0; col < 2; ++col)
+              if (gy0 + r < H && gx0 + col < W)
+                *reinterpret_cast<floatx4 *>(out + ((size_t)(gy0 + r) * W + gx0 + col) * 16) = y[r][col];
+          if (a.out_pool && gy0 < H && gx0 < W) {
+            floatx4 mx;
 #pragma unroll
-              for (int i = 0; i < 4; ++i) {
-                hs[r][col][0] = fmaf(a.head_w[c + i], y[r][col][i], hs[r][col][0]);
-                hs[r][col][1] = fmaf(a.head_w[a.cout + c + i], y[r][col][i], hs[r][col][1]);
-                hs[r][col][2] = fmaf(a.head_w[2 * a.cout + c + i], y[r][col][i], hs[r][col][2]);
-              }
-        }
-      } else if (live) {
-#pragma unroll
-        for (int r = 0; r < 2; ++r)
-#pragma unroll
-          for (int col = 0; col < 2; ++col) {
-            const int gy = gy0 + r, gx = gx0 + col;
-            if (gy < H && gx < W)
-              *reinterpret_cast<float4 *>(out + ((size_t)gy * W + gx) * a.cout + c) =
-                  make_float4(y[r][col][0], y[r][col][1], y[r][col][2], y[r][col][3]);
+            for (int i = 0; i < 4; ++i) mx[i] = fmaxf(fmaxf(y[0][0][i], y[0][1][i]), fmaxf(y[1][0][i], y[1][1][i]));
+            *reinterpret_cast<floatx4 *>(a.out_pool + (size_t)tl.img * a.pool_bs + cb * (HWp >> 2) * 16 +
+                                         ((size_t)(gy0 >> 1) * (W >> 1) + (gx0 >> 1)) * 16) = mx;
           }
-        if (out_pool && gy0 < H && gx0 < W) {
-          float m[4];
-#pragma unroll
-          for (int i = 0; i < 4; ++i) m[i] = fmaxf(fmaxf(y[0][0][i], y[0][1][i]), fmaxf(y[1][0][i], y[1][1][i]));
-          *reinterpret_cast<float4 *>(out_pool + ((size_t)(gy0 >> 1) * (W >> 1) + (gx0 >> 1)) * a.cout + c) =
-              make_float4(m[0], m[1], m[2], m[3]);
         }
       }
-    }
-    if constexpr (HEAD) {
-      // the tile holds every output channel (cout <= NCO): sum the head over
-      // the block's 8 threads; thread q < 4 writes pixel (q >> 1, q & 1)
-      float *head_out =
-          a.head_outs ? a.head_outs[d.bimg] : (a.head_out ? a.head_out + (size_t)d.bimg * 3 * H * W : nullptr);
-#pragma unroll
-      for (int r = 0; r < 2; ++r)
-#pragma unroll
-        for (int col = 0; col < 2; ++col)
+      if constexpr (HEAD) {
+        if (tl.cz == a.ncz - 1) {
+          // sum over the lanes of a block; lane kq writes pixel (kq >> 1, kq & 1)
+          const float *hb = reinterpret_cast<const float *>(sm + S::kHead) + 192;
+          float o[3] = {0.f, 0.f, 0.f};
 #pragma unroll
           for (int k = 0; k < 3; ++k)
 #pragma unroll
-            for (int m = 1; m < 8; m <<= 1) hs[r][col][k] += __shfl_xor(hs[r][col][k], m, 64);
-      if (q < 4) {
-        const int r = q >> 1, col = q & 1, gy = gy0 + r, gx = gx0 + col;
-        float o0 = hs[0][0][0], o1 = hs[0][0][1], o2 = hs[0][0][2];
+            for (int r = 0; r < 2; ++r)
 #pragma unroll
-        for (int rr = 0; rr < 2; ++rr)
+              for (int col = 0; col < 2; ++col) {
+                float x = hs[r][col][k];
+                x += __shfl_xor(x, 16, 64);
+                x += __shfl_xor(x, 32, 64);
+                if (kq == 2 * r + col) o[k] = x + hb[k];
+              }
+          float *head_out = a.head_outs ? a.head_outs[tl.img] : a.head_out + (size_t)tl.img * 3 * HWp;
+          const int gy = gy0 + (kq >> 1), gx = gx0 + (kq & 1);
+          if (gy < H && gx < W) {
+            const size_t px = (size_t)gy * W + gx;
 #pragma unroll
-          for (int cc = 0; cc < 2; ++cc)
-            if (rr == r && cc == col) {
-              o0 = hs[rr][cc][0];
-              o1 = hs[rr][cc][1];
-              o2 = hs[rr][cc][2];
-            }
-        if (gy < H && gx < W) {
-          const size_t HW = (size_t)H * W, p = (size_t)gy * W + gx;
-          head_out[p] = o0 + a.head_b[0];
-          head_out[HW + p] = o1 + a.head_b[1];
-          head_out[2 * HW + p] = o2 + a.head_b[2];
+            for (int k = 0; k < 3; ++k) head_out[k * HWp + px] = o[k];
+          }
         }
       }
-    }
-  };
-
-  // The chunks of this workgroup's tiles form one stream: chunk step t is
-  // multiplied from LDS buffer t & 1 while step t + 1 (the next chunk of the
-  // tile, or the first chunk of the next tile) is fetched into registers; it
-  // is then written to the other buffer, which every wave finished reading
-  // before the previous barrier.  After a tile's last chunk the epilogue runs
-  // on the buffer just finished, so the next tile's first chunk is already
-  // staged when its multiplications start.
-  if (t_first >= t_end) return;
-  const int nch = Cin / CK;
-  TileId cur = decode(t_first);
-  set_fetch_tile(cur);
-  {
-    uint4 v[NIN], w[NWR];
-    fetch_in(0, v);
-    fetch_w(0, w);
-    store_in(0, v);
-    store_w(0, w);
-  }
-  __syncthreads();
-  zero_acc();
-  uint4 v[NIN], w[NWR];
-  int T = t_first, c = 0, buf = 0;
-  for (;;) {
-    const bool last = c + 1 == nch;
-    const int Tn = last ? T + t_step : T;
-    const bool more = Tn < t_end;
-    TileId nxt = cur;
-    if (more) {
-      if (last) {
-        nxt = decode(Tn);
-        set_fetch_tile(nxt);
-      }
-      const int cn = last ? 0 : (c + 1) * CK;
-      fetch_w(cn, w);
-      fetch_in(cn, v);
-    } else {
-      // (defined values on every path keep the arrays in registers)
-#pragma unroll
-      for (int k = 0; k < NWR; ++k) w[k] = make_uint4(0u, 0u, 0u, 0u);
-#pragma unroll
-      for (int k = 0; k < NIN; ++k) v[k] = make_uint4(0u, 0u, 0u, 0u);
-    }
-    compute(buf);  // one call site: the accumulators stay in place
-    const int other = buf == 0 ? B1 : 0;
-    if (more) {
-      store_in(other, v);
-      store_w(other, w);
-    }
-    __syncthreads();
-    if (last) {
-      epilogue(smem + (buf == 0 ? 0 : BUF), cur);
-      if (!more) break;
-      __syncthreads();  // E is read before the buffer is staged again
       zero_acc();
-      cur = nxt;
-      T = Tn;
       c = 0;
-    } else {
-      ++c;
+      ++tile;
+      ++T;
     }
-    buf = other;
   }
 }
 
-// 1x1 head of a layer too wide to fuse it: weights [3][C], one thread per
-// pixel, planar output
-__global__ __launch_bounds__(256) void head32_kernel(const float *__restrict__ x, int C, int npix,
-                                                     const float *__restrict__ w, const float *__restrict__ b,
-                                                     float *__restrict__ out) {
-  const int p = blockIdx.x * 256 + threadIdx.x;
-  if (p >= npix) return;
-  float y0 = b[0], y1 = b[1], y2 = b[2];
-  for (int c = 0; c < C; c += 4) {
-    const float4 q = *reinterpret_cast<const float4 *>(x + (size_t)p * C + c);
-    const float v[4] = {q.x, q.y, q.z, q.w};
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      y0 = fmaf(w[c + i], v[i], y0);
-      y1 = fmaf(w[C + c + i], v[i], y1);
-      y2 = fmaf(w[2 * C + c + i], v[i], y2);
+// Launch of the float32 layers but the first, in two tile sizes: 32 channels
+// (M = 2) and 16 (M = 1), which fills the chip earlier, wastes nothing on 16 and
+// 48 channels, and repeats the input's transform for every 16.
+struct WinoGrid {
+  int units, group;  // workgroups at one run each, channel tiles that stay in one (with the fused head: all)
+  float cost;
+};
+template <int M>
+WinoGrid wino_grid(const ConvCall &c) {
+  const int batch = c.batch < 1 ? 1 : c.batch, ncz = (c.layer->cout + M * 16 - 1) / (M * 16);
+  WinoGrid g;
+  g.group = c.head_out || c.head_outs ? ncz : 1;
+  g.units = (c.W + 31) / 32 * ((c.H + WinoLds<M, false>::TH - 1) / WinoLds<M, false>::TH) * (ncz / g.group) * batch;
+  // Microseconds per chunk of 8 input channels that 1, 2 (and 3, M = 1)
+  // workgroups together on a CU took; a CU has no room for more.
+  static constexpr float kStep[2][4] = {{0.f, 1.1f, 1.6f, 2.2f}, {0.f, 1.5f, 2.5f, 0.f}};
+  constexpr int full = M == 1 ? 3 : 2;
+  const int k = (g.units + kCUs - 1) / kCUs;
+  g.cost = g.group * ((float)(k / full) * kStep[M - 1][full] + kStep[M - 1][k % full]);
+  return g;
+}
+template <int M>
+hipError_t wino_tiles(const ConvCall &c, const WinoGrid &g, hipStream_t s) {
+  Args a = make_args(c);
+  a.w = static_cast<const char *>(c.layer->wu);
+  // Short layers (at most 96 input channels) of many tiles: runs of up to 4
+  // tiles per workgroup, whose start then hides behind the tiles before (1080p,
+  // 32 -> 32 channels: 222 us in runs of one, 205 of four; 64 -> 64: 181, 178;
+  // 128 -> 128: 167, 168).  With few tiles, or longer ones, a run only leaves
+  // CUs idle at the end (256 -> 256 at 240 x 135: 204, 332).
+  const int slots = (M == 1 ? 3 : 2) * kCUs, steps = g.group * ((a.C0 + a.C1) / 8);
+  int run = 1;
+  if (steps <= 12 && g.units >= 4 * slots) {
+    long long best = 0;
+    for (int r = 1; r <= 4; ++r) {
+      const long long t = (g.units + (long long)r * slots - 1) / ((long long)r * slots) * (r * (steps + 1) + 1);
+      if (!best || t < best) best = t, run = r;
     }
   }
-  out[p] = y0;
-  out[(size_t)npix + p] = y1;
-  out[2 * (size_t)npix + p] = y2;
-}
-
-constexpr long kSmallGrid = 768;
-
-// Float32 layers whose inputs come in chunks of 16 channels (all but the
-// first) run as Winograd F(2x2, 3x3) in persistent workgroups, one resident
-// per CU (LDS), each walking its share of the 8 x 32 pixel tiles.
-template <int MB, int CK>
-hipError_t wino_launch_mc(const ConvArgs &a, int cout_pad, bool head, hipStream_t s) {
-  const int ntx = (a.W + 31) / 32, nty = (a.H + 7) / 8;
-  const int nzc = cout_pad / (32 * MB), ntiles = ntx * nty * nzc * a.batch;
-  static std::atomic<int> cus[64];
-  int dev = 0;
-  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return hipErrorInvalidDevice;
-  int n = cus[dev].load(std::memory_order_relaxed);
-  if (n == 0) {
-    if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n <= 0)
-      return hipErrorInvalidDevice;
-    cus[dev].store(n, std::memory_order_relaxed);
-  }
-  const int grid = ntiles < n ? ntiles : n;
-  if (head)
-    wino3x3_kernel<true, MB, CK><<<grid, 512, 0, s>>>(a, ntx, nty, nzc, ntiles);
+  const int batch = c.batch < 1 ? 1 : c.batch, cout = (a.cout + M * 16 - 1) / (M * 16) * (M * 16);
+  const int grid = set_tiles(a, WinoLds<M, false>::TH, M * 16, cout, batch, run * g.group, g.group);
+  if (c.head_out || c.head_outs)
+    wino_kernel<M, true><<<grid, 256, 0, s>>>(a);
   else
-    wino3x3_kernel<false, MB, CK><<<grid, 512, 0, s>>>(a, ntx, nty, nzc, ntiles);
+    wino_kernel<M, false><<<grid, 256, 0, s>>>(a);
   return hipGetLastError();
 }
-// Layers with a multiple of 64 output channels: tiles of 64 channels (each
-// wave reuses its input fragments for two MFMA blocks), staged 8 input
-// channels at a time (two LDS buffers of U for 64 channels must fit), unless
-// one image gives fewer than kSmallGrid such tiles (the 135x240 level of a
-// 1080p frame), where 32-channel tiles keep every CU busy; a layer with the
-// fused head needs all its channels (at most 64) in one tile.  Others: 32
-// channels, 16 input channels at a time.  Both take the same sums in the same
-// order, so the choice does not change results.
-hipError_t wino_launch(const ConvArgs &a, int cout_pad, bool head, hipStream_t s) {
-  const long tiles64 = (long)((a.W + 31) / 32) * ((a.H + 7) / 8) * (cout_pad / 64);
-  if (cout_pad % 64 == 0 && (tiles64 >= kSmallGrid || head)) return wino_launch_mc<2, 8>(a, cout_pad, head, s);
-  return wino_launch_mc<1, 16>(a, cout_pad, head, s);
+hipError_t wino_launch(const ConvCall &c, hipStream_t s) {
+  const WinoGrid g1 = wino_grid<1>(c), g2 = wino_grid<2>(c);
+  return g1.cost < g2.cost ? wino_tiles<1>(c, g1, s) : wino_tiles<2>(c, g2, s);
 }
 
-hipError_t first_launch(const ConvArgs &a, int cout_pad, hipStream_t s) {
-  const int bm = cout_pad % 64 == 0 ? 64 : 32;
-  const dim3 grid((a.W + 31) / 32, (a.H + 7) / 8, (cout_pad / bm) * a.batch);
+hipError_t first_launch(const ConvCall &c, hipStream_t s) {
+  const Args a = make_args(c);
+  const int cout_pad = c.layer->cout_pad, bm = cout_pad % 64 == 0 ? 64 : 32;
+  const dim3 grid((a.W + 31) / 32, (a.H + 7) / 8, (cout_pad / bm) * (c.batch < 1 ? 1 : c.batch));
   if (bm == 64)
     first3x3_kernel<64, 2><<<grid, 256, 0, s>>>(a);
   else
@@ -625,26 +575,19 @@ hipError_t first_launch(const ConvArgs &a, int cout_pad, hipStream_t s) {
 hipError_t launch_conv3x3(const ConvCall &c, Prec p, hipStream_t s) {
   if (p != Prec::F32) return launch_conv16(c, p, s);
   const ConvLayer &L = *c.layer;
-  const ConvArgs a{c.in0, c.in1, c.C0, c.C1, c.H, c.W, L.w, L.bias, L.cout, L.cin_pad, c.out, c.out_pool,
-                   c.head_w, c.head_b, c.head_out, c.batch < 1 ? 1 : c.batch, c.in0_bs / 4, c.in1_bs / 4,
-                   c.out_bs / 4, c.pool_bs / 4, c.head_outs, c.rgbda_depth, c.rgbda_rgba, c.rgbda_bs,
-                   static_cast<const float *>(L.wu)};
   const bool head = c.head_out || c.head_outs;
   if (head && (L.cout_pad > 64 || c.out_pool)) return hipErrorInvalidValue;
   if (c.rgbda_depth) {
     if (!c.rgbda_rgba || c.C1 != 0 || L.cin_pad != 8 || head || c.out_pool) return hipErrorInvalidValue;
-    return first_launch(a, L.cout_pad, s);
+    return first_launch(c, s);
   }
   if (!L.wu || c.C0 % 16 || c.C1 % 16 || c.C0 + c.C1 != L.cin_pad) return hipErrorInvalidValue;
-  return wino_launch(a, L.cout_pad, head, s);
+  if ((c.C1 || c.out_pool) && (c.H % 2 || c.W % 2)) return hipErrorInvalidValue;
+  return wino_launch(c, s);
 }
 
 hipError_t launch_head(const void *x, int C, int H, int W, const ConvLayer &head, Prec p, float *out, hipStream_t s) {
-  if (p != Prec::F32) return launch_head16(x, C, H, W, head, p, out, s);
-  const int npix = H * W;
-  head32_kernel<<<(npix + 255) / 256, 256, 0, s>>>(static_cast<const float *>(x), C, npix,
-                                                   static_cast<const float *>(head.w), head.bias, out);
-  return hipGetLastError();
+  return launch_head16(x, C, H, W, head, p, out, s);
 }
 
 }  // namespace lnr
