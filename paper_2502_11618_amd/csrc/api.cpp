@@ -720,7 +720,7 @@ static std::array<Buf *, 7> tiled_scratch(Scratch &scr) {
 }
 static std::array<size_t, 7> tiled_bytes(const TiledSplatGrid &g, uint32_t n_points, int n_views) {
   const size_t n = std::max<uint32_t>(1, n_points), v = (size_t)n_views;
-  return {8 * n * v, 16 * g.seg_cap * v, 4 * g.seg_cap * v, 8ull * g.n_tiles * v, (4ull * g.n_tiles + 4) * v, 4ull * g.n_tiles * v,
+  return {8 * n * v, 16 * g.seg_cap * v, 4 * g.seg_cap * v, 4ull * kTileCountWords * g.n_tiles * v, (4ull * g.n_tiles + 4) * v, 4ull * g.n_tiles * v,
           8ull * g.unit_cap * v};
 }
 static lnr_status ensure_tiled(lnr_context *ctx, Scratch &scr, const TiledSplatGrid &g, uint32_t n_points,
@@ -739,7 +739,7 @@ static TiledSplatBufs tiled_bufs(Scratch &scr, const TiledSplatGrid &g, uint32_t
   return TiledSplatBufs{static_cast<uint64_t *>(scr.recs.p) + v * n,
                         static_cast<uint4 *>(scr.segs.p) + v * g.seg_cap,
                         static_cast<uint32_t *>(scr.sorted.p) + v * g.seg_cap,
-                        static_cast<uint32_t *>(scr.tile_nseg.p) + v * 2 * g.n_tiles,
+                        static_cast<uint32_t *>(scr.tile_nseg.p) + v * kTileCountWords * g.n_tiles,
                         static_cast<uint32_t *>(scr.tile_off.p) + v * (g.n_tiles + 1),
                         static_cast<uint32_t *>(scr.tile_units.p) + v * g.n_tiles,
                         static_cast<uint2 *>(scr.units.p) + v * g.unit_cap};
@@ -840,7 +840,7 @@ static lnr_status render_impl(lnr_context *ctx, Scratch &scr, const lnr_cloud *c
   // keys of the tiles that merge through atomics, so only the counters here)
   LNR_LAUNCH(ctx, "clear", s,
              launch_clear(out->key, atomic ? npix : 0u, counters, kCounterWords,
-                          static_cast<uint32_t *>(scr.tile_nseg.p), atomic ? 0u : 2 * tg.n_tiles, s));
+                          static_cast<uint32_t *>(scr.tile_nseg.p), atomic ? 0u : kTileCountWords * tg.n_tiles, s));
   LNR_LAUNCH(ctx, "cull", s,
              launch_cull(c->d, prm, dev ? &dev->cull : nullptr, static_cast<uint8_t *>(scr.flags.p),
                          static_cast<uint2 *>(scr.chunks.p), atomic ? kSplatChunk : c->d.item_points, counters,
@@ -900,7 +900,7 @@ static lnr_status render_tiled_views(lnr_context *ctx, Scratch &scr, const lnr_c
   }
   LNR_LAUNCH(ctx, "clear", s,
              launch_clear(nullptr, 0u, counters, (uint32_t)(n * kViewCounterWords),
-                          static_cast<uint32_t *>(scr.tile_nseg.p), 2 * g.n_tiles * (uint32_t)n, s));
+                          static_cast<uint32_t *>(scr.tile_nseg.p), kTileCountWords * g.n_tiles * (uint32_t)n, s));
   LNR_LAUNCH(ctx, "cull_views", s,
              launch_cull_views(c->d, vc, dev, static_cast<uint8_t *>(scr.flags.p), items, c->d.item_points, counters,
                                s));

@@ -122,7 +122,7 @@ hipError_t launch_chunk_count(const uint32_t *cell_start, uint32_t n_cells, uint
 
 // render.hip
 // per-frame reset of the key buffer (npix words), n_counters words of the
-// counters and n_tiles words of the tiled splat's per-tile segment counts
+// counters and n_tiles words of the tiled splat's per-tile counts
 hipError_t launch_clear(uint64_t *key, uint32_t npix, uint32_t *counters, uint32_t n_counters, uint32_t *tile_nseg,
                         uint32_t n_tiles, hipStream_t s);
 // Screen-tiled splat (32 x 32 pixel tiles), in up to six launches (stage
@@ -131,9 +131,11 @@ hipError_t launch_clear(uint64_t *key, uint32_t npix, uint32_t *counters, uint32
 // only for the soft z-buffer).  Scratch per
 // render for a cloud of n points: recs u64[n] (a work item's records at its
 // points' positions), segs uint4[seg_cap] and sorted u32[seg_cap] (at most one
-// segment per record, and one per work item and tile), tile_nseg u32[2 n_tiles] (the counts, then the merged sort's
-// fill counters), tile_units u32[n_tiles], tile_off u32[n_tiles + 1], units
-// uint2[unit_cap].
+// segment per record, and one per work item and tile), tile_nseg
+// u32[kTileCountWords n_tiles] (per tile a u64, records << 32 | segments, then
+// the merged sort's fill counters; zeroed by launch_clear), tile_units
+// u32[n_tiles], tile_off u32[n_tiles + 1], units uint2[unit_cap].
+constexpr uint32_t kTileCountWords = 4;  // (even: the next view's u64 counts stay aligned)
 struct TiledSplatGrid {
   uint32_t tiles_x = 0, tiles_y = 0, n_tiles = 0;
   uint64_t seg_cap = 0, unit_cap = 0;
@@ -164,8 +166,7 @@ struct TiledSplatView {
   void *acc;
 };
 // true when the per-tile scan runs inside the segment sort (stage 1 then
-// launches nothing); tile_nseg then holds 2 n_tiles words: the counts, then
-// the fill counters of the sort, both zeroed by launch_clear
+// launches nothing)
 bool tiled_scan_merged(const TiledSplatView *views, int n);
 // work: the counters of the culling pass
 hipError_t launch_tiled_splat(const CloudDev &c, const uint2 *chunks, const uint32_t *work, const TiledSplatView &view,

@@ -499,7 +499,8 @@ __global__ __launch_bounds__(kThreads) void splat_views_kernel(const float *__re
 //             screen tile, as 8-byte records at the work item's own place in
 //             the record array.  Each (work item, tile) group is a segment.
 //   tilescan  one workgroup: per-tile segment offsets, and the units of work
-//             of the tile kernel: up to kSegsPerUnit segments of one tile.
+//             of the tile kernel: up to kSegsPerUnit segments, or a few
+//             thousand records, of one tile.
 //   segsort   groups the segment ids by tile, and empties the keys of the
 //             tiles of more than one unit (the only keys not written whole).
 //             Up to kMaxScanTiles tiles, segscan_kernel does both in one
@@ -524,6 +525,15 @@ constexpr int kTileSide = 1 << kTileShift;
 constexpr int kTilePx = kTileSide * kTileSide;
 constexpr int kHistBins = 1024;  // tiles one binning pass can address
 constexpr int kSegsPerUnit = 32;
+// Records per unit, about (see units_of).  Up to kFewTiles tiles (fewer
+// workgroups than the chip takes at once) the smaller: soft z-buffer of 2.8 M
+// points at 604 x 604: 139 us by segments alone, 92 with 4096, 85 with 2048.  Above
+// it the merging of more units costs more than it evens out: 100 M points at
+// 2560 x 1440: 340 us with 2048, 323 with 4096.
+constexpr uint32_t kFewTiles = 1024, kRecsPerUnitFew = 2048, kRecsPerUnitMany = 4096;
+__host__ __device__ inline uint32_t recs_per_unit(uint32_t n_tiles) {
+  return n_tiles <= kFewTiles ? kRecsPerUnitFew : kRecsPerUnitMany;
+}
 constexpr int kRecOffsetBits = 14;  // of a record: the point's offset in its work item
 static_assert(kBinDense <= 1u << kRecOffsetBits, "a record keeps the point offset within its work item");
 
@@ -566,7 +576,8 @@ struct TiledView {
   uint32_t *counters;  // kSegTopWord, kUnitsWord
   uint64_t *recs;
   uint4 *segs;
-  uint32_t *sorted, *tile_nseg, *tile_off, *tile_units;
+  unsigned long long *tile_nseg;  // per tile: records << 32 | segments; then u32 tile_fill per tile
+  uint32_t *sorted, *tile_off, *tile_units;
   uint2 *units;
   uint64_t *key;
   float *depth;
@@ -607,7 +618,7 @@ __global__ __launch_bounds__(NT, 4) void bin_kernel(const float *__restrict__ xs
   uint32_t *__restrict__ counters = a.counters;
   uint64_t *__restrict__ recs = a.recs;
   uint4 *__restrict__ segs = a.segs;
-  uint32_t *__restrict__ tile_nseg = a.tile_nseg;
+  unsigned long long *__restrict__ tile_nseg = a.tile_nseg;
   constexpr int kBlocks = BinItem<NT>::kBlocks, kWaves = NT / 64, kPts = 16;
   constexpr int kZb = ALL ? kHistBins / 2 : kBlocks * 64;
   __shared__ unsigned long long s_zb[kZb];  // z-buffer; or the tile histogram
@@ -733,7 +744,7 @@ __global__ __launch_bounds__(NT, 4) void bin_kernel(const float *__restrict__ xs
       base = __shfl(base, 0, 64);
       if (cnt) {
         segs[base + (uint32_t)__popcll(m & ((1ull << lane) - 1ull))] = make_uint4(tile, ch.x + first, cnt, ch.x);
-        atomicAdd(&tile_nseg[tile], 1u);
+        atomicAdd(&tile_nseg[tile], ((unsigned long long)cnt << 32) | 1ull);
       }
     }
     for (uint32_t b = wave; b < nblk; b += kWaves) {
@@ -800,7 +811,7 @@ __global__ __launch_bounds__(NT, 4) void bin_kernel(const float *__restrict__ xs
             const uint32_t tb = c0 + b;
             const uint32_t tile = (r0 + tb / tbw) * tg.tiles_x + (tx0 + tb % tbw);
             segs[seg_base + (run & 0xFFFFu)] = make_uint4(tile, ch.x + first, cnt[q], ch.x);
-            atomicAdd(&tile_nseg[tile], 1u);
+            atomicAdd(&tile_nseg[tile], ((unsigned long long)cnt[q] << 32) | 1ull);
           }
           s_hist[b] = first;  // bin -> cursor at its first record
           run += (cnt[q] << 16) | (cnt[q] ? 1u : 0u);
@@ -822,15 +833,26 @@ __global__ __launch_bounds__(NT, 4) void bin_kernel(const float *__restrict__ xs
   }
 }
 
+// Units of a tile (count: records << 32 | segments): enough for kSegsPerUnit
+// segments and about recs_per_unit() records each.  Where a near surface puts many
+// points of a few work items on a tile, the segments alone would leave one
+// workgroup with up to 32 x 8 K records while the others are done.
+__device__ inline uint32_t units_of(unsigned long long count, uint32_t n_tiles) {
+  const uint32_t ns = (uint32_t)count, nr = (uint32_t)(count >> 32), recs = recs_per_unit(n_tiles);
+  const uint32_t nu = max((ns + kSegsPerUnit - 1) / kSegsPerUnit, (nr + recs - 1) / recs);
+  return max(1u, min(nu, ns));
+}
+// segments per unit of a tile of ns segments and nu units (at most kSegsPerUnit)
+__device__ inline uint32_t unit_segs(uint32_t ns, uint32_t nu) { return (ns + nu - 1) / nu; }
+
 // One workgroup: per-tile segment offsets (tile_off[n_tiles + 1]) and the
-// units of the tile kernel: a tile with s segments gets max(1, ceil(s /
-// kSegsPerUnit)) units (tile_units[t]); units[u] = (tile, first segment of
-// the unit within the tile); counters[kUnitsWord] = number of units.
+// units of the tile kernel: tile_units[t] of them; units[u] = (tile, first
+// segment of the unit within the tile); counters[kUnitsWord] = number of units.
 constexpr int kScanThreads = 1024;
 template <int NV>
 __global__ __launch_bounds__(kScanThreads) void tilescan_kernel(TiledViews<NV> vs) {
   const TiledView &a = this_view(vs);
-  const uint32_t *__restrict__ tile_nseg = a.tile_nseg;
+  const unsigned long long *__restrict__ tile_nseg = a.tile_nseg;
   const TileGrid tg = a.tg;
   uint32_t *__restrict__ tile_off = a.tile_off, *__restrict__ tile_units = a.tile_units;
   uint2 *__restrict__ units = a.units;
@@ -841,8 +863,8 @@ __global__ __launch_bounds__(kScanThreads) void tilescan_kernel(TiledViews<NV> v
   uint32_t seg_base = 0, unit_base = 0;
   for (uint32_t t0 = 0; t0 < tg.n_tiles; t0 += kScanThreads) {
     const uint32_t t = t0 + tid;
-    const uint32_t ns = t < tg.n_tiles ? tile_nseg[t] : 0u;
-    const uint32_t nu = t < tg.n_tiles ? max(1u, (ns + kSegsPerUnit - 1) / kSegsPerUnit) : 0u;
+    const unsigned long long count = t < tg.n_tiles ? tile_nseg[t] : 0ull;
+    const uint32_t ns = (uint32_t)count, nu = t < tg.n_tiles ? units_of(count, tg.n_tiles) : 0u, per = unit_segs(ns, max(1u, nu));
     uint32_t tot_s, tot_u;
     const uint32_t es = block_exclusive_scan<kScanThreads>(ns, s_tmp, &tot_s);
     const uint32_t eu = block_exclusive_scan<kScanThreads>(nu, s_tmp, &tot_u);
@@ -850,7 +872,7 @@ __global__ __launch_bounds__(kScanThreads) void tilescan_kernel(TiledViews<NV> v
       tile_off[t] = seg_base + es;
       tile_units[t] = nu;
       for (uint32_t k = 0; k < nu; ++k)
-        if (unit_base + eu + k < unit_cap) units[unit_base + eu + k] = make_uint2(t, k * kSegsPerUnit);
+        if (unit_base + eu + k < unit_cap) units[unit_base + eu + k] = make_uint2(t, k * per);
     }
     seg_base += tot_s;
     unit_base += tot_u;
@@ -863,7 +885,7 @@ __global__ __launch_bounds__(kScanThreads) void tilescan_kernel(TiledViews<NV> v
 
 // Segment ids grouped by tile: segment i of tile t goes to one of the places
 // [tile_off[t], tile_off[t + 1]) (their order is irrelevant: the tile kernel
-// takes a minimum).  Counts tile_nseg back down to zero.  Also empties the
+// takes a minimum).  Counts tile_nseg's segments back down to zero.  Also empties the
 // key buffer over the tiles of more than one unit, whose units merge into it
 // with atomicMin (the tile kernel writes every other tile's keys whole), and
 // zeroes their colour sums (acc, the soft z-buffer).
@@ -873,7 +895,7 @@ __global__ __launch_bounds__(kThreads) void segsort_kernel(TiledViews<NV> vs) {
   const uint4 *__restrict__ segs = a.segs;
   const uint32_t *__restrict__ counters = a.counters, *__restrict__ tile_off = a.tile_off;
   const uint32_t *__restrict__ tile_units = a.tile_units;
-  uint32_t *__restrict__ tile_nseg = a.tile_nseg, *__restrict__ sorted = a.sorted;
+  uint32_t *__restrict__ tile_nseg = reinterpret_cast<uint32_t *>(a.tile_nseg), *__restrict__ sorted = a.sorted;
   const TileGrid tg = a.tg;
   const uint32_t W = a.W, H = a.H;
   uint64_t *__restrict__ key = a.key;
@@ -881,7 +903,7 @@ __global__ __launch_bounds__(kThreads) void segsort_kernel(TiledViews<NV> vs) {
   const uint32_t n = counters[kSegTopWord];
   for (uint32_t i = blockIdx.x * kThreads + threadIdx.x; i < n; i += gridDim.x * kThreads) {
     const uint32_t t = segs[i].x;
-    sorted[tile_off[t] + atomicSub(&tile_nseg[t], 1u) - 1u] = i;
+    sorted[tile_off[t] + atomicSub(&tile_nseg[2 * t], 1u) - 1u] = i;
   }
   for (uint32_t t = blockIdx.x; t < tg.n_tiles; t += gridDim.x) {
     if (tile_units[t] <= 1) continue;  // (the same for the whole block)
@@ -914,8 +936,8 @@ __global__ __launch_bounds__(kThreads) void segscan_kernel(TiledViews<NV> vs) {
   const uint4 *__restrict__ segs = a.segs;
   uint32_t *__restrict__ counters = a.counters;
   const TileGrid tg = a.tg;
-  const uint32_t *__restrict__ tile_nseg = a.tile_nseg;
-  uint32_t *__restrict__ tile_fill = a.tile_nseg + tg.n_tiles, *__restrict__ tile_off = a.tile_off;
+  const unsigned long long *__restrict__ tile_nseg = a.tile_nseg;
+  uint32_t *__restrict__ tile_fill = reinterpret_cast<uint32_t *>(a.tile_nseg + tg.n_tiles), *__restrict__ tile_off = a.tile_off;
   uint32_t *__restrict__ tile_units = a.tile_units, *__restrict__ sorted = a.sorted;
   uint2 *__restrict__ units = a.units;
   const uint32_t unit_cap = a.unit_cap, W = a.W, H = a.H;
@@ -931,22 +953,23 @@ __global__ __launch_bounds__(kThreads) void segscan_kernel(TiledViews<NV> vs) {
   const uint32_t t_lo = min(tg.n_tiles, tid * per), t_hi = min(tg.n_tiles, t_lo + per);
   uint32_t my_s = 0, my_u = 0;
   for (uint32_t t = t_lo; t < t_hi; ++t) {
-    const uint32_t ns = tile_nseg[t];
-    my_s += ns;
-    my_u += max(1u, (ns + kSegsPerUnit - 1) / kSegsPerUnit);
+    const unsigned long long count = tile_nseg[t];
+    my_s += (uint32_t)count;
+    my_u += units_of(count, tg.n_tiles);
   }
   uint32_t tot_s, tot_u;
   uint32_t seg = block_exclusive_scan<kThreads>(my_s, s_tmp, &tot_s);
   uint32_t unit = block_exclusive_scan<kThreads>(my_u, s_tmp, &tot_u);
   for (uint32_t t = t_lo; t < t_hi; ++t) {
-    const uint32_t ns = tile_nseg[t];
-    const uint32_t nu = max(1u, (ns + kSegsPerUnit - 1) / kSegsPerUnit);
+    const unsigned long long count = tile_nseg[t];
+    const uint32_t ns = (uint32_t)count, nu = units_of(count, tg.n_tiles);
     s_off[t] = seg;
     if (first) {
       tile_off[t] = seg;
       tile_units[t] = nu;
+      const uint32_t unit_len = unit_segs(ns, nu);
       for (uint32_t k = 0; k < nu; ++k)
-        if (unit + k < unit_cap) units[unit + k] = make_uint2(t, k * kSegsPerUnit);
+        if (unit + k < unit_cap) units[unit + k] = make_uint2(t, k * unit_len);
     }
     seg += ns;
     unit += nu;
@@ -965,7 +988,7 @@ __global__ __launch_bounds__(kThreads) void segscan_kernel(TiledViews<NV> vs) {
     sorted[s_off[t] + atomicAdd(&tile_fill[t], 1u)] = i;
   }
   for (uint32_t t = blockIdx.x; t < tg.n_tiles; t += gridDim.x) {
-    if (s_off[t + 1] - s_off[t] <= (uint32_t)kSegsPerUnit) continue;  // one unit (the same for the whole block)
+    if (units_of(tile_nseg[t], tg.n_tiles) == 1) continue;  // (the same for the whole block)
     const uint32_t tx = t % tg.tiles_x, ty = t / tg.tiles_x;
     for (int p = tid; p < kTilePx; p += kThreads) {
       const uint32_t gx = (tx << kTileShift) + (p & (kTileSide - 1));
@@ -1091,7 +1114,8 @@ __global__ __launch_bounds__(NT) void tile_kernel(TiledViews<NV> vs, const uint3
   for (uint32_t u = blockIdx.x; u < n_units; u += gridDim.x) {
     const uint2 un = units[u];
     const uint32_t t = un.x;
-    const uint32_t beg = tile_off[t] + un.y, end = min(tile_off[t + 1], beg + kSegsPerUnit);
+    const uint32_t off = tile_off[t], next = tile_off[t + 1];
+    const uint32_t beg = off + un.y, end = min(next, beg + unit_segs(next - off, tile_units[t]));
     const uint32_t nb = end > beg ? end - beg : 0u;
     const bool alone = tile_units[t] == 1;
     for (int p = tid; p < kTilePx; p += NT) zb[p] = ~0ull;
@@ -1159,7 +1183,8 @@ __global__ __launch_bounds__(NT) void soft_units_kernel(TiledViews<1> vs, const 
     const uint2 un = units[u];
     const uint32_t t = un.x;
     if (tile_units[t] == 1) continue;  // (the same for the whole block)
-    const uint32_t beg = tile_off[t] + un.y, end = min(tile_off[t + 1], beg + kSegsPerUnit);
+    const uint32_t off = tile_off[t], next = tile_off[t + 1];
+    const uint32_t beg = off + un.y, end = min(next, beg + unit_segs(next - off, tile_units[t]));
     const uint32_t nb = end > beg ? end - beg : 0u;
     const uint32_t tx = t % tg.tiles_x, ty = t / tg.tiles_x;
     auto pixel = [&](int p, size_t *i) {
@@ -1328,8 +1353,8 @@ TiledSplatGrid tiled_splat_grid(uint32_t W, uint32_t H, const CloudDev &c) {
   g.tiles_y = (H + kTileSide - 1) >> kTileShift;
   g.n_tiles = g.tiles_x * g.tiles_y;
   g.seg_cap = std::max<uint64_t>(1, std::min<uint64_t>(c.n, (uint64_t)c.max_items * g.n_tiles));
-  // a tile with s segments has max(1, ceil(s / kSegsPerUnit)) units
-  g.unit_cap = 2ull * g.n_tiles + g.seg_cap / kSegsPerUnit + 1;
+  // units_of() of every tile: at most 1 + s / kSegsPerUnit + r / recs_per_unit() for s segments and r records
+  g.unit_cap = 2ull * g.n_tiles + g.seg_cap / kSegsPerUnit + c.n / kRecsPerUnitFew + 1;
   return g;
 }
 
@@ -1344,8 +1369,8 @@ hipError_t tiled_stage(const CloudDev &c, const void *items, const uint32_t *wor
     const TiledSplatView &w = views[i < n ? i : 0];
     const TiledSplatGrid g = tiled_splat_grid(w.cam.W, w.H, c);
     vs.v[i] = TiledView{w.cam, w.cam_dev, w.cam.W, w.H, (uint32_t)g.unit_cap,
-                        TileGrid{g.tiles_x, g.tiles_y, g.n_tiles}, w.counters, w.b.recs, w.b.segs, w.b.sorted,
-                        w.b.tile_nseg, w.b.tile_off, w.b.tile_units, w.b.units, w.key, w.depth, w.rgba,
+                        TileGrid{g.tiles_x, g.tiles_y, g.n_tiles}, w.counters, w.b.recs, w.b.segs,
+                        reinterpret_cast<unsigned long long *>(w.b.tile_nseg), w.b.sorted, w.b.tile_off, w.b.tile_units, w.b.units, w.key, w.depth, w.rgba,
                         static_cast<uint4 *>(w.acc)};
     most_tiles = std::max(most_tiles, g.n_tiles);
     tile_grid = std::max(tile_grid,

@@ -90,3 +90,24 @@ def test_views_of_many_tiles(lnr, ctx, room_cloud, room_cams):
     for cam, img in zip(cams, _views(lnr, ctx, room_cloud, cams)):
         assert_images_equal(image_to_host(img), image_to_host(render_gpu(lnr, ctx, room_cloud, cam)),
                             f"{cam.width}x{cam.height}")
+
+
+@pytest.mark.parametrize("W", [1024, 1056])
+@pytest.mark.parametrize("n", [2048, 2049, 4097, 8193, 12289, 40000])
+def test_units_by_records(lnr, ctx, W, n):
+    """All points on two tiles, which take one unit of work per 2048 entries in
+    images of up to 1024 tiles and per 4096 in larger ones, but never more
+    units than segments (one per work item and tile)."""
+    import torch
+    print("units", W, n, flush=True)
+    H = 1024
+    xyz, rgb, cam = _cloud(np.random.default_rng(n), n, 500, 520, 24, 20, W, H)
+    g = G.partition(xyz, rgb, 100.0)
+    cloud = lnr.lnr_cloud_load(ctx, xyz, rgb, 100.0)
+    want = R.render(g, cam)
+    assert_images_equal(image_to_host(render_gpu(lnr, ctx, cloud, cam)), want, "hard")
+    img = lnr.Image(H, W)
+    lnr.lnr_render_soft(ctx, cloud, cam, img, 0.3)
+    torch.cuda.synchronize()
+    soft = R.soft_colors(g.xs, g.ys, g.zs, g.rgb, cam.P, W, H, cam.z_near, cam.z_far, want[0], 0.3)
+    assert_images_equal(image_to_host(img), (want[0], want[1], soft), "soft")
