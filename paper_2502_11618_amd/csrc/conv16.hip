@@ -161,60 +161,62 @@ struct FragOf<4> {
   using type = uint2;  // 8 e4m3 per lane
 };
 
-// One staged chunk of 16 input channels.  A step is one horizontal tap offset
-// dx: R + 2 input-row fragments and 3 MB weight fragments, which feed every
-// input row to the up-to-three vertical taps that use it.  A: this lane's
-// weights (half h, channel n of the chunk's first channel tile), B: this lane's
-// pixel (its wave's first halo row, column n); UBP: units per staged channel
-// block, LW: units per staged row.
-template <int MODE, int MB, int R>
-struct Frags {
-  typename FragOf<MODE>::type a[MB][3][Fmt<MODE>::kPlanes], b[R + 2][Fmt<MODE>::kPlanes];
-};
-template <int MODE, int MB, int R, int UBP, int LW>
-__device__ inline void read_frags(const char *A, const char *B, int dx, Frags<MODE, MB, R> &f) {
+// One staged chunk of 16 input channels: nine taps, horizontal offset dx outer,
+// vertical offset dy inner.  An input row's fragment, read once per dx, feeds
+// the up to three taps that use it.  A: this lane's weights (half h, channel n
+// of the chunk's first channel tile), B: this lane's pixel (its wave's first
+// halo row, column n); UBP: units per staged channel block, LW: units per staged
+// row.  A tap's fragments are read kAhead taps (8 matrix instructions or more)
+// before it, and load(-1), which prepares the loads of later steps, and load(0
+// .. LOADS - 1), which start them, stand between the matrix instructions of the
+// first six taps, which hide their scalar instructions.  PIN keeps the compiler to that order; with the
+// loads in front of the chunk and the reads in its own order the largest
+// 512-channel layers at 240 x 135 took 319 us for 300, 13 x 13 pixels
+// with split e4m3 operands 52.8 for 42.2; a kernel of one chunk is better left
+// to it (37.4 for 35.3 us).  Branches around the loads past the last step cost
+// more than the masked loads (208 x 208, split e4m3: 371 for 330 us), and a second
+// copy of the chunk without loads spills.
+template <int MODE, int MB, int R, int UBP, int LW, int LOADS, bool PIN, typename Load>
+__device__ inline void chunk_mma(const char *A, const char *B, floatx16 (&acc)[MB][R], Load load) {
   using F = typename FragOf<MODE>::type;
   constexpr int P = Fmt<MODE>::kPlanes, WU = Fmt<MODE>::kWUnits;
   constexpr int AT = (WU / P) * 512, AP = 9 * AT, AM = P * AP;  // bytes per tap, plane, channel tile
+  constexpr int kPerTap = MB * R * (MODE == 2 || MODE == 5 ? 3 : 1), kAhead = kPerTap >= 8 ? 1 : (8 + kPerTap - 1) / kPerTap;
+  constexpr int kPerLoads = (LOADS + 4) / 5;  // loads per tap, all within the first five
+  F a[3][3][MB][P], b[3][R + 2][P];
+  auto read = [&](int s) {
+    const int dx = s / 3, dy = s % 3;
 #pragma unroll
-  for (int i = 0; i < R + 2; ++i)
+    for (int i = dy == 0 ? 0 : R - 1 + dy; i < R + dy; ++i)
 #pragma unroll
-    for (int p = 0; p < P; ++p)
-      f.b[i][p] = *reinterpret_cast<const F *>(B + p * 2 * UBP * 16 + (i * LW + dx) * 16);
-#pragma unroll
-  for (int dy = 0; dy < 3; ++dy)
+      for (int p = 0; p < P; ++p)
+        b[dx][i][p] = *reinterpret_cast<const F *>(B + p * 2 * UBP * 16 + (i * LW + dx) * 16);
 #pragma unroll
     for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
       for (int p = 0; p < P; ++p)
-        f.a[mb][dy][p] = *reinterpret_cast<const F *>(A + mb * AM + p * AP + (dy * 3 + dx) * AT);
-}
-template <int MODE, int MB, int R>
-__device__ inline void mma_frags(const Frags<MODE, MB, R> &f, floatx16 (&acc)[MB][R]) {
+        a[dx][dy][mb][p] = *reinterpret_cast<const F *>(A + mb * AM + p * AP + (dy * 3 + dx) * AT);
+  };
 #pragma unroll
-  for (int dy = 0; dy < 3; ++dy)
+  for (int s = 0; s < kAhead; ++s) read(s);
 #pragma unroll
-    for (int r = 0; r < R; ++r)
+  for (int s = 0; s < 9; ++s) {
+    if constexpr (PIN) __builtin_amdgcn_sched_barrier(0);
+    if (s + kAhead < 9) read(s + kAhead);
+    int l = (s - 1) * kPerLoads;
 #pragma unroll
-      for (int mb = 0; mb < MB; ++mb) mma<MODE>(f.a[mb][dy], f.b[r + dy], acc[mb][r]);
-}
-// The chunk, given its first step's fragments.  AHEAD (few matrix instructions
-// per step, R = 2): the next step's fragments are read before this one's
-// instructions are issued, which hide the reads; the compiler's own order,
-// which keeps fewer registers, waits for each read in turn (24 steps of a
-// small layer: 25.9 -> 24.3 us).
-template <int MODE, int MB, int R, int UBP, int LW, bool AHEAD>
-__device__ inline void chunk_mma(const char *A, const char *B, Frags<MODE, MB, R> &f0, floatx16 (&acc)[MB][R]) {
-  constexpr bool kAhead = AHEAD;
-  Frags<MODE, MB, R> f1, f2;
-  read_frags<MODE, MB, R, UBP, LW>(A, B, 1, f1);
-  if constexpr (kAhead) __builtin_amdgcn_sched_barrier(0);
-  mma_frags<MODE, MB, R>(f0, acc);
-  if constexpr (kAhead) __builtin_amdgcn_sched_barrier(0);
-  read_frags<MODE, MB, R, UBP, LW>(A, B, 2, f2);
-  if constexpr (kAhead) __builtin_amdgcn_sched_barrier(0);
-  mma_frags<MODE, MB, R>(f1, acc);
-  mma_frags<MODE, MB, R>(f2, acc);
+    for (int r = 0; r < R; ++r) {
+      if constexpr (PIN) __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int mb = 0; mb < MB; ++mb) mma<MODE>(a[s / 3][s % 3][mb], b[s / 3][r + s % 3], acc[mb][r]);
+      if (LOADS > 0 && s == 0 && r == 0) load(-1);
+      const int until = (s - 1) * kPerLoads + (r + 1) * kPerLoads / R;
+#pragma unroll
+      for (; l < until; ++l)
+        if (l >= 0 && l < LOADS) load(l);
+    }
+  }
+  if constexpr (PIN) __builtin_amdgcn_sched_barrier(0);
 }
 // this lane's offsets within a chunk's weights and a pixel's units
 template <int MODE>
@@ -400,7 +402,8 @@ __device__ inline void epilogue(const Args &a, int img, int co0, int gy0, int gx
 // t is multiplied from LDS while the input of step t + DI and the weights of
 // step t + DW are loaded straight into the slots that step t - 1 left, with one
 // barrier per step, so a tile's first chunks are on their way while the
-// previous tile is finished.  Pixels outside the image are written as zeros,
+// previous tile is finished.  Past the last step the loads are masked off, so
+// every step counts the same.  Pixels outside the image are written as zeros,
 // the loads leave them alone.
 template <int MODE, int MB, int R, int NW, int CW, int DI, int DW, bool HEAD>
 struct ConvLds {
@@ -447,29 +450,32 @@ __global__ __launch_bounds__(64 * NW, 2) void conv_kernel(Args a) {
   const int wg = a.wgroup;                                  // 32-channel tiles per packed group
   const char *wptr = nullptr;
   int wT = walk.first, wc = 0, wtile = 0, wslot = 0;
-  auto load_weights = [&](int t) {
-    if (resident && t >= 2) return;
-    if (wc == 0) {
-      const int ct = __builtin_amdgcn_readfirstlane(wT % a.ncz) * CT;
-      wptr = uniform(a.w + ((size_t)(wg == 2 ? ct >> 1 : ct) * nch * wg + (wg == 2 ? ct & 1 : 0)) * S::WCH + wv * 1024);
-      if (wv == 0) {  // the tile's biases and weight scales
-        const uint32_t db = sm0 + S::kBias + (wtile & 1) * (2 * CT * 32 * 4);
-        constexpr uint64_t lanes = CT == 2 ? ~0ull : 0xFFFFFFFFull;
-        load_lds4(a.bias + ct * 32, lane * 4, db, lanes);
-        if constexpr (MODE == 4 || MODE == 5) load_lds4(a.wscale + ct * 32, lane * 4, db + CT * 32 * 4, lanes);
-      }
+  uint64_t wlanes = ~0ull;  // 0 past the last step (and where they are resident): masked loads keep the counts
+  auto begin_weights = [&]() {
+    if (wc != 0) return;
+    if (wT >= walk.end || (resident && wtile * nch >= 2)) {
+      wlanes = 0;
+      return;
     }
-    const uint32_t dst = sm0 + S::kWeights + wslot * S::WB + wv * 1024;
-#pragma unroll
-    for (int k = 0; k < NKW; ++k) {
-      // units past the end: the load, or half of it, is masked
-      uint64_t lanes = ~0ull;
-      if ((k + 1) * NW * 64 > NWU) {
-        const int left = NWU - (wv + NW * k) * 64;
-        lanes = left >= 64 ? ~0ull : (left > 0 ? 0xFFFFFFFFull : 0ull);
-      }
-      load_lds16(wptr + k * NW * 1024, lane * 16, dst + k * NW * 1024, lanes);
+    const int ct = __builtin_amdgcn_readfirstlane(wT % a.ncz) * CT;
+    wptr = uniform(a.w + ((size_t)(wg == 2 ? ct >> 1 : ct) * nch * wg + (wg == 2 ? ct & 1 : 0)) * S::WCH + wv * 1024);
+    if (wv == 0) {  // the tile's biases and weight scales
+      const uint32_t db = sm0 + S::kBias + (wtile & 1) * (2 * CT * 32 * 4);
+      constexpr uint64_t lanes = CT == 2 ? ~0ull : 0xFFFFFFFFull;
+      load_lds4(a.bias + ct * 32, lane * 4, db, lanes);
+      if constexpr (MODE == 4 || MODE == 5) load_lds4(a.wscale + ct * 32, lane * 4, db + CT * 32 * 4, lanes);
     }
+  };
+  auto issue_weights = [&](int k) {
+    // units past the end: the load, or half of it, is masked
+    uint64_t lanes = wlanes;
+    if ((k + 1) * NW * 64 > NWU) {
+      const int left = NWU - (wv + NW * k) * 64;
+      lanes &= left >= 64 ? ~0ull : (left > 0 ? 0xFFFFFFFFull : 0ull);
+    }
+    load_lds16(wptr + k * NW * 1024, lane * 16, sm0 + S::kWeights + wslot * S::WB + wv * 1024 + k * NW * 1024, lanes);
+  };
+  auto end_weights = [&]() {
     wptr += wg * S::WCH;
     wslot = wslot == DW ? 0 : wslot + 1;
     if (++wc == nch) {
@@ -506,8 +512,12 @@ __global__ __launch_bounds__(64 * NW, 2) void conv_kernel(Args a) {
       voff[k] = (uint32_t)((((iy0 - 1 + urow[k]) >> sh) - y0) * Ws + ((ix0 - 1 + ucol[k]) >> sh)) * 16u;
   };
   int islot = 0;
-  auto load_input = [&]() {
-    if (ic == 0) {
+  auto begin_input = [&]() {
+    if (ic == 0 && iT >= walk.end) {
+#pragma unroll
+      for (int k = 0; k < NK; ++k) lanes[k] = 0;
+      border = false;
+    } else if (ic == 0) {
       const Tile t = tile_at(a, iT);
       iy0 = t.ty * TH;
       ix0 = t.tx * 32;
@@ -523,24 +533,25 @@ __global__ __launch_bounds__(64 * NW, 2) void conv_kernel(Args a) {
       border = __ballot(outside != 0) != 0;
     }
     if (ic == 0 || ic == nch0) set_source(ic != 0);
-    const uint32_t dst = islot * S::INB + wv * 1024;
-    islot = islot == DI ? 0 : islot + 1;
-#pragma unroll
-    for (int b = 0; b < NB; ++b) {
-      const char *sb = src + (b & 1) * blk + (MODE == 2 && b >= 2 ? pln : 0);
-#pragma unroll
-      for (int k = 0; k < NK; ++k) load_lds16(sb, voff[k], sm0 + dst + b * UBP * 16 + k * NW * 1024, lanes[k]);
-    }
+  };
+  auto issue_input = [&](int j) {
+    const int b = j / NK, k = j % NK;
+    load_lds16(src + (b & 1) * blk + (MODE == 2 && b >= 2 ? pln : 0), voff[k],
+               sm0 + islot * S::INB + wv * 1024 + b * UBP * 16 + k * NW * 1024, lanes[k]);
+  };
+  auto end_input = [&]() {
     if (border) {
 #pragma unroll
       for (int k = 0; k < NK; ++k)
         if ((outside >> k) & 1u) {
 #pragma unroll
           for (int b = 0; b < NB; ++b)
-            *reinterpret_cast<uint4 *>(sm + dst + b * UBP * 16 + k * NW * 1024 + lane * 16) = make_uint4(0u, 0u, 0u, 0u);
+            *reinterpret_cast<uint4 *>(sm + islot * S::INB + wv * 1024 + b * UBP * 16 + k * NW * 1024 + lane * 16) =
+                make_uint4(0u, 0u, 0u, 0u);
         }
     }
     src += (MODE == 4 ? 1 : 2) * blk;
+    islot = islot == DI ? 0 : islot + 1;
     if (++ic == nch) {
       ic = 0;
       ++iT;
@@ -559,34 +570,45 @@ __global__ __launch_bounds__(64 * NW, 2) void conv_kernel(Args a) {
   zero_acc();
   const char *A = sm + S::kWeights + wc0 * S::WCH + lane_a<MODE>(n, h);
   const char *B = sm + lane_b<MODE, UBP>(wr * R * LW + n, h);
+  constexpr int NI = NB * NK;  // a wave's input loads per step
+  auto load_weights = [&]() {
+    begin_weights();
+#pragma unroll
+    for (int k = 0; k < NKW; ++k) issue_weights(k);
+    end_weights();
+  };
+  auto load_input = [&]() {
+    begin_input();
+#pragma unroll
+    for (int j = 0; j < NI; ++j) issue_input(j);
+    end_input();
+  };
 #pragma unroll
   for (int d = 0; d < DI; ++d) {
-    if (d < DW && d < steps) load_weights(d);
-    if (d < steps) load_input();
+    if (d >= steps) continue;
+    if (d < DW) load_weights();
+    load_input();
   }
-  // Before step t: its loads are done, while newer ones may be in flight: with
-  // DI = 2 and DW = 1 the input of step t + 1, with DI = DW = D the weights and
+  // Before a step: its loads are done, while newer ones may be in flight: with
+  // DI = 2 and DW = 1 the input of the next step, with DI = DW = D the weights and
   // the input of D - 1 steps.  (Waiting before the epilogue keeps its stores
   // out of the count; the loads of a tile's biases only make it stricter.)
-  constexpr int kNewer = DI == DW ? (DI - 1) * (NKW + NB * NK) : NB * NK;
+  constexpr int kNewer = DI == DW ? (DI - 1) * (NKW + NI) : NI;
   static_assert(kNewer < 64, "vmcnt has six bits");
-  auto wait_for = [&](int t) {
-    if (kNewer > 0 && t - 1 + DI < steps) wait_loads<kNewer>();
-    else wait_loads<0>();
-  };
-  wait_for(0);
+  if (steps >= DI) wait_loads<kNewer>();
+  else wait_loads<0>();
   __syncthreads();
   int T = walk.first, tile = 0, c = 0, in_slot = 0, w_slot = 0;
   for (int t = 0; t < steps; ++t) {
-    // the first fragments are read before the loads are issued, whose scalar
-    // instructions hide them
     const char *At = A + w_slot * S::WB, *Bt = B + in_slot * S::INB;
-    Frags<MODE, MB, R> f;
-    read_frags<MODE, MB, R, UBP, LW>(At, Bt, 0, f);
-    if (t + DW < steps) load_weights(t + DW);
-    if (t + DI < steps) load_input();
-    chunk_mma<MODE, MB, R, UBP, LW, R == 2>(At, Bt, f, acc);
-    wait_for(t + 1);
+    chunk_mma<MODE, MB, R, UBP, LW, NKW + NI, true>(At, Bt, acc, [&](int i) {
+      if (i < 0) begin_weights(), begin_input();
+      else if (i < NKW) issue_weights(i);
+      else issue_input(i - NKW);
+    });
+    end_weights();
+    end_input();
+    wait_loads<kNewer>();
     __syncthreads();
     in_slot = in_slot == DI ? 0 : in_slot + 1;
     w_slot = w_slot == DW ? 0 : w_slot + 1;
@@ -667,9 +689,7 @@ __global__ __launch_bounds__(64 * NW, 2) void first_kernel(Args a) {
       for (int k = 0; k < 16; ++k) acc[mb][r][k] = 0.f;
   __syncthreads();
   const char *A = sm + INB + lane_a<MODE>(n, h), *B = sm + lane_b<MODE, UBP>(wv * R * LW + n, h);
-  Frags<MODE, MB, R> f;
-  read_frags<MODE, MB, R, UBP, LW>(A, B, 0, f);
-  chunk_mma<MODE, MB, R, UBP, LW, false>(A, B, f, acc);
+  chunk_mma<MODE, MB, R, UBP, LW, 0, false>(A, B, acc, [](int) {});
   epilogue<MODE, MB, R, false>(a, t.img, co0, ty0 + wv * R, tx0 + n, h, acc, s_bias, s_bias + MB * 32, nullptr);
 }
 
@@ -838,9 +858,7 @@ __global__ __launch_bounds__(64 * NW, 2) void enc0_kernel(Args a0, Args a1) {
     for (int c = 0; c < S::NCH; ++c) {
       const char *A = s_w1 + c * S::WCH + lane_a<MODE>(n, h);
       const char *B = sm + c * NB * UBP * 16 + lane_b<MODE, UBP>(wv * R * LW + n, h);
-      Frags<MODE, 1, R> f;
-      read_frags<MODE, 1, R, UBP, LW>(A, B, 0, f);
-      chunk_mma<MODE, 1, R, UBP, LW, false>(A, B, f, acc);
+      chunk_mma<MODE, 1, R, UBP, LW, 0, true>(A, B, acc, [](int) {});
     }
     if (more) stage();
     epilogue<MODE, 1, R, false>(a1, t.img, 0, ty0 + wv * R, tx0 + n, h, acc, s_bias + 64, s_bias + 96, nullptr);
