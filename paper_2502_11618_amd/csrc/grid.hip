@@ -222,17 +222,14 @@ __global__ __launch_bounds__(kThreads) void gather_kernel(const float *__restric
   rgbx[j] = (uint32_t)rgb[3 * p] | ((uint32_t)rgb[3 * p + 1] << 8) | ((uint32_t)rgb[3 * p + 2] << 16);
 }
 
-// one wave per cell: exact float min / max of its points
-__global__ __launch_bounds__(kThreads) void cell_aabb_kernel(const float *__restrict__ x, const float *__restrict__ y,
-                                                             const float *__restrict__ z,
-                                                             const uint32_t *__restrict__ cell_start,
-                                                             uint32_t n_cells, float *__restrict__ aabb) {
-  const uint32_t c = blockIdx.x * (kThreads / 64) + (threadIdx.x >> 6);
-  const int lane = threadIdx.x & 63;
-  if (c >= n_cells) return;
-  const uint32_t a = cell_start[c], b = cell_start[c + 1];
-  float lo[3] = {INFINITY, INFINITY, INFINITY}, hi[3] = {-INFINITY, -INFINITY, -INFINITY};
-  for (uint32_t j = a + lane; j < b; j += 64) {
+// Exact float min / max of each cell's points, of the points [a, b) by one wave.
+__device__ inline void wave_bounds(const float *__restrict__ x, const float *__restrict__ y,
+                                   const float *__restrict__ z, uint32_t a, uint32_t b, float (&lo)[3], float (&hi)[3]) {
+  for (int k = 0; k < 3; ++k) {
+    lo[k] = INFINITY;
+    hi[k] = -INFINITY;
+  }
+  for (uint32_t j = a + (threadIdx.x & 63); j < b; j += 64) {
     const float v[3] = {x[j], y[j], z[j]};
     for (int k = 0; k < 3; ++k) {
       lo[k] = fminf(lo[k], v[k]);
@@ -244,7 +241,59 @@ __global__ __launch_bounds__(kThreads) void cell_aabb_kernel(const float *__rest
       lo[k] = fminf(lo[k], __shfl_xor(lo[k], off, 64));
       hi[k] = fmaxf(hi[k], __shfl_xor(hi[k], off, 64));
     }
+}
+// min / max of a float in memory: the order of the bits is the order of the
+// values for non-negative floats and the reverse for negative ones
+__device__ inline void atomic_min_float(float *p, float v) {
+  const uint32_t u = __float_as_uint(v);
+  if (u >> 31) atomicMax(reinterpret_cast<unsigned int *>(p), u);
+  else atomicMin(reinterpret_cast<int *>(p), (int)u);
+}
+__device__ inline void atomic_max_float(float *p, float v) {
+  const uint32_t u = __float_as_uint(v);
+  if (u >> 31) atomicMin(reinterpret_cast<unsigned int *>(p), u);
+  else atomicMax(reinterpret_cast<int *>(p), (int)u);
+}
+// One wave per cell of up to kCellWave points.  Larger cells are emptied here and
+// taken by cell_aabb_large_kernel, in slices of kCellWave consecutive points
+// per wave: one wave for a cell of 40 K points kept all others waiting (5 M points in
+// 1200 cells: 194 us).
+constexpr uint32_t kCellWave = 1024;
+__global__ __launch_bounds__(kThreads) void cell_aabb_kernel(const float *__restrict__ x, const float *__restrict__ y,
+                                                             const float *__restrict__ z,
+                                                             const uint32_t *__restrict__ cell_start,
+                                                             uint32_t n_cells, float *__restrict__ aabb) {
+  const uint32_t c = blockIdx.x * (kThreads / 64) + (threadIdx.x >> 6);
+  const int lane = threadIdx.x & 63;
+  if (c >= n_cells) return;
+  const uint32_t a = cell_start[c], b = cell_start[c + 1];
+  float lo[3], hi[3];
+  wave_bounds(x, y, z, a, b - a > kCellWave ? a : b, lo, hi);
   if (lane < 6) aabb[6ull * c + lane] = lane < 3 ? lo[lane] : hi[lane - 3];
+}
+// A slice meets at most two cells of more than kCellWave points: the cells of
+// its first and of its last point.
+__global__ __launch_bounds__(kThreads) void cell_aabb_large_kernel(const float *__restrict__ x,
+                                                                   const float *__restrict__ y,
+                                                                   const float *__restrict__ z,
+                                                                   const uint32_t *__restrict__ cell_start,
+                                                                   const uint32_t *__restrict__ cell, uint32_t n,
+                                                                   float *__restrict__ aabb) {
+  const uint64_t first = (uint64_t)(blockIdx.x * (kThreads / 64) + (threadIdx.x >> 6)) * kCellWave;
+  if (first >= n) return;
+  const uint32_t a = (uint32_t)first, b = n - a > kCellWave ? a + kCellWave : n;
+  const uint32_t c0 = cell[a], c1 = cell[b - 1];
+  for (int i = 0; i < (c1 != c0 ? 2 : 1); ++i) {
+    const uint32_t c = i ? c1 : c0, ca = cell_start[c], cb = cell_start[c + 1];
+    if (cb - ca <= kCellWave) continue;
+    float lo[3], hi[3];
+    wave_bounds(x, y, z, max(a, ca), min(b, cb), lo, hi);
+    if ((threadIdx.x & 63) == 0)
+      for (int k = 0; k < 3; ++k) {
+        atomic_min_float(&aabb[6ull * c + k], lo[k]);
+        atomic_max_float(&aabb[6ull * c + 3 + k], hi[k]);
+      }
+  }
 }
 
 __global__ __launch_bounds__(kThreads) void chunk_count_kernel(const uint32_t *__restrict__ cell_start,
@@ -368,8 +417,12 @@ hipError_t launch_gather_points(const float *xyz, const uint8_t *rgb, const uint
 }
 
 hipError_t launch_cell_aabb(const float *x, const float *y, const float *z, const uint32_t *cell_start,
-                            uint32_t n_cells, float *aabb, hipStream_t s) {
+                            uint32_t n_cells, const uint32_t *sorted_cell, uint32_t n, float *aabb, hipStream_t s) {
   cell_aabb_kernel<<<div_up(n_cells, kThreads / 64), kThreads, 0, s>>>(x, y, z, cell_start, n_cells, aabb);
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess || n <= kCellWave) return e;
+  cell_aabb_large_kernel<<<div_up(div_up(n, kCellWave), kThreads / 64), kThreads, 0, s>>>(x, y, z, cell_start, sorted_cell,
+                                                                                          n, aabb);
   return hipGetLastError();
 }
 

@@ -116,7 +116,7 @@ hipError_t exclusive_scan_u32(const uint32_t *in, uint32_t *out, uint32_t n, voi
 hipError_t launch_gather_points(const float *xyz, const uint8_t *rgb, const uint32_t *perm, uint32_t n, float *x,
                                 float *y, float *z, uint32_t *rgbx, hipStream_t s);
 hipError_t launch_cell_aabb(const float *x, const float *y, const float *z, const uint32_t *cell_start,
-                            uint32_t n_cells, float *aabb, hipStream_t s);
+                            uint32_t n_cells, const uint32_t *sorted_cell, uint32_t n, float *aabb, hipStream_t s);
 // sums over cells of ceil(count / kSplatChunk) and ceil(count / kBinDense) into total[0..1] (zeroed by the caller)
 hipError_t launch_chunk_count(const uint32_t *cell_start, uint32_t n_cells, uint32_t *total, hipStream_t s);
 
