@@ -268,7 +268,7 @@ def sampled_error(fd, fr, blob, outs, H, W, progress=None, tol=None):
 
 
 TRAFFIC_JSON = os.path.join(ROOT, "profiles", "traffic_unet_fp32_multiroom_1080p.json")
-TRAFFIC_SOURCES = [os.path.join(ROOT, "paper_2502_11618_amd", "csrc", f) for f in ("unet.hip", "api.cpp")]
+TRAFFIC_SOURCES = [os.path.join(ROOT, "paper_2502_11618_amd", "csrc", f) for f in ("unet.hip", "conv_stage.h", "api.cpp")]
 
 
 def _sources_sha():
@@ -283,9 +283,9 @@ def summarize_counters(args):
     """Per-kernel HBM bytes from rocprofv3 --pmc csv files of a float32 frames
     run, each counter scaled by what it reads for a plain 1 GiB device copy.
     Convolutions are named by their place in the frame (a frame's first
-    convolution is the one that stages the RGBDA image, or follows the input
-    pack; the n-th after it is the n-th layer of conv_shapes), so the figures
-    stay tied to layers whatever template a layer dispatches to.
+    convolution is the one that reads the RGBDA image; the n-th after it is the
+    n-th layer of conv_shapes), so the figures stay tied to layers whatever
+    template a layer dispatches to.
     Writes every layer's figures next to the hash of the sources that decide
     them."""
     import collections
@@ -314,11 +314,9 @@ def summarize_counters(args):
         conv_i = None
         for r in rows(path):
             name = short(r["Kernel_Name"])
-            if name.startswith("pack_kernel"):
-                conv_i = 0
-            if name.startswith("conv3x3") and name.endswith(", true>"):
-                conv_i = 0  # the first convolution stages the RGBDA image itself
-            if name.startswith(("conv3x3", "wino3x3")) and conv_i is not None and conv_i < len(layer_names):
+            if name.startswith("first3x3"):
+                conv_i = 0  # the first convolution, which reads the RGBDA image itself
+            if name.startswith(("first3x3", "wino_kernel")) and conv_i is not None and conv_i < len(layer_names):
                 kname[layer_names[conv_i]] = name
                 name = layer_names[conv_i]
                 conv_i += 1
