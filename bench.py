@@ -462,10 +462,10 @@ def serve_sweep(L, scene, cloud, blob, seconds, counts=(8, 16, 32, 64)):
 
 def multiview_render(L, ctx, cloud, cams, W, H, batch, nbatch):
     """Projection of one batch of views, view by view (the default tiled splat,
-    each view reading its visible cells' points) against lnr_render_views (one
-    pass per 8 views, each point of a cell visible in any of them read once):
-    time per batch by HIP events on the stream both run on, points read, and
-    whether every image is the same bit for bit."""
+    each view reading its visible cells' points) against lnr_render_views (up
+    to 8 views in the same launches): time per batch by HIP events on the
+    stream both run on, points of the cells visible in each view and in any
+    view of a pass, and whether every image is the same bit for bit."""
     import numpy as np
     import torch
 

@@ -183,9 +183,8 @@ lnr_status lnr_render(lnr_context *ctx, const lnr_cloud *c, const lnr_camera *ca
 lnr_status lnr_render_soft(lnr_context *ctx, const lnr_cloud *c, const lnr_camera *cam, lnr_image *out,
                            float soft_eps, uint32_t flags, void *hip_stream);
 /* Render several views of one cloud (a batch of cameras, e.g. the views of
- * one serving step), reading each point from device memory once per pass
- * instead of once per view (Method, "Point Cloud Projection", applied to
- * every camera of the batch).  outs[v] receives exactly what lnr_render of
+ * one serving step), up to 8 of them in the same launches (Method, "Point
+ * Cloud Projection", applied to every camera of the batch).  outs[v] receives exactly what lnr_render of
  * cams[v] alone writes, bit for bit, for every v.
  *   cams, outs : HOST arrays of n_views cameras and images (the images'
  *                buffers are device buffers, as for lnr_render); no two
@@ -205,7 +204,7 @@ lnr_status lnr_render_soft(lnr_context *ctx, const lnr_cloud *c, const lnr_camer
  * each point once.  Uses 16 bytes of context scratch per work item and depth
  * bucket besides.
  * lnr_render_stats then reports the last pass: cells visible in at least one
- * of its views, and the points of those cells, each read once.  Errors as
+ * of its views, and the points of those cells, each counted once.  Errors as
  * lnr_render, checked for every view before anything is enqueued. */
 lnr_status lnr_render_views(lnr_context *ctx, const lnr_cloud *c, const lnr_camera *cams, lnr_image *outs,
                             int32_t n_views, uint32_t flags, void *hip_stream);
