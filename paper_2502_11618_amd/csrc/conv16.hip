@@ -414,7 +414,11 @@ struct ConvLds {
   static constexpr int WCH = Fmt<MODE>::kWUnits * 288 * 16;     // its weights per 32 channels
   static constexpr int WB = CT * WCH;
   static constexpr int kWeights = (DI + 1) * INB, kBias = kWeights + (DW + 1) * WB;
-  static constexpr int kHead = kBias + 2 * 2 * CT * 32 * 4;     // two tiles' biases and weight scales
+  // Two tiles' biases and weight scales.  A tile's are loaded DW steps before its
+  // first step and read after its last one, while faster waves are in the next
+  // step already: with DW = 1, two slots hold for tiles of two steps or more, for
+  // runs of two tiles, or where every tile has the same ones (launch() sees to it).
+  static constexpr int kHead = kBias + 2 * 2 * CT * 32 * 4;
   static constexpr int kBytes = kHead + (HEAD ? (3 * 32 * CT + 4) * 4 : 0);
 };
 template <int MODE, int MB, int R, int NW, int CW, int DI, int DW, bool HEAD>
@@ -912,6 +916,8 @@ hipError_t launch(const ConvCall &c, hipStream_t s) {
     set_tiles(a, S::TH, 32 * S::CT, c.layer->cout_pad, batch, 1);
     run = a.ntiles / (2 * kCUs * (8 / NW));
     run = run < 1 ? 1 : (run > 8 ? 8 : run);
+    // tiles of one step and different channels: runs of two (the bias slots)
+    if (a.C0 + a.C1 == 16 && a.ncz > 1) run = run < 2 ? run : 2;
   }
   const int grid = set_tiles(a, S::TH, 32 * S::CT, c.layer->cout_pad, batch, run);
   if (c.head_out || c.head_outs) {

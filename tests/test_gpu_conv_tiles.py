@@ -61,3 +61,26 @@ def test_unfused_head(lnr, ctx, prec):
     net = lnr.lnr_unet_load(ctx, blob, prec)
     err = M.max_abs(_run(lnr, ctx, net, depth, rgba), U.forward(U.parse_blob(blob), depth, rgba))
     check_unet_error(prec, err, "widths (80, 96) 26x70")
+
+
+@pytest.mark.parametrize("prec", UNET_PRECISIONS)
+@pytest.mark.parametrize("widths", [(16, 80), (16, 160)])
+def test_runs_of_one_chunk_tiles(lnr, ctx, prec, widths):
+    """Level 1 reads 16 channels (one step per tile) and writes three or five
+    32-channel tiles, in a picture large enough for workgroups that walk several
+    tiles of different channels: their biases must not mix.  Against windows
+    whose level 1 takes one tile per workgroup, bit for bit."""
+    print("runs", prec, widths, flush=True)
+    net = lnr.lnr_unet_load(ctx, synth.make_unet_blob(widths, seed=22, bias="uniform"), prec)
+    H, W, side, m = 1056, 2112, 544, 12
+    depth, rgba = _rgbda(4, H, W)
+    big = _run(lnr, ctx, net, depth, rgba)
+    for y in range(0, H - 2 * m, side - 2 * m):
+        for x in range(0, W - 2 * m, side - 2 * m):
+            y1, x1 = min(y + side, H), min(x + side, W)
+            got = _run(lnr, ctx, net, depth[y:y1, x:x1].copy(), rgba[y:y1, x:x1].copy())
+            # away from the cuts (the picture's own borders are the window's)
+            a, b = (m if y else 0), (y1 - y - (m if y1 < H else 0))
+            c, d = (m if x else 0), (x1 - x - (m if x1 < W else 0))
+            assert np.array_equal(got[:, a:b, c:d].view(np.uint32),
+                                  big[:, y + a:y + b, x + c:x + d].view(np.uint32)), f"window at {y}, {x}"
