@@ -4,7 +4,6 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
-#include <array>
 #include <deque>
 #include <map>
 #include <tuple>
@@ -33,8 +32,8 @@ thread_local std::string g_create_error;
 // device scratch reused by consecutive calls on one stream
 struct Scratch {
   Buf flags, chunks, counters, pyramid, act, soft_acc;
-  Buf recs, segs, sorted, tile_nseg, tile_off, tile_units, units;  // tiled splat
-  Buf views;                                                         // multi-view work items
+  Buf tiled;  // tiled splat (see tiled_bufs)
+  Buf views;  // multi-view work items
 };
 
 }  // namespace
@@ -169,8 +168,9 @@ void dfree(lnr_context *ctx, void *p, size_t bytes) {
   ctx->allocated -= std::min<uint64_t>(ctx->allocated, bytes);
 }
 
-// grow-only scratch; an old buffer is released only after the device is idle
-lnr_status ensure(lnr_context *ctx, Buf &b, size_t bytes) {
+// grow-only scratch; an old buffer is released only after the device is idle.
+// pad: bytes beyond those accounted for (the alignment of parts)
+lnr_status ensure(lnr_context *ctx, Buf &b, size_t bytes, size_t pad = 0) {
   if (b.cap >= bytes && b.p) return LNR_OK;
   if (b.p) {
     LNR_HIP(ctx, hipDeviceSynchronize());
@@ -178,7 +178,7 @@ lnr_status ensure(lnr_context *ctx, Buf &b, size_t bytes) {
     b.p = nullptr;
     b.cap = 0;
   }
-  lnr_status st = dalloc(ctx, &b.p, bytes);
+  lnr_status st = dalloc(ctx, &b.p, bytes, bytes + pad);
   if (st == LNR_OK) b.cap = bytes;
   return st;
 }
@@ -557,8 +557,7 @@ void context_free(lnr_context *ctx) {
   (void)hipSetDevice(ctx->device);
   (void)hipDeviceSynchronize();
   for (Buf *b : {&ctx->sc.flags, &ctx->sc.chunks, &ctx->sc.counters, &ctx->sc.pyramid, &ctx->sc.act, &ctx->sc.soft_acc,
-                 &ctx->sc.recs, &ctx->sc.segs, &ctx->sc.sorted, &ctx->sc.tile_nseg, &ctx->sc.tile_off,
-                 &ctx->sc.tile_units, &ctx->sc.units, &ctx->sc.views})
+                 &ctx->sc.tiled, &ctx->sc.views})
     dfree(ctx, b->p, b->cap);
   for (auto &r : ctx->recs) {
     (void)hipEventDestroy(r.a);
@@ -739,37 +738,42 @@ void lnr_cloud_destroy(lnr_cloud *c) {
 // ---------------------------------------------------------------------------
 // render
 // ---------------------------------------------------------------------------
-// Scratch of the tiled splat for n_views views at once of a cloud of n_points
-// points, sized for grid g (the largest view's, see TiledSplatGrid): bytes of
-// each buffer, in the order below.
-static std::array<Buf *, 7> tiled_scratch(Scratch &scr) {
-  return {&scr.recs, &scr.segs, &scr.sorted, &scr.tile_nseg, &scr.tile_off, &scr.tile_units, &scr.units};
+// Scratch of the tiled splat for n_views views at once of a cloud of n points,
+// sized for grid g (the largest view's, see TiledSplatGrid): one allocation,
+// kTiledPad bytes beyond the arrays' own for their alignment.  (With one per
+// array a new context's first frame of 20M points at 1080p took 1080 us, 1020
+// with one; soft z-buffer, 5M points: 290 and 245.)
+constexpr size_t kTiledPad = 8 * 256;
+static size_t tiled_bytes(const TiledSplatGrid &g, uint32_t n, int n_views) {
+  const size_t v = (size_t)n_views;
+  return v * (8ull * n + 20 * g.seg_cap + 8 * g.unit_cap + 4ull * tile_count_words(g.n_tiles) + 8ull * g.n_tiles + 4);
 }
-static std::array<size_t, 7> tiled_bytes(const TiledSplatGrid &g, uint32_t n_points, int n_views) {
-  const size_t n = std::max<uint32_t>(1, n_points), v = (size_t)n_views;
-  return {8 * n * v, 16 * g.seg_cap * v, 4 * g.seg_cap * v, 4ull * kTileCountWords * g.n_tiles * v, (4ull * g.n_tiles + 4) * v, 4ull * g.n_tiles * v,
-          8ull * g.unit_cap * v};
+// What lnr_render allocates for one view: with room for a segment per record, so
+// that no cloud of fewer points at no more tiles needs more, whatever its cells
+// (a caller who captures its launches warms the context with its largest).
+static size_t tiled_reserve(TiledSplatGrid g, uint32_t n) {
+  g.seg_cap = std::max<uint32_t>(1, n);
+  g.unit_cap = tiled_unit_cap(g.n_tiles, g.seg_cap, n);
+  return tiled_bytes(g, n, 1);
 }
-static lnr_status ensure_tiled(lnr_context *ctx, Scratch &scr, const TiledSplatGrid &g, uint32_t n_points,
-                               int n_views = 1) {
-  const auto bufs = tiled_scratch(scr);
-  const auto need = tiled_bytes(g, n_points, n_views);
-  for (size_t i = 0; i < bufs.size(); ++i) {
-    const lnr_status st = ensure(ctx, *bufs[i], need[i]);
-    if (st != LNR_OK) return st;
-  }
-  return LNR_OK;
-}
-// the part of view v
-static TiledSplatBufs tiled_bufs(Scratch &scr, const TiledSplatGrid &g, uint32_t n_points, size_t v = 0) {
-  const size_t n = std::max<uint32_t>(1, n_points);
-  return TiledSplatBufs{static_cast<uint64_t *>(scr.recs.p) + v * n,
-                        static_cast<uint4 *>(scr.segs.p) + v * g.seg_cap,
-                        static_cast<uint32_t *>(scr.sorted.p) + v * g.seg_cap,
-                        static_cast<uint32_t *>(scr.tile_nseg.p) + v * kTileCountWords * g.n_tiles,
-                        static_cast<uint32_t *>(scr.tile_off.p) + v * (g.n_tiles + 1),
-                        static_cast<uint32_t *>(scr.tile_units.p) + v * g.n_tiles,
-                        static_cast<uint2 *>(scr.units.p) + v * g.unit_cap};
+// the part of view v of n_views
+static TiledSplatBufs tiled_bufs(const Buf &b, const TiledSplatGrid &g, uint32_t n, int n_views = 1, int view = 0) {
+  const size_t nv = (size_t)n_views, v = (size_t)view;
+  char *at = static_cast<char *>(b.p);
+  auto take = [&](size_t bytes) {  // every view's array, bytes each
+    char *p = at;
+    at += (nv * bytes + 255) / 256 * 256;
+    return p + v * bytes;
+  };
+  TiledSplatBufs t;
+  t.recs = reinterpret_cast<uint64_t *>(take(8ull * n));
+  t.segs = reinterpret_cast<uint4 *>(take(16 * g.seg_cap));
+  t.sorted = reinterpret_cast<uint32_t *>(take(4 * g.seg_cap));
+  t.units = reinterpret_cast<uint2 *>(take(8 * g.unit_cap));
+  t.tile_nseg = reinterpret_cast<uint32_t *>(take(4ull * tile_count_words(g.n_tiles)));
+  t.tile_off = reinterpret_cast<uint32_t *>(take(4ull * g.n_tiles + 4));
+  t.tile_units = reinterpret_cast<uint32_t *>(take(4ull * g.n_tiles));
+  return t;
 }
 
 // How many of n views the tiled splat takes at once: all of them while their
@@ -778,26 +782,18 @@ static TiledSplatBufs tiled_bufs(Scratch &scr, const TiledSplatGrid &g, uint32_t
 // the device memory still free; shared out evenly over the passes.  0: not even
 // one view's scratch fits the budget.
 constexpr size_t kViewsScratch = 6ull << 30;
-static int tiled_views_at_once(lnr_context *ctx, Scratch &scr, const TiledSplatGrid &g, uint32_t n_points, int n) {
-  const auto bufs = tiled_scratch(scr);
-  size_t held = 0;
-  for (Buf *b : bufs) held += b->p ? b->cap : 0;
+static int tiled_views_at_once(lnr_context *ctx, const Buf &held, const TiledSplatGrid &g, uint32_t n_points, int n) {
   size_t free_bytes = 0, total_bytes = 0;
   bool asked = false;
   for (int v = std::min(n, kViewsPerPass); v >= 1; --v) {
-    const auto need = tiled_bytes(g, n_points, v);
-    size_t sum = 0, more = 0;
-    for (size_t i = 0; i < bufs.size(); ++i) {
-      sum += need[i];
-      if (!bufs[i]->p || bufs[i]->cap < need[i]) more += need[i];
-    }
-    if (more) {
-      if (ctx->budget && ctx->allocated - std::min<uint64_t>(ctx->allocated, held) + sum > ctx->budget) continue;
+    const size_t need = tiled_bytes(g, n_points, v);
+    if (need > held.cap) {
+      if (ctx->budget && ctx->allocated - held.cap + need > ctx->budget) continue;
       if (v > 1) {
-        if (sum > kViewsScratch) continue;
+        if (need > kViewsScratch) continue;
         if (!asked && hipMemGetInfo(&free_bytes, &total_bytes) != hipSuccess) free_bytes = 0;
         asked = true;
-        if (more > free_bytes / 4) continue;
+        if (need > free_bytes / 4) continue;
       }
     }
     const int passes = (n + v - 1) / v;
@@ -860,14 +856,17 @@ static lnr_status render_impl(lnr_context *ctx, Scratch &scr, const lnr_cloud *c
   const bool atomic = count || (flags & LNR_RENDER_ATOMIC_SPLAT) != 0;
   const TiledSplatGrid tg = tiled_splat_grid((uint32_t)cam->width, (uint32_t)cam->height, c->d);
   // every allocation comes before the first launch: a failure leaves the image untouched
-  if (!atomic && (st = ensure_tiled(ctx, scr, tg, c->d.n)) != LNR_OK) return st;
+  if (!atomic && scr.tiled.cap < tiled_bytes(tg, c->d.n, 1) &&
+      (st = ensure(ctx, scr.tiled, tiled_reserve(tg, c->d.n), kTiledPad)) != LNR_OK)
+    return st;
   if (soft && (st = ensure(ctx, scr.soft_acc, 16ull * npix)) != LNR_OK) return st;
   if (dev && atomic) return fail(ctx, LNR_E_INVALID_ARG, "a camera in device memory needs the tiled splat");
+  const TiledSplatBufs tb = atomic ? TiledSplatBufs{} : tiled_bufs(scr.tiled, tg, c->d.n);
   // (the tiled splat writes every key itself: its segment sort empties the
   // keys of the tiles that merge through atomics, so only the counters here)
   LNR_LAUNCH(ctx, "clear", s,
              launch_clear(out->key, atomic ? npix : 0u, counters, kCounterWords,
-                          static_cast<uint32_t *>(scr.tile_nseg.p), atomic ? 0u : kTileCountWords * tg.n_tiles, s));
+                          tb.tile_nseg, atomic ? 0u : tile_count_words(tg.n_tiles), s));
   LNR_LAUNCH(ctx, "cull", s,
              launch_cull(c->d, prm, dev ? &dev->cull : nullptr, static_cast<uint8_t *>(scr.flags.p),
                          static_cast<uint2 *>(scr.chunks.p), atomic ? kSplatChunk : c->d.item_points, counters,
@@ -879,7 +878,7 @@ static lnr_status render_impl(lnr_context *ctx, Scratch &scr, const lnr_cloud *c
     if (!soft) LNR_LAUNCH(ctx, "resolve", s, launch_resolve(out->key, c->d.rgbx, out->depth, rgba32, npix, s));
   } else {
     static const char *const names[6] = {"bin", "tilescan", "segsort", "tile", "soft", "tileres"};
-    const TiledSplatView view{sc, dev ? &dev->splat : nullptr, (uint32_t)cam->height, tiled_bufs(scr, tg, c->d.n),
+    const TiledSplatView view{sc, dev ? &dev->splat : nullptr, (uint32_t)cam->height, tb,
                               counters, out->key, out->depth, rgba32, soft ? scr.soft_acc.p : nullptr};
     const bool merged = tiled_scan_merged(&view, 1);  // the scan runs inside the segment sort
     for (int stage = 0; stage < 6; ++stage)
@@ -922,12 +921,12 @@ static lnr_status render_tiled_views(lnr_context *ctx, Scratch &scr, const lnr_c
   for (int v = 0; v < n; ++v) {
     if (!dev) vc.v[v] = make_cull_params(&cams[v], no_cull);
     views[v] = TiledSplatView{make_splat_cam(&cams[v]), dev ? &dev[v].splat : nullptr, (uint32_t)cams[v].height,
-                              tiled_bufs(scr, g, c->d.n, (size_t)v), counters + (size_t)v * kViewCounterWords,
+                              tiled_bufs(scr.tiled, g, c->d.n, n, v), counters + (size_t)v * kViewCounterWords,
                               outs[v].key, outs[v].depth, reinterpret_cast<uint32_t *>(outs[v].rgba), nullptr};
   }
   LNR_LAUNCH(ctx, "clear", s,
              launch_clear(nullptr, 0u, counters, (uint32_t)(n * kViewCounterWords),
-                          static_cast<uint32_t *>(scr.tile_nseg.p), kTileCountWords * g.n_tiles * (uint32_t)n, s));
+                          views[0].b.tile_nseg, tile_count_words(g.n_tiles) * (uint32_t)n, s));
   LNR_LAUNCH(ctx, "cull_views", s,
              launch_cull_views(c->d, vc, dev, static_cast<uint8_t *>(scr.flags.p), items, c->d.item_points, counters,
                                s));
@@ -990,9 +989,9 @@ lnr_status lnr_render_views(lnr_context *ctx, const lnr_cloud *c, const lnr_came
   uint4 *items = static_cast<uint4 *>(scr.views.p);
   const bool no_cull = (flags & LNR_RENDER_NO_CULL) != 0;
   const TiledSplatGrid grid = largest_grid(c, cams, n_views);
-  const int at_once = tiled_views_at_once(ctx, scr, grid, c->d.n, std::min(n_views, kViewsPerPass));
+  const int at_once = tiled_views_at_once(ctx, scr.tiled, grid, c->d.n, std::min(n_views, kViewsPerPass));
   if (at_once > 0) {
-    if ((st = ensure_tiled(ctx, scr, grid, c->d.n, at_once)) != LNR_OK) return st;
+    if ((st = ensure(ctx, scr.tiled, tiled_bytes(grid, c->d.n, at_once), kTiledPad)) != LNR_OK) return st;
     for (int g = 0; g < n_views; g += at_once)
       if ((st = render_tiled_views(ctx, scr, c, cams + g, outs + g, std::min(at_once, n_views - g), grid, no_cull, s,
                                    nullptr)) != LNR_OK)
@@ -1544,8 +1543,7 @@ void server_release(lnr_server *srv) {
     if (l.stream) (void)hipStreamSynchronize(l.stream);
     for (auto &g : l.graphs) (void)hipGraphExecDestroy(g.second);
     for (auto g : l.graph_defs) (void)hipGraphDestroy(g);
-    for (Buf *b : {&l.sc.flags, &l.sc.chunks, &l.sc.counters, &l.sc.pyramid, &l.sc.act, &l.sc.soft_acc, &l.sc.recs,
-                   &l.sc.segs, &l.sc.sorted, &l.sc.tile_nseg, &l.sc.tile_off, &l.sc.tile_units, &l.sc.units,
+    for (Buf *b : {&l.sc.flags, &l.sc.chunks, &l.sc.counters, &l.sc.pyramid, &l.sc.act, &l.sc.soft_acc, &l.sc.tiled,
                    &l.sc.views})
       dfree(ctx, b->p, b->cap);
     if (l.head_outs_dev) dfree(ctx, l.head_outs_dev, 8ull * 16);
@@ -1647,7 +1645,8 @@ lnr_status lnr_server_create(lnr_context *ctx, const lnr_cloud *c, const lnr_une
         (st = ensure(ctx, l.sc.chunks, 8ull * kDepthBuckets * std::max<uint32_t>(1, c->d.max_chunks))) != LNR_OK ||
         (st = ensure(ctx, l.sc.counters, 4 * kViewCounterWords * kViewsPerPass)) != LNR_OK ||
         (st = ensure(ctx, l.sc.pyramid, pyr)) != LNR_OK || (st = ensure(ctx, l.sc.act, act)) != LNR_OK ||
-        (st = ensure_tiled(ctx, l.sc, tiled_splat_grid((uint32_t)mW, (uint32_t)mH, c->d), c->d.n)) != LNR_OK ||
+        (st = ensure(ctx, l.sc.tiled, tiled_bytes(tiled_splat_grid((uint32_t)mW, (uint32_t)mH, c->d), c->d.n, 1),
+                     kTiledPad)) != LNR_OK ||
         (cfg->soft && (st = ensure(ctx, l.sc.soft_acc, 16 * npix)) != LNR_OK) ||
         (st = dalloc(ctx, (void **)&l.head_outs_dev, 8ull * 16)) != LNR_OK ||
         (st = dalloc(ctx, (void **)&l.cams_dev, sizeof(DevCam) * 16)) != LNR_OK ||
@@ -1666,17 +1665,16 @@ lnr_status lnr_server_create(lnr_context *ctx, const lnr_cloud *c, const lnr_une
     const size_t most = 28ull * c->d.n + npix * (u->prec == Prec::F32 ? 32 : u->prec == Prec::BF16X3 ? 64 : 32) *
                                              (size_t)cfg->max_batch;
     for (auto &l : srv->lanes) {
-      int v = tiled_views_at_once(ctx, l.sc, g, c->d.n, std::min(cfg->max_batch, kViewsPerPass));
+      int v = tiled_views_at_once(ctx, l.sc.tiled, g, c->d.n, std::min(cfg->max_batch, kViewsPerPass));
       auto needs = [&](int n) {
-        size_t sum = 16ull * kDepthBuckets * std::max<uint32_t>(1, c->d.max_chunks) + pyr * (size_t)(n - 1);
-        for (size_t b : tiled_bytes(g, c->d.n, n)) sum += b;
-        return sum;
+        return 16ull * kDepthBuckets * std::max<uint32_t>(1, c->d.max_chunks) + pyr * (size_t)(n - 1) +
+               tiled_bytes(g, c->d.n, n);
       };
       while (v > 1 && ctx->budget && needs(v) > most) --v;
       if (v <= 1) continue;
       if ((st = ensure(ctx, l.sc.views, 16ull * kDepthBuckets * std::max<uint32_t>(1, c->d.max_chunks))) != LNR_OK ||
           (st = ensure(ctx, l.sc.pyramid, pyr * (size_t)v)) != LNR_OK ||
-          (st = ensure_tiled(ctx, l.sc, g, c->d.n, v)) != LNR_OK) {
+          (st = ensure(ctx, l.sc.tiled, tiled_bytes(g, c->d.n, v), kTiledPad)) != LNR_OK) {
         server_release(srv.get());
         return st;
       }

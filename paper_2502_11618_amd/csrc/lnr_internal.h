@@ -132,15 +132,17 @@ hipError_t launch_clear(uint64_t *key, uint32_t npix, uint32_t *counters, uint32
 // render for a cloud of n points: recs u64[n] (a work item's records at its
 // points' positions), segs uint4[seg_cap] and sorted u32[seg_cap] (at most one
 // segment per record, and one per work item and tile), tile_nseg
-// u32[kTileCountWords n_tiles] (per tile a u64, records << 32 | segments, then
-// the merged sort's fill counters; zeroed by launch_clear), tile_units
+// u32[tile_count_words(n_tiles)] (per tile a u64, records << 32 | segments,
+// then the merged sort's fill counters; zeroed by launch_clear), tile_units
 // u32[n_tiles], tile_off u32[n_tiles + 1], units uint2[unit_cap].
-constexpr uint32_t kTileCountWords = 4;  // (even: the next view's u64 counts stay aligned)
+inline uint32_t tile_count_words(uint32_t n_tiles) { return (3 * n_tiles + 1) / 2 * 2; }  // (u64 counts of the next view stay aligned)
 struct TiledSplatGrid {
   uint32_t tiles_x = 0, tiles_y = 0, n_tiles = 0;
   uint64_t seg_cap = 0, unit_cap = 0;
 };
 TiledSplatGrid tiled_splat_grid(uint32_t W, uint32_t H, const CloudDev &c);
+// units of n_tiles tiles, at most seg_cap segments and n records
+uint64_t tiled_unit_cap(uint32_t n_tiles, uint64_t seg_cap, uint32_t n);
 struct TiledSplatBufs {
   uint64_t *recs;
   uint4 *segs;

@@ -1353,9 +1353,14 @@ TiledSplatGrid tiled_splat_grid(uint32_t W, uint32_t H, const CloudDev &c) {
   g.tiles_y = (H + kTileSide - 1) >> kTileShift;
   g.n_tiles = g.tiles_x * g.tiles_y;
   g.seg_cap = std::max<uint64_t>(1, std::min<uint64_t>(c.n, (uint64_t)c.max_items * g.n_tiles));
-  // units_of() of every tile: at most 1 + s / kSegsPerUnit + r / recs_per_unit() for s segments and r records
-  g.unit_cap = 2ull * g.n_tiles + g.seg_cap / kSegsPerUnit + c.n / kRecsPerUnitFew + 1;
+  g.unit_cap = tiled_unit_cap(g.n_tiles, g.seg_cap, c.n);
   return g;
+}
+// units_of() of a tile of s segments and r >= s records is less than
+// 1 + max(s / kSegsPerUnit, r / R), at most 1 + s / kSegsPerUnit + (r - s) / R
+// for R = recs_per_unit() > kSegsPerUnit; the sum grows with both totals.
+uint64_t tiled_unit_cap(uint32_t n_tiles, uint64_t seg_cap, uint32_t n) {
+  return (uint64_t)n_tiles + seg_cap / kSegsPerUnit + (n - std::min<uint64_t>(n, seg_cap)) / recs_per_unit(n_tiles) + 1;
 }
 
 namespace {

@@ -1,0 +1,96 @@
+"""The contexts' device scratch: what a call needs depends on the sizes that
+its documentation names and on nothing else, and what is taken beyond that (the
+multi-view launches) refuses no call, moves nothing that a captured graph
+reads, and is left out where it cannot be had.  Images against single renders."""
+
+import numpy as np
+import pytest
+
+from synth.camera import Camera
+from tests.gpu_util import assert_images_equal, image_to_host, render_gpu
+
+pytestmark = pytest.mark.gpu
+
+
+def _camera(W, H, f=60.0):
+    return Camera(np.array([f, 0, W / 2, 0, 0, f, H / 2, 0, 0, 0, 1, 0], np.float32), W, H)
+
+
+def _grid_cloud(per_cell, side=200, depth=4.0):
+    """per_cell points in each of side x side cells of 0.1 m, in front of the camera."""
+    rng = np.random.default_rng(per_cell)
+    i = np.repeat(np.arange(side * side), per_cell)
+    c = np.stack([i % side, i // side], 1) * 0.1 - side * 0.05 + 0.05
+    xy = c + rng.uniform(-0.03, 0.03, c.shape)
+    xyz = np.concatenate([xy, np.full((len(xy), 1), depth)], 1).astype(np.float32)
+    return xyz, rng.integers(0, 256, (len(xyz), 3)).astype(np.uint8)
+
+
+def _tiles(cam):
+    return -(-cam.width // 32) * -(-cam.height // 32)
+
+
+def _documented(n, n_cells, items, cam):
+    """Bytes of lnr_render: cull flags, work queues, counters, and the tiled
+    splat's 28 per point with a unit of work per 32 of them and a few words per tile."""
+    return n_cells + 128 * items + 92 + 28 * n + 8 * (n // 32) + 32 * _tiles(cam) + 12
+
+
+@pytest.mark.parametrize("W,H", [(20, 17), (640, 480)])
+def test_render_scratch_is_what_is_documented(lnr, ctx, W, H):
+    """Sparse cells: as many segments as points are possible."""
+    xyz, rgb = _grid_cloud(1)
+    cloud = lnr.lnr_cloud_load(ctx, xyz, rgb, 0.1)
+    cells = len(lnr.lnr_cloud_cell_start(cloud)) - 1
+    items = int((np.diff(lnr.lnr_cloud_cell_start(cloud).astype(np.int64)) > 0).sum())
+    c = lnr.lnr_context_create(0)
+    cam = _camera(W, H)
+    render_gpu(lnr, c, cloud, cam)
+    assert lnr.lnr_allocated_bytes(c) <= _documented(len(xyz), cells, items, cam)
+
+
+def test_render_scratch_warmed_by_the_largest_cloud(lnr, ctx):
+    """A context that has rendered a cloud of more points, and holds the work
+    queues of another, allocates nothing for the other at the same size."""
+    big = np.zeros((200_000, 3), np.float32)
+    big[:, 2] = 2.0 + np.linspace(0, 1, len(big))
+    dense = lnr.lnr_cloud_load(ctx, big, np.zeros((len(big), 3), np.uint8), 100.0)
+    sparse = lnr.lnr_cloud_load(ctx, *_grid_cloud(3), 0.1)
+    c = lnr.lnr_context_create(0)
+    cam = _camera(256, 256)
+    render_gpu(lnr, c, sparse, cam, flags=lnr.LNR_RENDER_ATOMIC_SPLAT)
+    render_gpu(lnr, c, dense, cam)
+    warm = lnr.lnr_allocated_bytes(c)
+    img = render_gpu(lnr, c, sparse, cam)
+    assert lnr.lnr_allocated_bytes(c) == warm
+    assert_images_equal(image_to_host(img), image_to_host(render_gpu(lnr, ctx, sparse, cam)), "sparse")
+
+
+def _views(lnr, ctx, cloud, cams):
+    import torch
+    imgs = [lnr.Image(c.height, c.width) for c in cams]
+    lnr.lnr_render_views(ctx, cloud, cams, imgs)
+    torch.cuda.synchronize()
+    return imgs
+
+
+def _assert_views(lnr, ctx, cloud, cams, imgs, what):
+    for v, (cam, img) in enumerate(zip(cams, imgs)):
+        assert_images_equal(image_to_host(img), image_to_host(render_gpu(lnr, ctx, cloud, cam)), f"{what}: view {v}")
+
+
+def test_views_of_a_small_cloud_after_a_large_one_under_a_budget(lnr, ctx, room_cloud, room_cams):
+    """Scratch that is larger than needed stays as it is: views whose other
+    needs have grown past the budget meanwhile still render."""
+    rng = np.random.default_rng(3)
+    xyz = rng.uniform(-1, 1, (3000, 3)).astype(np.float32) + np.float32([0, 0, 3])
+    small = lnr.lnr_cloud_load(ctx, xyz, rng.integers(0, 256, (3000, 3)).astype(np.uint8), 100.0)
+    free = lnr.lnr_context_create(0)
+    render_gpu(lnr, free, room_cloud, room_cams[0])
+    budget = lnr.lnr_allocated_bytes(free) + 200_000
+    c = lnr.lnr_context_create(0, budget)
+    render_gpu(lnr, c, room_cloud, room_cams[0])
+    cams = [_camera(1920, 1080, 400.0 + v) for v in range(8)]
+    imgs = _views(lnr, c, small, cams)
+    assert lnr.lnr_allocated_bytes(c) <= budget
+    _assert_views(lnr, ctx, small, cams, imgs, "small cloud")
