@@ -48,6 +48,10 @@ struct lnr_context {
   bool counted = false;  // the last render counted its z-buffer atomics
   uint32_t last_cells = 0;
   Scratch sc;
+  // lnr_render_views' tiled splat.  Its own, since it follows the number and the
+  // size of the views: what lnr_render uses stays in place under it (a caller
+  // may have captured those launches).
+  Buf views_tiled;
   // kernel timing
   struct Rec {
     const char *name;
@@ -557,7 +561,7 @@ void context_free(lnr_context *ctx) {
   (void)hipSetDevice(ctx->device);
   (void)hipDeviceSynchronize();
   for (Buf *b : {&ctx->sc.flags, &ctx->sc.chunks, &ctx->sc.counters, &ctx->sc.pyramid, &ctx->sc.act, &ctx->sc.soft_acc,
-                 &ctx->sc.tiled, &ctx->sc.views})
+                 &ctx->sc.tiled, &ctx->sc.views, &ctx->views_tiled})
     dfree(ctx, b->p, b->cap);
   for (auto &r : ctx->recs) {
     (void)hipEventDestroy(r.a);
@@ -738,7 +742,8 @@ void lnr_cloud_destroy(lnr_cloud *c) {
 // ---------------------------------------------------------------------------
 // render
 // ---------------------------------------------------------------------------
-// Scratch of the tiled splat for n_views views at once of a cloud of n points,
+// Scratch of the tiled splat for n_views views at once of a cloud of n points
+// (with the counters of every view but the first, which has the context's),
 // sized for grid g (the largest view's, see TiledSplatGrid): one allocation,
 // kTiledPad bytes beyond the arrays' own for their alignment.  (With one per
 // array a new context's first frame of 20M points at 1080p took 1080 us, 1020
@@ -746,7 +751,8 @@ void lnr_cloud_destroy(lnr_cloud *c) {
 constexpr size_t kTiledPad = 8 * 256;
 static size_t tiled_bytes(const TiledSplatGrid &g, uint32_t n, int n_views) {
   const size_t v = (size_t)n_views;
-  return v * (8ull * n + 20 * g.seg_cap + 8 * g.unit_cap + 4ull * tile_count_words(g.n_tiles) + 8ull * g.n_tiles + 4);
+  return v * (8ull * n + 20 * g.seg_cap + 8 * g.unit_cap + 4ull * tile_count_words(g.n_tiles) + 8ull * g.n_tiles + 4) +
+         (v - 1) * 4 * kViewCounterWords;
 }
 // What lnr_render allocates for one view: with room for a segment per record, so
 // that no cloud of fewer points at no more tiles needs more, whatever its cells
@@ -756,8 +762,14 @@ static size_t tiled_reserve(TiledSplatGrid g, uint32_t n) {
   g.unit_cap = tiled_unit_cap(g.n_tiles, g.seg_cap, n);
   return tiled_bytes(g, n, 1);
 }
-// the part of view v of n_views
-static TiledSplatBufs tiled_bufs(const Buf &b, const TiledSplatGrid &g, uint32_t n, int n_views = 1, int view = 0) {
+// the words to clear, from the first view's tile_nseg on: per-tile counts of
+// every view, then the counters of every view but the first
+static uint32_t tiled_clear_words(const TiledSplatGrid &g, int n_views = 1) {
+  return tile_count_words(g.n_tiles) * (uint32_t)n_views + kViewCounterWords * (uint32_t)(n_views - 1);
+}
+// the part of view v of n_views; *counters (views past the first): its counters
+static TiledSplatBufs tiled_bufs(const Buf &b, const TiledSplatGrid &g, uint32_t n, int n_views = 1, int view = 0,
+                                 uint32_t **counters = nullptr) {
   const size_t nv = (size_t)n_views, v = (size_t)view;
   char *at = static_cast<char *>(b.p);
   auto take = [&](size_t bytes) {  // every view's array, bytes each
@@ -770,7 +782,10 @@ static TiledSplatBufs tiled_bufs(const Buf &b, const TiledSplatGrid &g, uint32_t
   t.segs = reinterpret_cast<uint4 *>(take(16 * g.seg_cap));
   t.sorted = reinterpret_cast<uint32_t *>(take(4 * g.seg_cap));
   t.units = reinterpret_cast<uint2 *>(take(8 * g.unit_cap));
-  t.tile_nseg = reinterpret_cast<uint32_t *>(take(4ull * tile_count_words(g.n_tiles)));
+  t.tile_nseg = reinterpret_cast<uint32_t *>(at) + v * tile_count_words(g.n_tiles);
+  if (view > 0)
+    *counters = reinterpret_cast<uint32_t *>(at) + nv * tile_count_words(g.n_tiles) + (v - 1) * kViewCounterWords;
+  at += (4ull * tiled_clear_words(g, n_views) + 255) / 256 * 256;
   t.tile_off = reinterpret_cast<uint32_t *>(take(4ull * g.n_tiles + 4));
   t.tile_units = reinterpret_cast<uint32_t *>(take(4ull * g.n_tiles));
   return t;
@@ -866,7 +881,7 @@ static lnr_status render_impl(lnr_context *ctx, Scratch &scr, const lnr_cloud *c
   // keys of the tiles that merge through atomics, so only the counters here)
   LNR_LAUNCH(ctx, "clear", s,
              launch_clear(out->key, atomic ? npix : 0u, counters, kCounterWords,
-                          tb.tile_nseg, atomic ? 0u : tile_count_words(tg.n_tiles), s));
+                          tb.tile_nseg, atomic ? 0u : tiled_clear_words(tg), s));
   LNR_LAUNCH(ctx, "cull", s,
              launch_cull(c->d, prm, dev ? &dev->cull : nullptr, static_cast<uint8_t *>(scr.flags.p),
                          static_cast<uint2 *>(scr.chunks.p), atomic ? kSplatChunk : c->d.item_points, counters,
@@ -908,11 +923,11 @@ static TiledSplatGrid largest_grid(const lnr_cloud *c, const lnr_camera *cams, i
 }
 
 // Up to kViewsPerPass views (n) in the same launches of the tiled splat, whose
-// scratch (flags, views, counters, and the tiled splat's for n views of grid g)
+// scratch (flags, views, counters, and in `tiled` the tiled splat's for n views of grid g)
 // is there.  dev (may be nullptr): the views' cameras in device memory.
-static lnr_status render_tiled_views(lnr_context *ctx, Scratch &scr, const lnr_cloud *c, const lnr_camera *cams,
-                                     const lnr_image *outs, int n, const TiledSplatGrid &g, bool no_cull,
-                                     hipStream_t s, const DevCam *dev) {
+static lnr_status render_tiled_views(lnr_context *ctx, Scratch &scr, const Buf &tiled, const lnr_cloud *c,
+                                     const lnr_camera *cams, const lnr_image *outs, int n, const TiledSplatGrid &g,
+                                     bool no_cull, hipStream_t s, const DevCam *dev) {
   uint32_t *counters = static_cast<uint32_t *>(scr.counters.p);
   uint4 *items = static_cast<uint4 *>(scr.views.p);
   ViewsCull vc{};
@@ -920,13 +935,13 @@ static lnr_status render_tiled_views(lnr_context *ctx, Scratch &scr, const lnr_c
   TiledSplatView views[kViewsPerPass];
   for (int v = 0; v < n; ++v) {
     if (!dev) vc.v[v] = make_cull_params(&cams[v], no_cull);
-    views[v] = TiledSplatView{make_splat_cam(&cams[v]), dev ? &dev[v].splat : nullptr, (uint32_t)cams[v].height,
-                              tiled_bufs(scr.tiled, g, c->d.n, n, v), counters + (size_t)v * kViewCounterWords,
+    uint32_t *own = counters;
+    const TiledSplatBufs tb = tiled_bufs(tiled, g, c->d.n, n, v, &own);
+    views[v] = TiledSplatView{make_splat_cam(&cams[v]), dev ? &dev[v].splat : nullptr, (uint32_t)cams[v].height, tb, own,
                               outs[v].key, outs[v].depth, reinterpret_cast<uint32_t *>(outs[v].rgba), nullptr};
   }
   LNR_LAUNCH(ctx, "clear", s,
-             launch_clear(nullptr, 0u, counters, (uint32_t)(n * kViewCounterWords),
-                          views[0].b.tile_nseg, tile_count_words(g.n_tiles) * (uint32_t)n, s));
+             launch_clear(nullptr, 0u, counters, kCounterWords, views[0].b.tile_nseg, tiled_clear_words(g, n), s));
   LNR_LAUNCH(ctx, "cull_views", s,
              launch_cull_views(c->d, vc, dev, static_cast<uint8_t *>(scr.flags.p), items, c->d.item_points, counters,
                                s));
@@ -984,16 +999,16 @@ lnr_status lnr_render_views(lnr_context *ctx, const lnr_cloud *c, const lnr_came
   if ((st = ensure(ctx, scr.flags, c->d.n_cells)) != LNR_OK) return st;
   if ((st = ensure(ctx, scr.views, 16ull * kDepthBuckets * std::max<uint32_t>(1, c->d.max_chunks))) != LNR_OK)
     return st;
-  if ((st = ensure(ctx, scr.counters, 4 * kViewCounterWords * kViewsPerPass)) != LNR_OK) return st;
+  if ((st = ensure(ctx, scr.counters, 4 * kCounterWords)) != LNR_OK) return st;
   uint32_t *counters = static_cast<uint32_t *>(scr.counters.p);
   uint4 *items = static_cast<uint4 *>(scr.views.p);
   const bool no_cull = (flags & LNR_RENDER_NO_CULL) != 0;
   const TiledSplatGrid grid = largest_grid(c, cams, n_views);
-  const int at_once = tiled_views_at_once(ctx, scr.tiled, grid, c->d.n, std::min(n_views, kViewsPerPass));
+  const int at_once = tiled_views_at_once(ctx, ctx->views_tiled, grid, c->d.n, std::min(n_views, kViewsPerPass));
   if (at_once > 0) {
-    if ((st = ensure(ctx, scr.tiled, tiled_bytes(grid, c->d.n, at_once), kTiledPad)) != LNR_OK) return st;
+    if ((st = ensure(ctx, ctx->views_tiled, tiled_bytes(grid, c->d.n, at_once), kTiledPad)) != LNR_OK) return st;
     for (int g = 0; g < n_views; g += at_once)
-      if ((st = render_tiled_views(ctx, scr, c, cams + g, outs + g, std::min(at_once, n_views - g), grid, no_cull, s,
+      if ((st = render_tiled_views(ctx, scr, ctx->views_tiled, c, cams + g, outs + g, std::min(at_once, n_views - g), grid, no_cull, s,
                                    nullptr)) != LNR_OK)
         return st;
     ctx->last_stream = s;
@@ -1643,7 +1658,7 @@ lnr_status lnr_server_create(lnr_context *ctx, const lnr_cloud *c, const lnr_une
     }
     if ((st = ensure(ctx, l.sc.flags, c->d.n_cells)) != LNR_OK ||
         (st = ensure(ctx, l.sc.chunks, 8ull * kDepthBuckets * std::max<uint32_t>(1, c->d.max_chunks))) != LNR_OK ||
-        (st = ensure(ctx, l.sc.counters, 4 * kViewCounterWords * kViewsPerPass)) != LNR_OK ||
+        (st = ensure(ctx, l.sc.counters, 4 * kCounterWords)) != LNR_OK ||
         (st = ensure(ctx, l.sc.pyramid, pyr)) != LNR_OK || (st = ensure(ctx, l.sc.act, act)) != LNR_OK ||
         (st = ensure(ctx, l.sc.tiled, tiled_bytes(tiled_splat_grid((uint32_t)mW, (uint32_t)mH, c->d), c->d.n, 1),
                      kTiledPad)) != LNR_OK ||
@@ -1866,7 +1881,7 @@ lnr_status lnr_server_step(lnr_server *srv, int32_t *launched) {
       lnr_status r;
       if (n > 1) {
         const TiledSplatGrid g = tiled_splat_grid((uint32_t)W, (uint32_t)H, srv->cloud->d);
-        r = render_tiled_views(ctx, lane->sc, srv->cloud, cams, img, n, g, false, s, lane->cams_dev + b);
+        r = render_tiled_views(ctx, lane->sc, lane->sc.tiled, srv->cloud, cams, img, n, g, false, s, lane->cams_dev + b);
       } else {
         r = render_impl(ctx, lane->sc, srv->cloud, &cams[0], &img[0], 0, srv->cfg.soft != 0, srv->cfg.soft_eps, s,
                         lane->cams_dev + b);

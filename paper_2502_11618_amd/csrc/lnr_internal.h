@@ -92,7 +92,7 @@ constexpr int kAtomicWord = 4 + kDepthBuckets;
 constexpr int kSegTopWord = kAtomicWord + 1;
 constexpr int kUnitsWord = kSegTopWord + 1;
 constexpr int kCounterWords = kUnitsWord + 1;
-constexpr int kViewCounterWords = 64;  // counters of view v of a multi-view render start at word 64 v
+constexpr int kViewCounterWords = 64;  // of each view of a multi-view render but the first (256 bytes apart: they are atomics of other workgroups)
 static_assert(kCounterWords <= kViewCounterWords, "a view's counters");
 
 // ----------------------------------------------------------------------------

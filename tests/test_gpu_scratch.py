@@ -94,3 +94,28 @@ def test_views_of_a_small_cloud_after_a_large_one_under_a_budget(lnr, ctx, room_
     imgs = _views(lnr, c, small, cams)
     assert lnr.lnr_allocated_bytes(c) <= budget
     _assert_views(lnr, ctx, small, cams, imgs, "small cloud")
+
+
+def test_a_captured_render_outlives_larger_views(lnr, ctx, room_cloud, room_cams):
+    """A graph of lnr_render stays valid while lnr_render_views takes scratch
+    for more and larger views on the same context."""
+    import torch
+    c = lnr.lnr_context_create(0)
+    want = image_to_host(render_gpu(lnr, ctx, room_cloud, room_cams[0]))
+    img = lnr.Image(room_cams[0].height, room_cams[0].width)
+    lnr.lnr_render(c, room_cloud, room_cams[0], img)
+    torch.cuda.synchronize()
+    held = lnr.lnr_allocated_bytes(c)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        lnr.lnr_render(c, room_cloud, room_cams[0], img)
+    for n in (2, 8):
+        cams = list(room_cams[1:1 + n])
+        imgs = _views(lnr, c, room_cloud, cams)
+        _assert_views(lnr, ctx, room_cloud, cams, imgs, f"{n} views")
+        assert lnr.lnr_allocated_bytes(c) > held
+        img.key.fill_(0)
+        img.rgba.fill_(7)
+        graph.replay()
+        torch.cuda.synchronize()
+        assert_images_equal(image_to_host(img), want, f"replay after {n} views")
