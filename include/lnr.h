@@ -198,11 +198,11 @@ lnr_status lnr_render_soft(lnr_context *ctx, const lnr_cloud *c, const lnr_camer
  * A pass is the screen-tiled splat of all its views in the same launches.  Its
  * scratch is lnr_render's once per view, so a pass takes as many views as fit
  * in 6 GiB of scratch, the context's budget and a quarter of the free device
- * memory.  Where the budget does not hold even one view's, the z-buffers are
+ * memory.  Where not even one view's does, or can be allocated, the z-buffers are
  * the images' key buffers, lowered with 64-bit atomicMin after an on-chip
  * z-buffer per work item (LNR_RENDER_ATOMIC_SPLAT's method), and a pass loads
  * each point once.  Uses 16 bytes of context scratch per work item and depth
- * bucket besides.
+ * bucket besides, the only scratch without which the call fails.
  * lnr_render_stats then reports the last pass: cells visible in at least one
  * of its views, and the points of those cells, each counted once.  Errors as
  * lnr_render, checked for every view before anything is enqueued. */
@@ -305,7 +305,8 @@ lnr_status lnr_profile_enable(lnr_context *ctx, int enable);
  * failed hipMalloc does (LNR_E_OUT_OF_MEMORY; no device memory is taken), and
  * injection then switches itself off.  after < 0 switches it off.  Every
  * entry point must then return that status, free what it allocated and leave
- * caller buffers untouched. */
+ * caller buffers untouched, or, where the allocation is one that it can do
+ * without (lnr_render_views' per-point scratch), succeed all the same. */
 lnr_status lnr_debug_fail_allocation(lnr_context *ctx, int64_t after);
 lnr_status lnr_profile_read(lnr_context *ctx, lnr_kernel_time *out, int32_t max, int32_t *count);
 

@@ -793,9 +793,9 @@ static TiledSplatBufs tiled_bufs(const Buf &b, const TiledSplatGrid &g, uint32_t
 
 // How many of n views the tiled splat takes at once: all of them while their
 // scratch stays within kViewsScratch (more per launch fills the chip better,
-// but the scratch is 28 bytes per point and view), the budget, and a quarter of
-// the device memory still free; shared out evenly over the passes.  0: not even
-// one view's scratch fits the budget.
+// but the scratch is up to 28 bytes per point and view), the budget, and a
+// quarter of the device memory still free; shared out evenly over the passes.
+// 0: not even one view's scratch does, beyond what `held` has.
 constexpr size_t kViewsScratch = 6ull << 30;
 static int tiled_views_at_once(lnr_context *ctx, const Buf &held, const TiledSplatGrid &g, uint32_t n_points, int n) {
   size_t free_bytes = 0, total_bytes = 0;
@@ -804,17 +804,28 @@ static int tiled_views_at_once(lnr_context *ctx, const Buf &held, const TiledSpl
     const size_t need = tiled_bytes(g, n_points, v);
     if (need > held.cap) {
       if (ctx->budget && ctx->allocated - held.cap + need > ctx->budget) continue;
-      if (v > 1) {
-        if (need > kViewsScratch) continue;
-        if (!asked && hipMemGetInfo(&free_bytes, &total_bytes) != hipSuccess) free_bytes = 0;
-        asked = true;
-        if (need > free_bytes / 4) continue;
-      }
+      if (v > 1 && need > kViewsScratch) continue;
+      if (!asked && hipMemGetInfo(&free_bytes, &total_bytes) != hipSuccess) free_bytes = 0;
+      asked = true;
+      if (need - held.cap > free_bytes / 4) continue;
     }
     const int passes = (n + v - 1) / v;
     return (n + passes - 1) / passes;
   }
   return 0;
+}
+// The same for lnr_render_views, with the scratch allocated.  It is a faster way
+// to the same images, so that an allocation that fails refuses nothing: fewer views
+// are tried, then none.
+static int views_at_once(lnr_context *ctx, const TiledSplatGrid &g, uint32_t n_points, int n) {
+  const std::string err = ctx->err;
+  int v = std::min(n, kViewsPerPass);
+  while ((v = tiled_views_at_once(ctx, ctx->views_tiled, g, n_points, v)) > 0 &&
+         ensure(ctx, ctx->views_tiled, tiled_bytes(g, n_points, v), kTiledPad) != LNR_OK) {
+    ctx->err = err;
+    --v;
+  }
+  return v;
 }
 
 static SplatCam make_splat_cam(const lnr_camera *cam) {
@@ -999,14 +1010,13 @@ lnr_status lnr_render_views(lnr_context *ctx, const lnr_cloud *c, const lnr_came
   if ((st = ensure(ctx, scr.flags, c->d.n_cells)) != LNR_OK) return st;
   if ((st = ensure(ctx, scr.views, 16ull * kDepthBuckets * std::max<uint32_t>(1, c->d.max_chunks))) != LNR_OK)
     return st;
+  const TiledSplatGrid grid = largest_grid(c, cams, n_views);
+  const int at_once = views_at_once(ctx, grid, c->d.n, n_views);
   if ((st = ensure(ctx, scr.counters, 4 * kCounterWords)) != LNR_OK) return st;
   uint32_t *counters = static_cast<uint32_t *>(scr.counters.p);
   uint4 *items = static_cast<uint4 *>(scr.views.p);
   const bool no_cull = (flags & LNR_RENDER_NO_CULL) != 0;
-  const TiledSplatGrid grid = largest_grid(c, cams, n_views);
-  const int at_once = tiled_views_at_once(ctx, ctx->views_tiled, grid, c->d.n, std::min(n_views, kViewsPerPass));
   if (at_once > 0) {
-    if ((st = ensure(ctx, ctx->views_tiled, tiled_bytes(grid, c->d.n, at_once), kTiledPad)) != LNR_OK) return st;
     for (int g = 0; g < n_views; g += at_once)
       if ((st = render_tiled_views(ctx, scr, ctx->views_tiled, c, cams + g, outs + g, std::min(at_once, n_views - g), grid, no_cull, s,
                                    nullptr)) != LNR_OK)
@@ -1017,7 +1027,7 @@ lnr_status lnr_render_views(lnr_context *ctx, const lnr_cloud *c, const lnr_came
     ctx->last_cells = c->d.n_cells;
     return LNR_OK;
   }
-  // the tiled splat's scratch does not fit the budget: z-buffers in device memory
+  // no scratch for the tiled splat: z-buffers in device memory
   for (int g = 0; g < n_views; g += kViewsPerPass) {
     const int n = std::min(kViewsPerPass, n_views - g);
     ViewsCull vc{};

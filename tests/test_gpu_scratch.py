@@ -119,3 +119,21 @@ def test_a_captured_render_outlives_larger_views(lnr, ctx, room_cloud, room_cams
         graph.replay()
         torch.cuda.synchronize()
         assert_images_equal(image_to_host(img), want, f"replay after {n} views")
+
+
+@pytest.mark.parametrize("n", [8, 1])
+def test_views_take_fewer_where_scratch_cannot_be_allocated(lnr, ctx, room_cloud, room_cams, n):
+    """A failed allocation refuses no multi-view call: fewer views per pass
+    then, and with one view z-buffers in device memory."""
+    cams = list(room_cams[:n])
+    grew = []
+    for fail in (1, -1):  # the second allocation (after the work items), none
+        c = lnr.lnr_context_create(0)
+        render_gpu(lnr, c, room_cloud, cams[0], flags=lnr.LNR_RENDER_ATOMIC_SPLAT)  # cull flags and counters
+        before = lnr.lnr_allocated_bytes(c)
+        lnr.lnr_debug_fail_allocation(c, fail)
+        imgs = _views(lnr, c, room_cloud, cams)
+        lnr.lnr_debug_fail_allocation(c, -1)
+        grew.append(lnr.lnr_allocated_bytes(c) - before)
+        _assert_views(lnr, ctx, room_cloud, cams, imgs, f"failure {fail}")
+    assert grew[0] < grew[1]
