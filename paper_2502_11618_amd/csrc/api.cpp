@@ -52,6 +52,9 @@ struct lnr_context {
   // size of the views: what lnr_render uses stays in place under it (a caller
   // may have captured those launches).
   Buf views_tiled;
+  bool views_captured = false;     // views_tiled is used by launches that a caller has captured:
+  std::vector<Buf> views_kept;     // it is then kept until the context goes, a larger one beside it
+  size_t views_refused = SIZE_MAX; // this much was refused once and is not asked for again
   // kernel timing
   struct Rec {
     const char *name;
@@ -563,6 +566,7 @@ void context_free(lnr_context *ctx) {
   for (Buf *b : {&ctx->sc.flags, &ctx->sc.chunks, &ctx->sc.counters, &ctx->sc.pyramid, &ctx->sc.act, &ctx->sc.soft_acc,
                  &ctx->sc.tiled, &ctx->sc.views, &ctx->views_tiled})
     dfree(ctx, b->p, b->cap);
+  for (const Buf &b : ctx->views_kept) dfree(ctx, b.p, b.cap);
   for (auto &r : ctx->recs) {
     (void)hipEventDestroy(r.a);
     (void)hipEventDestroy(r.b);
@@ -797,17 +801,20 @@ static TiledSplatBufs tiled_bufs(const Buf &b, const TiledSplatGrid &g, uint32_t
 // quarter of the device memory still free; shared out evenly over the passes.
 // 0: not even one view's scratch does, beyond what `held` has.
 constexpr size_t kViewsScratch = 6ull << 30;
-static int tiled_views_at_once(lnr_context *ctx, const Buf &held, const TiledSplatGrid &g, uint32_t n_points, int n) {
+static int tiled_views_at_once(lnr_context *ctx, const Buf &held, const TiledSplatGrid &g, uint32_t n_points, int n,
+                               size_t *refused) {
   size_t free_bytes = 0, total_bytes = 0;
   bool asked = false;
   for (int v = std::min(n, kViewsPerPass); v >= 1; --v) {
     const size_t need = tiled_bytes(g, n_points, v);
     if (need > held.cap) {
-      if (ctx->budget && ctx->allocated - held.cap + need > ctx->budget) continue;
-      if (v > 1 && need > kViewsScratch) continue;
+      if (need >= *refused || (v > 1 && need > kViewsScratch)) continue;
       if (!asked && hipMemGetInfo(&free_bytes, &total_bytes) != hipSuccess) free_bytes = 0;
       asked = true;
-      if (need - held.cap > free_bytes / 4) continue;
+      if ((ctx->budget && ctx->allocated - held.cap + need > ctx->budget) || need - held.cap > free_bytes / 4) {
+        *refused = need;
+        continue;
+      }
     }
     const int passes = (n + v - 1) / v;
     return (n + passes - 1) / passes;
@@ -815,15 +822,42 @@ static int tiled_views_at_once(lnr_context *ctx, const Buf &held, const TiledSpl
   return 0;
 }
 // The same for lnr_render_views, with the scratch allocated.  It is a faster way
-// to the same images, so that an allocation that fails refuses nothing: fewer views
-// are tried, then none.
-static int views_at_once(lnr_context *ctx, const TiledSplatGrid &g, uint32_t n_points, int n) {
+// to the same images:
+//  - an allocation that fails refuses nothing: fewer views are tried, then none;
+//  - what was refused once is not asked for again, so that a repeated call
+//    neither asks nor allocates;
+//  - nothing is allocated while the caller captures the stream, and what the
+//    captured launches use is never freed under them (within kViewsScratch in all).
+static int views_at_once(lnr_context *ctx, const TiledSplatGrid &g, uint32_t n_points, int n, hipStream_t s) {
+  Buf &held = ctx->views_tiled;
+  hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+  const bool asked = hipStreamIsCapturing(s, &capture) == hipSuccess;
+  if (!asked || capture != hipStreamCaptureStatusNone) {
+    (void)hipGetLastError();
+    size_t nothing = 0;
+    const int v = tiled_views_at_once(ctx, held, g, n_points, n, &nothing);
+    if (v > 0) ctx->views_captured = true;
+    return v;
+  }
   const std::string err = ctx->err;
-  int v = std::min(n, kViewsPerPass);
-  while ((v = tiled_views_at_once(ctx, ctx->views_tiled, g, n_points, v)) > 0 &&
-         ensure(ctx, ctx->views_tiled, tiled_bytes(g, n_points, v), kTiledPad) != LNR_OK) {
+  int v = n;
+  while ((v = tiled_views_at_once(ctx, held, g, n_points, v, &ctx->views_refused)) > 0) {
+    const size_t need = tiled_bytes(g, n_points, v);
+    if (need > held.cap && ctx->views_captured) {
+      size_t sum = held.cap + need;
+      for (const Buf &b : ctx->views_kept) sum += b.cap;
+      Buf larger;
+      if (sum <= kViewsScratch && ensure(ctx, larger, need, kTiledPad) == LNR_OK) {
+        ctx->views_kept.push_back(held);
+        held = larger;
+        ctx->views_captured = false;
+        break;
+      }
+    } else if (ensure(ctx, held, need, kTiledPad) == LNR_OK) {
+      break;
+    }
     ctx->err = err;
-    --v;
+    ctx->views_refused = need;
   }
   return v;
 }
@@ -1011,7 +1045,7 @@ lnr_status lnr_render_views(lnr_context *ctx, const lnr_cloud *c, const lnr_came
   if ((st = ensure(ctx, scr.views, 16ull * kDepthBuckets * std::max<uint32_t>(1, c->d.max_chunks))) != LNR_OK)
     return st;
   const TiledSplatGrid grid = largest_grid(c, cams, n_views);
-  const int at_once = views_at_once(ctx, grid, c->d.n, n_views);
+  const int at_once = views_at_once(ctx, grid, c->d.n, std::min(n_views, kViewsPerPass), s);
   if ((st = ensure(ctx, scr.counters, 4 * kCounterWords)) != LNR_OK) return st;
   uint32_t *counters = static_cast<uint32_t *>(scr.counters.p);
   uint4 *items = static_cast<uint4 *>(scr.views.p);
@@ -1690,7 +1724,8 @@ lnr_status lnr_server_create(lnr_context *ctx, const lnr_cloud *c, const lnr_une
     const size_t most = 28ull * c->d.n + npix * (u->prec == Prec::F32 ? 32 : u->prec == Prec::BF16X3 ? 64 : 32) *
                                              (size_t)cfg->max_batch;
     for (auto &l : srv->lanes) {
-      int v = tiled_views_at_once(ctx, l.sc.tiled, g, c->d.n, std::min(cfg->max_batch, kViewsPerPass));
+      size_t refused = SIZE_MAX;
+      int v = tiled_views_at_once(ctx, l.sc.tiled, g, c->d.n, std::min(cfg->max_batch, kViewsPerPass), &refused);
       auto needs = [&](int n) {
         return 16ull * kDepthBuckets * std::max<uint32_t>(1, c->d.max_chunks) + pyr * (size_t)(n - 1) +
                tiled_bytes(g, c->d.n, n);

@@ -137,3 +137,49 @@ def test_views_take_fewer_where_scratch_cannot_be_allocated(lnr, ctx, room_cloud
         grew.append(lnr.lnr_allocated_bytes(c) - before)
         _assert_views(lnr, ctx, room_cloud, cams, imgs, f"failure {fail}")
     assert grew[0] < grew[1]
+
+
+def test_views_do_not_ask_again(lnr, ctx, room_cloud, room_cams):
+    """What a first call was refused, a repeated one does not allocate either."""
+    cams = list(room_cams[:8])
+    c = lnr.lnr_context_create(0)
+    render_gpu(lnr, c, room_cloud, cams[0], flags=lnr.LNR_RENDER_ATOMIC_SPLAT)
+    lnr.lnr_debug_fail_allocation(c, 1)
+    _views(lnr, c, room_cloud, cams)
+    lnr.lnr_debug_fail_allocation(c, -1)
+    first = lnr.lnr_allocated_bytes(c)
+    imgs = _views(lnr, c, room_cloud, cams)
+    assert lnr.lnr_allocated_bytes(c) == first
+    _assert_views(lnr, ctx, room_cloud, cams, imgs, "again")
+
+
+@pytest.mark.parametrize("warm", [1, 2, 8])
+def test_captured_views(lnr, ctx, room_cloud, room_cams, warm):
+    """Eight views captured on a context that has rendered `warm` small ones: no
+    allocation under capture, and every replay gives the images, also after the
+    context has taken scratch for larger views."""
+    import dataclasses
+    import torch
+    c = lnr.lnr_context_create(0)
+    small = [dataclasses.replace(k, width=128, height=96) for k in room_cams[:warm]]
+    _views(lnr, c, room_cloud, small)
+    held = lnr.lnr_allocated_bytes(c)
+    cams = list(room_cams[:8])
+    imgs = [lnr.Image(k.height, k.width) for k in cams]
+    graph = torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph):
+        lnr.lnr_render_views(c, room_cloud, cams, imgs)
+    assert lnr.lnr_allocated_bytes(c) == held
+    large = [dataclasses.replace(k, width=1024, height=768) for k in room_cams[8:16]]
+    for n in (0, 4, 8):
+        if n:
+            _assert_views(lnr, ctx, room_cloud, large[:n], _views(lnr, c, room_cloud, large[:n]), f"{n} large")
+        for img in imgs:
+            img.key.fill_(0)
+            img.rgba.fill_(7)
+        graph.replay()
+        torch.cuda.synchronize()
+        _assert_views(lnr, ctx, room_cloud, cams, imgs, f"replay after {n}")
+    del graph
+    lnr.lnr_context_destroy(c)
