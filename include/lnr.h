@@ -202,7 +202,10 @@ lnr_status lnr_render_soft(lnr_context *ctx, const lnr_cloud *c, const lnr_camer
  * the images' key buffers, lowered with 64-bit atomicMin after an on-chip
  * z-buffer per work item (LNR_RENDER_ATOMIC_SPLAT's method), and a pass loads
  * each point once.  Uses 16 bytes of context scratch per work item and depth
- * bucket besides, the only scratch without which the call fails.
+ * bucket besides, the only scratch without which the call fails: the rest
+ * is kept from call to call, but given back when another allocation through
+ * the context does not fit beside it.  Under stream capture it is used as it is
+ * (with a budget: not at all) and then kept until the context goes.
  * lnr_render_stats then reports the last pass: cells visible in at least one
  * of its views, and the points of those cells, each counted once.  Errors as
  * lnr_render, checked for every view before anything is enqueued. */

@@ -148,17 +148,35 @@ const char *const kConvNames[2][6][2] = {
     {{"conv/dec0a", "conv/dec0b"}, {"conv/dec1a", "conv/dec1b"}, {"conv/dec2a", "conv/dec2b"},
      {"conv/dec3a", "conv/dec3b"}, {"conv/dec4a", "conv/dec4b"}, {"conv/dec5a", "conv/dec5b"}}};
 
+void dfree(lnr_context *ctx, void *p, size_t bytes);
+
+// lnr_render_views' scratch is only there for speed: it gives way to whatever else
+// does not fit beside it (and is not asked for in that size again)
+bool release_views(lnr_context *ctx) {
+  Buf &b = ctx->views_tiled;
+  if (!b.p || ctx->views_captured || hipDeviceSynchronize() != hipSuccess) return false;
+  ctx->views_refused = std::min(ctx->views_refused, b.cap);
+  dfree(ctx, b.p, b.cap);
+  b = Buf();
+  return true;
+}
+
 // room: bytes to allocate, where that is more than what is accounted for
 lnr_status dalloc(lnr_context *ctx, void **p, size_t bytes, size_t room = 0) {
   *p = nullptr;
   if (bytes == 0) bytes = 256;
   if (ctx->fail_alloc_after >= 0 && ctx->fail_alloc_after-- == 0)
     return fail(ctx, LNR_E_OUT_OF_MEMORY, "hipMalloc(" + std::to_string(bytes) + ") failed: injected failure");
-  if (ctx->budget && ctx->allocated + bytes > ctx->budget)
+  const auto over = [&] { return ctx->budget && ctx->allocated + bytes > ctx->budget; };
+  if (over() && (!release_views(ctx) || over()))
     return fail(ctx, LNR_E_BUDGET,
                 "allocation of " + std::to_string(bytes) + " bytes exceeds the context budget of " +
                     std::to_string(ctx->budget) + " bytes (" + std::to_string(ctx->allocated) + " in use)");
   hipError_t e = hipMalloc(p, std::max(bytes, room));
+  if (e != hipSuccess && release_views(ctx)) {
+    (void)hipGetLastError();
+    e = hipMalloc(p, std::max(bytes, room));
+  }
   if (e != hipSuccess) {
     *p = nullptr;
     (void)hipGetLastError();
@@ -826,6 +844,7 @@ static int tiled_views_at_once(lnr_context *ctx, const Buf &held, const TiledSpl
 //  - an allocation that fails refuses nothing: fewer views are tried, then none;
 //  - what was refused once is not asked for again, so that a repeated call
 //    neither asks nor allocates;
+//  - it gives way to every other allocation (release_views);
 //  - nothing is allocated while the caller captures the stream, and what the
 //    captured launches use is never freed under them (within kViewsScratch in all).
 static int views_at_once(lnr_context *ctx, const TiledSplatGrid &g, uint32_t n_points, int n, hipStream_t s) {
@@ -834,6 +853,7 @@ static int views_at_once(lnr_context *ctx, const TiledSplatGrid &g, uint32_t n_p
   const bool asked = hipStreamIsCapturing(s, &capture) == hipSuccess;
   if (!asked || capture != hipStreamCaptureStatusNone) {
     (void)hipGetLastError();
+    if (ctx->budget) return 0;  // (what is captured could not give way)
     size_t nothing = 0;
     const int v = tiled_views_at_once(ctx, held, g, n_points, n, &nothing);
     if (v > 0) ctx->views_captured = true;

@@ -183,3 +183,40 @@ def test_captured_views(lnr, ctx, room_cloud, room_cams, warm):
         _assert_views(lnr, ctx, room_cloud, cams, imgs, f"replay after {n}")
     del graph
     lnr.lnr_context_destroy(c)
+
+
+def test_views_give_way_under_a_budget(lnr, room_cloud, room_cams):
+    """A budget that holds a network, a reconstruction, a small cloud, a server
+    and a session besides what a multi-view call cannot do without: none of
+    them is refused after a multi-view call, which renders the same before and
+    after."""
+    import torch
+    import synth
+    cams = list(room_cams[:8])
+    blob = synth.make_unet_blob((16, 32), seed=0)
+    rng = np.random.default_rng(1)
+    xyz, rgb = rng.uniform(-1, 1, (1000, 3)).astype(np.float32), rng.integers(0, 256, (1000, 3)).astype(np.uint8)
+    out = torch.empty((3, cams[0].height, cams[0].width), dtype=torch.float32, device="cuda")
+
+    def everything(c, views):
+        net = lnr.lnr_unet_load(c, blob, lnr.LNR_FP16)
+        img = lnr.Image(cams[0].height, cams[0].width)
+        img.depth.zero_()
+        img.rgba.zero_()
+        first = _views(lnr, c, room_cloud, cams) if views else None
+        lnr.lnr_reconstruct(c, net, img, out)
+        cloud = lnr.lnr_cloud_load(c, xyz, rgb, 100.0)
+        srv = lnr.lnr_server_create(c, cloud, net, max_batch=1, lanes=2, n_levels=3, max_width=128, max_height=96)
+        lnr.lnr_server_open_session(srv, 128, 96)
+        if views:
+            again = _views(lnr, c, room_cloud, cams)
+            for a, b in zip(first, again):
+                assert_images_equal(image_to_host(a), image_to_host(b), "again")
+        return lnr.lnr_allocated_bytes(c)
+
+    items = int((np.diff(lnr.lnr_cloud_cell_start(room_cloud).astype(np.int64)) + 4095 >> 12).sum())
+    cells = len(lnr.lnr_cloud_cell_start(room_cloud)) - 1
+    # (loading the small cloud takes 100 KB for a moment)
+    budget = everything(lnr.lnr_context_create(0), False) + cells + 256 * items + 92 + 100_000
+    c = lnr.lnr_context_create(0, budget)
+    assert everything(c, True) <= budget
