@@ -309,7 +309,8 @@ lnr_status lnr_profile_enable(lnr_context *ctx, int enable);
  * injection then switches itself off.  after < 0 switches it off.  Every
  * entry point must then return that status, free what it allocated and leave
  * caller buffers untouched, or, where the allocation is one that it can do
- * without (lnr_render_views' per-point scratch), succeed all the same. */
+ * without (lnr_render_views' per-point scratch, a server lane's for several
+ * requests per launch), succeed all the same. */
 lnr_status lnr_debug_fail_allocation(lnr_context *ctx, int64_t after);
 lnr_status lnr_profile_read(lnr_context *ctx, lnr_kernel_time *out, int32_t max, int32_t *count);
 

@@ -1736,29 +1736,39 @@ lnr_status lnr_server_create(lnr_context *ctx, const lnr_cloud *c, const lnr_une
     l.slot_bytes = slot_bytes;
     l.slot_px = slot_px;
   }
-  // More scratch for several slots per launch.  A budget is for sessions: under
-  // one, a lane takes no more in all than 28 bytes per point and a 16-channel
-  // input tensor of the batch, so that this refuses no session.
+  // More scratch for several slots per launch, where it can be had: a lane does
+  // without.  A budget is for sessions: under one, a lane takes no more in all
+  // than 28 bytes per point and a 16-channel input tensor of the batch, so that
+  // this refuses no session.
   if (!cfg->soft && cfg->max_batch > 1) {
     const TiledSplatGrid g = tiled_splat_grid((uint32_t)mW, (uint32_t)mH, c->d);
     const size_t most = 28ull * c->d.n + npix * (u->prec == Prec::F32 ? 32 : u->prec == Prec::BF16X3 ? 64 : 32) *
                                              (size_t)cfg->max_batch;
+    const size_t items = 16ull * kDepthBuckets * std::max<uint32_t>(1, c->d.max_chunks);
+    const std::string err = ctx->err;
     for (auto &l : srv->lanes) {
       size_t refused = SIZE_MAX;
       int v = tiled_views_at_once(ctx, l.sc.tiled, g, c->d.n, std::min(cfg->max_batch, kViewsPerPass), &refused);
-      auto needs = [&](int n) {
-        return 16ull * kDepthBuckets * std::max<uint32_t>(1, c->d.max_chunks) + pyr * (size_t)(n - 1) +
-               tiled_bytes(g, c->d.n, n);
-      };
-      while (v > 1 && ctx->budget && needs(v) > most) --v;
+      auto needs = [&](int n) { return items + pyr * (size_t)(n - 1) + tiled_bytes(g, c->d.n, n); };
+      while (v > 1 && ctx->budget &&
+             (needs(v) > most || ctx->allocated - std::min(l.sc.tiled.cap, tiled_bytes(g, c->d.n, v)) + needs(v) > ctx->budget))
+        --v;
       if (v <= 1) continue;
-      if ((st = ensure(ctx, l.sc.views, 16ull * kDepthBuckets * std::max<uint32_t>(1, c->d.max_chunks))) != LNR_OK ||
-          (st = ensure(ctx, l.sc.pyramid, pyr * (size_t)v)) != LNR_OK ||
-          (st = ensure(ctx, l.sc.tiled, tiled_bytes(g, c->d.n, v), kTiledPad)) != LNR_OK) {
+      if (ensure(ctx, l.sc.views, items) == LNR_OK && ensure(ctx, l.sc.pyramid, pyr * (size_t)v) == LNR_OK &&
+          ensure(ctx, l.sc.tiled, tiled_bytes(g, c->d.n, v), kTiledPad) == LNR_OK) {
+        l.views = v;
+        continue;
+      }
+      ctx->err = err;
+      for (Buf *b : {&l.sc.views, &l.sc.pyramid}) {
+        dfree(ctx, b->p, b->cap);
+        *b = Buf();
+      }
+      if ((st = ensure(ctx, l.sc.pyramid, pyr)) != LNR_OK ||
+          (st = ensure(ctx, l.sc.tiled, tiled_bytes(g, c->d.n, 1), kTiledPad)) != LNR_OK) {
         server_release(srv.get());
         return st;
       }
-      l.views = v;
     }
   }
   ++ctx->children;

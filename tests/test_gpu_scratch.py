@@ -220,3 +220,74 @@ def test_views_give_way_under_a_budget(lnr, room_cloud, room_cams):
     budget = everything(lnr.lnr_context_create(0), False) + cells + 256 * items + 92 + 100_000
     c = lnr.lnr_context_create(0, budget)
     assert everything(c, True) <= budget
+
+
+def _serve_two(lnr, ctx, srv, cloud, net, cams):
+    """Two sessions' requests in one batch against the frames computed alone."""
+    import torch
+    sids = [lnr.lnr_server_open_session(srv, k.width, k.height) for k in cams]
+    for t, (sid, k) in enumerate(zip(sids, cams)):
+        lnr.lnr_server_submit(srv, sid, k, t)
+    got = {}
+    for _ in range(100000):
+        lnr.lnr_server_step(srv)
+        for r in lnr.lnr_server_poll(srv):
+            out = torch.empty((3, r["height"], r["width"]), dtype=torch.float32, device="cuda")
+            lnr.copy_from_device(r["rgb"], out)
+            got[r["tag"]] = out
+            assert r["batch"] == 2
+        if len(got) == 2:
+            break
+    for t, k in enumerate(cams):
+        img = render_gpu(lnr, ctx, cloud, k)
+        lnr.lnr_depth_filter(ctx, img, 3, 0.5)
+        want = torch.empty_like(got[t])
+        lnr.lnr_reconstruct(ctx, net, img, want)
+        torch.cuda.synchronize()
+        assert torch.equal(got[t], want), f"request {t}"
+
+
+def test_server_without_the_scratch_for_several_requests(lnr, ctx, room_cloud, room_cams):
+    """A server lane's scratch for several requests per launch refuses no
+    server, where it cannot be allocated or does not fit the budget."""
+    import dataclasses
+    import synth
+    cams = [dataclasses.replace(k, width=128, height=96) for k in room_cams[:2]]
+    blob = synth.make_unet_blob((16, 32, 64), seed=0)
+    net = lnr.lnr_unet_load(ctx, blob, lnr.LNR_FP16)
+
+    def create(c):
+        net = lnr.lnr_unet_load(c, blob, lnr.LNR_FP16)
+        return lnr.lnr_server_create(c, room_cloud, net, max_batch=2, lanes=1, n_levels=3, filter_strength=0.5,
+                                     max_width=128, max_height=96)
+
+    c = lnr.lnr_context_create(0)
+    keep = create(c)
+    full = lnr.lnr_allocated_bytes(c)
+    lnr.lnr_server_destroy(keep)
+    without = None
+    for n in range(64):
+        c = lnr.lnr_context_create(0)
+        net_c = lnr.lnr_unet_load(c, blob, lnr.LNR_FP16)
+        lnr.lnr_debug_fail_allocation(c, n)
+        try:
+            srv = lnr.lnr_server_create(c, room_cloud, net_c, max_batch=2, lanes=1, n_levels=3, filter_strength=0.5,
+                                        max_width=128, max_height=96)
+        except lnr.LnrError as e:
+            assert e.status == lnr.LNR_E_OUT_OF_MEMORY
+            continue
+        finally:
+            lnr.lnr_debug_fail_allocation(c, -1)
+        if lnr.lnr_allocated_bytes(c) == full:
+            lnr.lnr_server_destroy(srv)
+            break
+        assert without in (None, lnr.lnr_allocated_bytes(c))
+        without = lnr.lnr_allocated_bytes(c)
+        _serve_two(lnr, ctx, srv, room_cloud, net, cams)
+        lnr.lnr_server_destroy(srv)
+    assert without is not None and without < full
+
+    # a budget that holds the second view's splat scratch, but not all of the rest
+    c = lnr.lnr_context_create(0, full - 50_000)
+    srv = create(c)
+    assert lnr.lnr_allocated_bytes(c) == without
