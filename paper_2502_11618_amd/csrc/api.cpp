@@ -27,12 +27,33 @@ struct Buf {
   size_t cap = 0;
 };
 
+// Scratch of the tiled splat (see tiled_bufs): one allocation up to kOneAllocation
+// bytes, above it the records and the segments in allocations of their own.
+// hipMalloc takes about 60 us for sizes up to 1.5 GB and 320 from 2 GB on: the
+// first call of a new context, 8 views of 20M points at 1080p, took 905 us with
+// one allocation of 2.5 GB, 720 with three.  Below, every allocation more only costs: the first frame
+// of 20M points at 1080p took 1080 us with one per array and 1020 in one, the first
+// soft z-buffer of 5M points 290 and 245.
+constexpr size_t kOneAllocation = 3ull << 29;
+constexpr size_t kTiledPad = 8 * 256;  // beyond the arrays' own bytes, for their alignment
+struct TiledNeed {
+  size_t recs = 0, segs = 0, rest = 0;
+  size_t sum() const { return recs + segs + rest; }
+};
+struct TiledBuf {
+  Buf main, recs, segs;
+  size_t cap() const { return main.cap + recs.cap + segs.cap; }
+  bool holds(const TiledNeed &n) const {
+    return recs.p ? n.recs <= recs.cap && n.segs <= segs.cap && n.rest <= main.cap : n.sum() <= main.cap;
+  }
+};
+
 thread_local std::string g_create_error;
 
 // device scratch reused by consecutive calls on one stream
 struct Scratch {
   Buf flags, chunks, counters, pyramid, act, soft_acc;
-  Buf tiled;  // tiled splat (see tiled_bufs)
+  TiledBuf tiled;
   Buf views;  // multi-view work items
 };
 
@@ -51,10 +72,10 @@ struct lnr_context {
   // lnr_render_views' tiled splat.  Its own, since it follows the number and the
   // size of the views: what lnr_render uses stays in place under it (a caller
   // may have captured those launches).
-  Buf views_tiled;
-  bool views_captured = false;     // views_tiled is used by launches that a caller has captured:
-  std::vector<Buf> views_kept;     // it is then kept until the context goes, a larger one beside it
-  size_t views_refused = SIZE_MAX; // this much was refused once and is not asked for again
+  TiledBuf views_tiled;
+  bool views_captured = false;       // views_tiled is used by launches that a caller has captured:
+  std::vector<TiledBuf> views_kept;  // it is then kept until the context goes, a larger one beside it
+  size_t views_refused = SIZE_MAX;   // this much was refused once and is not asked for again
   // kernel timing
   struct Rec {
     const char *name;
@@ -148,16 +169,15 @@ const char *const kConvNames[2][6][2] = {
     {{"conv/dec0a", "conv/dec0b"}, {"conv/dec1a", "conv/dec1b"}, {"conv/dec2a", "conv/dec2b"},
      {"conv/dec3a", "conv/dec3b"}, {"conv/dec4a", "conv/dec4b"}, {"conv/dec5a", "conv/dec5b"}}};
 
-void dfree(lnr_context *ctx, void *p, size_t bytes);
+void drop(lnr_context *ctx, TiledBuf &b);
 
 // lnr_render_views' scratch is only there for speed: it gives way to whatever else
 // does not fit beside it (and is not asked for in that size again)
 bool release_views(lnr_context *ctx) {
-  Buf &b = ctx->views_tiled;
-  if (!b.p || ctx->views_captured || hipDeviceSynchronize() != hipSuccess) return false;
-  ctx->views_refused = std::min(ctx->views_refused, b.cap);
-  dfree(ctx, b.p, b.cap);
-  b = Buf();
+  TiledBuf &b = ctx->views_tiled;
+  if (!b.cap() || ctx->views_captured || hipDeviceSynchronize() != hipSuccess) return false;
+  ctx->views_refused = std::min(ctx->views_refused, b.cap());
+  drop(ctx, b);
   return true;
 }
 
@@ -193,9 +213,18 @@ void dfree(lnr_context *ctx, void *p, size_t bytes) {
   ctx->allocated -= std::min<uint64_t>(ctx->allocated, bytes);
 }
 
-// grow-only scratch; an old buffer is released only after the device is idle.
-// pad: bytes beyond those accounted for (the alignment of parts)
-lnr_status ensure(lnr_context *ctx, Buf &b, size_t bytes, size_t pad = 0) {
+void drop(lnr_context *ctx, Buf &b) {
+  dfree(ctx, b.p, b.cap);
+  b = Buf();
+}
+void drop(lnr_context *ctx, TiledBuf &b) {
+  drop(ctx, b.main);
+  drop(ctx, b.recs);
+  drop(ctx, b.segs);
+}
+
+// grow-only scratch; an old buffer is released only after the device is idle
+lnr_status ensure(lnr_context *ctx, Buf &b, size_t bytes) {
   if (b.cap >= bytes && b.p) return LNR_OK;
   if (b.p) {
     LNR_HIP(ctx, hipDeviceSynchronize());
@@ -203,9 +232,28 @@ lnr_status ensure(lnr_context *ctx, Buf &b, size_t bytes, size_t pad = 0) {
     b.p = nullptr;
     b.cap = 0;
   }
-  lnr_status st = dalloc(ctx, &b.p, bytes, bytes + pad);
+  lnr_status st = dalloc(ctx, &b.p, bytes);
   if (st == LNR_OK) b.cap = bytes;
   return st;
+}
+lnr_status ensure(lnr_context *ctx, TiledBuf &b, const TiledNeed &need) {
+  if (b.holds(need)) return LNR_OK;
+  if (b.cap()) {
+    LNR_HIP(ctx, hipDeviceSynchronize());
+    drop(ctx, b);
+  }
+  const bool one = need.sum() <= kOneAllocation;
+  for (const auto &[buf, bytes] : {std::make_pair(&b.recs, one ? 0 : need.recs), std::make_pair(&b.segs, one ? 0 : need.segs),
+                                   std::make_pair(&b.main, one ? need.sum() : need.rest)}) {
+    if (!bytes) continue;
+    const lnr_status st = dalloc(ctx, &buf->p, bytes, bytes + kTiledPad);
+    if (st != LNR_OK) {
+      drop(ctx, b);
+      return st;
+    }
+    buf->cap = bytes;
+  }
+  return LNR_OK;
 }
 
 bool aligned(const void *p, size_t a) { return (reinterpret_cast<uintptr_t>(p) % a) == 0; }
@@ -582,9 +630,11 @@ void context_free(lnr_context *ctx) {
   (void)hipSetDevice(ctx->device);
   (void)hipDeviceSynchronize();
   for (Buf *b : {&ctx->sc.flags, &ctx->sc.chunks, &ctx->sc.counters, &ctx->sc.pyramid, &ctx->sc.act, &ctx->sc.soft_acc,
-                 &ctx->sc.tiled, &ctx->sc.views, &ctx->views_tiled})
-    dfree(ctx, b->p, b->cap);
-  for (const Buf &b : ctx->views_kept) dfree(ctx, b.p, b.cap);
+                 &ctx->sc.views})
+    drop(ctx, *b);
+  drop(ctx, ctx->sc.tiled);
+  drop(ctx, ctx->views_tiled);
+  for (TiledBuf &b : ctx->views_kept) drop(ctx, b);
   for (auto &r : ctx->recs) {
     (void)hipEventDestroy(r.a);
     (void)hipEventDestroy(r.b);
@@ -766,23 +816,20 @@ void lnr_cloud_destroy(lnr_cloud *c) {
 // ---------------------------------------------------------------------------
 // Scratch of the tiled splat for n_views views at once of a cloud of n points
 // (with the counters of every view but the first, which has the context's),
-// sized for grid g (the largest view's, see TiledSplatGrid): one allocation,
-// kTiledPad bytes beyond the arrays' own for their alignment.  (With one per
-// array a new context's first frame of 20M points at 1080p took 1080 us, 1020
-// with one; soft z-buffer, 5M points: 290 and 245.)
-constexpr size_t kTiledPad = 8 * 256;
-static size_t tiled_bytes(const TiledSplatGrid &g, uint32_t n, int n_views) {
+// sized for grid g (the largest view's, see TiledSplatGrid).
+static TiledNeed tiled_need(const TiledSplatGrid &g, uint32_t n, int n_views) {
   const size_t v = (size_t)n_views;
-  return v * (8ull * n + 20 * g.seg_cap + 8 * g.unit_cap + 4ull * tile_count_words(g.n_tiles) + 8ull * g.n_tiles + 4) +
-         (v - 1) * 4 * kViewCounterWords;
+  return {v * 8 * n, v * 16 * g.seg_cap,
+          v * (4 * g.seg_cap + 8 * g.unit_cap + 4ull * tile_count_words(g.n_tiles) + 8ull * g.n_tiles + 4) +
+              (v - 1) * 4 * kViewCounterWords};
 }
 // What lnr_render allocates for one view: with room for a segment per record, so
 // that no cloud of fewer points at no more tiles needs more, whatever its cells
 // (a caller who captures its launches warms the context with its largest).
-static size_t tiled_reserve(TiledSplatGrid g, uint32_t n) {
+static TiledNeed tiled_reserve(TiledSplatGrid g, uint32_t n) {
   g.seg_cap = std::max<uint32_t>(1, n);
   g.unit_cap = tiled_unit_cap(g.n_tiles, g.seg_cap, n);
-  return tiled_bytes(g, n, 1);
+  return tiled_need(g, n, 1);
 }
 // the words to clear, from the first view's tile_nseg on: per-tile counts of
 // every view, then the counters of every view but the first
@@ -790,18 +837,21 @@ static uint32_t tiled_clear_words(const TiledSplatGrid &g, int n_views = 1) {
   return tile_count_words(g.n_tiles) * (uint32_t)n_views + kViewCounterWords * (uint32_t)(n_views - 1);
 }
 // the part of view v of n_views; *counters (views past the first): its counters
-static TiledSplatBufs tiled_bufs(const Buf &b, const TiledSplatGrid &g, uint32_t n, int n_views = 1, int view = 0,
+static TiledSplatBufs tiled_bufs(const TiledBuf &b, const TiledSplatGrid &g, uint32_t n, int n_views = 1, int view = 0,
                                  uint32_t **counters = nullptr) {
   const size_t nv = (size_t)n_views, v = (size_t)view;
-  char *at = static_cast<char *>(b.p);
+  char *at = nullptr;
   auto take = [&](size_t bytes) {  // every view's array, bytes each
     char *p = at;
     at += (nv * bytes + 255) / 256 * 256;
     return p + v * bytes;
   };
   TiledSplatBufs t;
+  at = static_cast<char *>(b.recs.p ? b.recs.p : b.main.p);
   t.recs = reinterpret_cast<uint64_t *>(take(8ull * n));
+  if (b.recs.p) at = static_cast<char *>(b.segs.p);
   t.segs = reinterpret_cast<uint4 *>(take(16 * g.seg_cap));
+  if (b.recs.p) at = static_cast<char *>(b.main.p);
   t.sorted = reinterpret_cast<uint32_t *>(take(4 * g.seg_cap));
   t.units = reinterpret_cast<uint2 *>(take(8 * g.unit_cap));
   t.tile_nseg = reinterpret_cast<uint32_t *>(at) + v * tile_count_words(g.n_tiles);
@@ -819,17 +869,18 @@ static TiledSplatBufs tiled_bufs(const Buf &b, const TiledSplatGrid &g, uint32_t
 // quarter of the device memory still free; shared out evenly over the passes.
 // 0: not even one view's scratch does, beyond what `held` has.
 constexpr size_t kViewsScratch = 6ull << 30;
-static int tiled_views_at_once(lnr_context *ctx, const Buf &held, const TiledSplatGrid &g, uint32_t n_points, int n,
+static int tiled_views_at_once(lnr_context *ctx, const TiledBuf &held, const TiledSplatGrid &g, uint32_t n_points, int n,
                                size_t *refused) {
   size_t free_bytes = 0, total_bytes = 0;
   bool asked = false;
   for (int v = std::min(n, kViewsPerPass); v >= 1; --v) {
-    const size_t need = tiled_bytes(g, n_points, v);
-    if (need > held.cap) {
+    const TiledNeed parts = tiled_need(g, n_points, v);
+    if (!held.holds(parts)) {
+      const size_t need = parts.sum();
       if (need >= *refused || (v > 1 && need > kViewsScratch)) continue;
       if (!asked && hipMemGetInfo(&free_bytes, &total_bytes) != hipSuccess) free_bytes = 0;
       asked = true;
-      if ((ctx->budget && ctx->allocated - held.cap + need > ctx->budget) || need - held.cap > free_bytes / 4) {
+      if ((ctx->budget && ctx->allocated - held.cap() + need > ctx->budget) || need > held.cap() + free_bytes / 4) {
         *refused = need;
         continue;
       }
@@ -848,7 +899,7 @@ static int tiled_views_at_once(lnr_context *ctx, const Buf &held, const TiledSpl
 //  - nothing is allocated while the caller captures the stream, and what the
 //    captured launches use is never freed under them (within kViewsScratch in all).
 static int views_at_once(lnr_context *ctx, const TiledSplatGrid &g, uint32_t n_points, int n, hipStream_t s) {
-  Buf &held = ctx->views_tiled;
+  TiledBuf &held = ctx->views_tiled;
   hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
   const bool asked = hipStreamIsCapturing(s, &capture) == hipSuccess;
   if (!asked || capture != hipStreamCaptureStatusNone) {
@@ -862,22 +913,22 @@ static int views_at_once(lnr_context *ctx, const TiledSplatGrid &g, uint32_t n_p
   const std::string err = ctx->err;
   int v = n;
   while ((v = tiled_views_at_once(ctx, held, g, n_points, v, &ctx->views_refused)) > 0) {
-    const size_t need = tiled_bytes(g, n_points, v);
-    if (need > held.cap && ctx->views_captured) {
-      size_t sum = held.cap + need;
-      for (const Buf &b : ctx->views_kept) sum += b.cap;
-      Buf larger;
-      if (sum <= kViewsScratch && ensure(ctx, larger, need, kTiledPad) == LNR_OK) {
+    const TiledNeed need = tiled_need(g, n_points, v);
+    if (!held.holds(need) && ctx->views_captured) {
+      size_t sum = held.cap() + need.sum();
+      for (const TiledBuf &b : ctx->views_kept) sum += b.cap();
+      TiledBuf larger;
+      if (sum <= kViewsScratch && ensure(ctx, larger, need) == LNR_OK) {
         ctx->views_kept.push_back(held);
         held = larger;
         ctx->views_captured = false;
         break;
       }
-    } else if (ensure(ctx, held, need, kTiledPad) == LNR_OK) {
+    } else if (ensure(ctx, held, need) == LNR_OK) {
       break;
     }
     ctx->err = err;
-    ctx->views_refused = need;
+    ctx->views_refused = need.sum();
   }
   return v;
 }
@@ -936,8 +987,8 @@ static lnr_status render_impl(lnr_context *ctx, Scratch &scr, const lnr_cloud *c
   const bool atomic = count || (flags & LNR_RENDER_ATOMIC_SPLAT) != 0;
   const TiledSplatGrid tg = tiled_splat_grid((uint32_t)cam->width, (uint32_t)cam->height, c->d);
   // every allocation comes before the first launch: a failure leaves the image untouched
-  if (!atomic && scr.tiled.cap < tiled_bytes(tg, c->d.n, 1) &&
-      (st = ensure(ctx, scr.tiled, tiled_reserve(tg, c->d.n), kTiledPad)) != LNR_OK)
+  if (!atomic && !scr.tiled.holds(tiled_need(tg, c->d.n, 1)) &&
+      (st = ensure(ctx, scr.tiled, tiled_reserve(tg, c->d.n))) != LNR_OK)
     return st;
   if (soft && (st = ensure(ctx, scr.soft_acc, 16ull * npix)) != LNR_OK) return st;
   if (dev && atomic) return fail(ctx, LNR_E_INVALID_ARG, "a camera in device memory needs the tiled splat");
@@ -990,7 +1041,7 @@ static TiledSplatGrid largest_grid(const lnr_cloud *c, const lnr_camera *cams, i
 // Up to kViewsPerPass views (n) in the same launches of the tiled splat, whose
 // scratch (flags, views, counters, and in `tiled` the tiled splat's for n views of grid g)
 // is there.  dev (may be nullptr): the views' cameras in device memory.
-static lnr_status render_tiled_views(lnr_context *ctx, Scratch &scr, const Buf &tiled, const lnr_cloud *c,
+static lnr_status render_tiled_views(lnr_context *ctx, Scratch &scr, const TiledBuf &tiled, const lnr_cloud *c,
                                      const lnr_camera *cams, const lnr_image *outs, int n, const TiledSplatGrid &g,
                                      bool no_cull, hipStream_t s, const DevCam *dev) {
   uint32_t *counters = static_cast<uint32_t *>(scr.counters.p);
@@ -1622,9 +1673,10 @@ void server_release(lnr_server *srv) {
     if (l.stream) (void)hipStreamSynchronize(l.stream);
     for (auto &g : l.graphs) (void)hipGraphExecDestroy(g.second);
     for (auto g : l.graph_defs) (void)hipGraphDestroy(g);
-    for (Buf *b : {&l.sc.flags, &l.sc.chunks, &l.sc.counters, &l.sc.pyramid, &l.sc.act, &l.sc.soft_acc, &l.sc.tiled,
+    for (Buf *b : {&l.sc.flags, &l.sc.chunks, &l.sc.counters, &l.sc.pyramid, &l.sc.act, &l.sc.soft_acc,
                    &l.sc.views})
-      dfree(ctx, b->p, b->cap);
+      drop(ctx, *b);
+    drop(ctx, l.sc.tiled);
     if (l.head_outs_dev) dfree(ctx, l.head_outs_dev, 8ull * 16);
     if (l.head_outs_host) (void)hipHostFree(l.head_outs_host);
     if (l.cams_dev) dfree(ctx, l.cams_dev, sizeof(DevCam) * 16);
@@ -1724,8 +1776,8 @@ lnr_status lnr_server_create(lnr_context *ctx, const lnr_cloud *c, const lnr_une
         (st = ensure(ctx, l.sc.chunks, 8ull * kDepthBuckets * std::max<uint32_t>(1, c->d.max_chunks))) != LNR_OK ||
         (st = ensure(ctx, l.sc.counters, 4 * kCounterWords)) != LNR_OK ||
         (st = ensure(ctx, l.sc.pyramid, pyr)) != LNR_OK || (st = ensure(ctx, l.sc.act, act)) != LNR_OK ||
-        (st = ensure(ctx, l.sc.tiled, tiled_bytes(tiled_splat_grid((uint32_t)mW, (uint32_t)mH, c->d), c->d.n, 1),
-                     kTiledPad)) != LNR_OK ||
+        (st = ensure(ctx, l.sc.tiled, tiled_need(tiled_splat_grid((uint32_t)mW, (uint32_t)mH, c->d), c->d.n, 1))) !=
+            LNR_OK ||
         (cfg->soft && (st = ensure(ctx, l.sc.soft_acc, 16 * npix)) != LNR_OK) ||
         (st = dalloc(ctx, (void **)&l.head_outs_dev, 8ull * 16)) != LNR_OK ||
         (st = dalloc(ctx, (void **)&l.cams_dev, sizeof(DevCam) * 16)) != LNR_OK ||
@@ -1749,23 +1801,19 @@ lnr_status lnr_server_create(lnr_context *ctx, const lnr_cloud *c, const lnr_une
     for (auto &l : srv->lanes) {
       size_t refused = SIZE_MAX;
       int v = tiled_views_at_once(ctx, l.sc.tiled, g, c->d.n, std::min(cfg->max_batch, kViewsPerPass), &refused);
-      auto needs = [&](int n) { return items + pyr * (size_t)(n - 1) + tiled_bytes(g, c->d.n, n); };
-      while (v > 1 && ctx->budget &&
-             (needs(v) > most || ctx->allocated - std::min(l.sc.tiled.cap, tiled_bytes(g, c->d.n, v)) + needs(v) > ctx->budget))
-        --v;
+      auto needs = [&](int n) { return items + pyr * (size_t)(n - 1) + tiled_need(g, c->d.n, n).sum(); };
+      while (v > 1 && ctx->budget && (needs(v) > most || ctx->allocated - l.sc.tiled.cap() + needs(v) > ctx->budget)) --v;
       if (v <= 1) continue;
       if (ensure(ctx, l.sc.views, items) == LNR_OK && ensure(ctx, l.sc.pyramid, pyr * (size_t)v) == LNR_OK &&
-          ensure(ctx, l.sc.tiled, tiled_bytes(g, c->d.n, v), kTiledPad) == LNR_OK) {
+          ensure(ctx, l.sc.tiled, tiled_need(g, c->d.n, v)) == LNR_OK) {
         l.views = v;
         continue;
       }
       ctx->err = err;
-      for (Buf *b : {&l.sc.views, &l.sc.pyramid}) {
-        dfree(ctx, b->p, b->cap);
-        *b = Buf();
-      }
+      drop(ctx, l.sc.views);
+      drop(ctx, l.sc.pyramid);
       if ((st = ensure(ctx, l.sc.pyramid, pyr)) != LNR_OK ||
-          (st = ensure(ctx, l.sc.tiled, tiled_bytes(g, c->d.n, 1), kTiledPad)) != LNR_OK) {
+          (st = ensure(ctx, l.sc.tiled, tiled_need(g, c->d.n, 1))) != LNR_OK) {
         server_release(srv.get());
         return st;
       }

@@ -291,3 +291,17 @@ def test_server_without_the_scratch_for_several_requests(lnr, ctx, room_cloud, r
     c = lnr.lnr_context_create(0, full - 50_000)
     srv = create(c)
     assert lnr.lnr_allocated_bytes(c) == without
+
+
+def test_views_with_scratch_in_several_allocations(lnr, ctx):
+    """Scratch of more than 1.5 GiB is three allocations."""
+    rng = np.random.default_rng(12)
+    xyz = rng.uniform(-4, 4, (12_000_000, 3)).astype(np.float32) + np.float32([0, 0, 6])
+    rgb = rng.integers(0, 256, (len(xyz), 3)).astype(np.uint8)
+    cloud = lnr.lnr_cloud_load(ctx, xyz, rgb, 0.25)
+    cams = [_camera(640 + 32 * v, 480, 300.0 + 10 * v) for v in range(8)]
+    c = lnr.lnr_context_create(0)
+    imgs = _views(lnr, c, cloud, cams)
+    assert lnr.lnr_allocated_bytes(c) > 3 << 29
+    _assert_views(lnr, ctx, cloud, cams, imgs, "12M points")
+    lnr.lnr_cloud_destroy(cloud)
