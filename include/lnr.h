@@ -198,7 +198,8 @@ lnr_status lnr_render_soft(lnr_context *ctx, const lnr_cloud *c, const lnr_camer
  * A pass is the screen-tiled splat of all its views in the same launches.  Its
  * scratch is lnr_render's once per view, so a pass takes as many views as fit
  * in 6 GiB of scratch, the context's budget and a quarter of the free device
- * memory.  Where not even one view's does, or can be allocated, the z-buffers are
+ * memory.  Where not even one view's does, or can be allocated, and for few views
+ * or small images of small clouds, where that is faster, the z-buffers are
  * the images' key buffers, lowered with 64-bit atomicMin after an on-chip
  * z-buffer per work item (LNR_RENDER_ATOMIC_SPLAT's method), and a pass loads
  * each point once.  Uses 16 bytes of context scratch per work item and depth

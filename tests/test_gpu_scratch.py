@@ -305,3 +305,20 @@ def test_views_with_scratch_in_several_allocations(lnr, ctx):
     assert lnr.lnr_allocated_bytes(c) > 3 << 29
     _assert_views(lnr, ctx, cloud, cams, imgs, "12M points")
     lnr.lnr_cloud_destroy(cloud)
+
+
+@pytest.mark.parametrize("per_cell,n_views,W,H,tiled", [
+    (1, 1, 640, 480, False), (1, 5, 640, 480, False), (1, 6, 640, 480, True), (1, 8, 160, 149, False),
+    (1, 8, 160, 281, False), (1, 8, 160, 282, True), (7, 5, 320, 281, False), (7, 5, 320, 282, True),
+    (0, 1, 160, 149, False), (0, 3, 160, 149, True), (0, 1, 160, 151, True)])
+def test_views_by_either_splat(lnr, ctx, room_cloud, per_cell, n_views, W, H, tiled):
+    """The choice between the tiled splat and the images' key buffers, at its
+    limits (40000 cells of 1 or 7 points; the room's 760): the same images."""
+    cloud = lnr.lnr_cloud_load(ctx, *_grid_cloud(per_cell), 0.1) if per_cell else room_cloud
+    cams = [_camera(W, H, 60.0 + 9 * v) for v in range(n_views)]
+    c = lnr.lnr_context_create(0)
+    lnr.lnr_profile_enable(c, True)
+    imgs = _views(lnr, c, cloud, cams)
+    names = {name for name, _ in lnr.lnr_profile_read(c)}
+    assert ("bin" in names, "splat_views" in names) == (tiled, not tiled)
+    _assert_views(lnr, ctx, cloud, cams, imgs, "views")
