@@ -309,10 +309,10 @@ __global__ __launch_bounds__(kThreads) void chunk_count_kernel(const uint32_t *_
     v += __shfl_xor(v, off, 64);
     d += __shfl_xor(d, off, 64);
   }
-  if ((threadIdx.x & 63) == 0 && v) {
-    atomicAdd(&total[0], v);
-    atomicAdd(&total[1], d);
-  }
+  // both sums (below 2^32) in one atomic: waves of a grid of a million cells queue
+  // up for it (100K points in 1M cells: load 1040 us with two, 880 with one)
+  if ((threadIdx.x & 63) == 0 && v)
+    atomicAdd(reinterpret_cast<unsigned long long *>(total), (unsigned long long)d << 32 | v);
 }
 
 inline uint32_t div_up(uint64_t a, uint64_t b) { return (uint32_t)((a + b - 1) / b); }
