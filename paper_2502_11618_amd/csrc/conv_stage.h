@@ -24,6 +24,9 @@ __device__ inline const char *uniform(const char *p) {
 // instruction is issued whatever the mask, so a wave can count its loads in
 // flight.  The compiler does not see the LDS write: wait_loads() and a barrier
 // come before the data are read.
+// m0 is overwritten, which a clobber list cannot say (the register is reserved):
+// no kernel with these loads may have another user of m0 (tests/test_kernel_asm.py
+// looks at the compiled code).  exec is all ones before and after.
 __device__ inline void load_lds16(const char *base, uint32_t voff, uint32_t lds, uint64_t lanes) {
   asm volatile("s_mov_b32 m0, %0\n\ts_mov_b64 exec, %3\n\tglobal_load_lds_dwordx4 %1, %2\n\ts_mov_b64 exec, -1"
                :
