@@ -1387,11 +1387,13 @@ hipError_t tiled_stage(const CloudDev &c, const void *items, const uint32_t *wor
     case 0:
 #define LNR_BIN(NT, ALL)                                                                                              \
   bin_kernel<NT, NV, ALL><<<dim3(c.max_items, ny), NT, 0, s>>>(c.x, c.y, c.z, items, c.max_chunks, work, vs)
-      if (c.item_points == kBinDense) {
-        if (soft) LNR_BIN(512, true); else LNR_BIN(512, false);
-      } else {
-        if (soft) LNR_BIN(256, true); else LNR_BIN(256, false);
+      if constexpr (NV == 1) {  // (the soft z-buffer renders one view at a time)
+        if (soft) {
+          if (c.item_points == kBinDense) LNR_BIN(512, true); else LNR_BIN(256, true);
+          break;
+        }
       }
+      if (c.item_points == kBinDense) LNR_BIN(512, false); else LNR_BIN(256, false);
 #undef LNR_BIN
       break;
     case 1:
