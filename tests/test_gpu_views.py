@@ -147,3 +147,28 @@ def test_views_reject_bad_arguments_before_drawing(lnr, ctx, room_cloud, room_ca
     with pytest.raises(lnr.LnrError):
         lnr.lnr_render_views(ctx, room_cloud, [cams[0], c, cams[2]], imgs)
     assert untouched(imgs)
+
+
+def test_views_dedup_and_direct_paths_of_the_key_buffer_splat(lnr, ctx):
+    """The same as test_views_dedup_and_direct_paths_in_one_pass through the
+    splat into the images' key buffers, which a budget without room for the
+    tiled splat's scratch takes: rectangles of 4096 pixels and one more, the
+    largest that meet in the on-chip z-buffer and the smallest that do not."""
+    rng = np.random.default_rng(10)
+    n = 4096
+    ux = rng.integers(0, 64, n) + 0.25
+    vy = rng.integers(0, 64, n) + 0.5
+    ux[:2], vy[:2] = (0.25, 63.25), (0.5, 63.5)
+    w = np.where(np.arange(n) % 2 == 0, 1.0, 2.0)
+    xyz = np.stack([ux * w, vy * w, w], axis=1).astype(np.float32)
+    rgb = rng.integers(0, 256, (n, 3), dtype=np.uint8)
+    g = G.partition(xyz, rgb, 1e4)
+    cloud = lnr.lnr_cloud_load(ctx, xyz, rgb, 1e4)
+    cams = [_identity_like(80, 70, 1.0, 0.0), _identity_like(140, 70, 2.0, 0.0), _identity_like(80, 70, 1.0, -32.0),
+            _identity_like(64, 64, 1.0, 0.0), _identity_like(200, 70, 2.0, 5.0), _identity_like(80, 70, 65 / 64, 0.0)]
+    c = lnr.lnr_context_create(0, 1 + 256 + 92)  # cull flags, work items, counters
+    lnr.lnr_profile_enable(c, True)
+    imgs = _render_views(lnr, c, cloud, cams)
+    assert "splat_views" in {name for name, _ in lnr.lnr_profile_read(c)}
+    for v, cam in enumerate(cams):
+        assert_images_equal(image_to_host(imgs[v]), R.render(g, cam), f"view {v}")
