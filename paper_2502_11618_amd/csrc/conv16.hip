@@ -959,7 +959,15 @@ inline double rounds(const ConvCall &c, int rows, int channels) {
 // us), and 32 channels x 8 rows, two steps in flight, where even that leaves
 // CUs idle (60 x 80 x 256 channels: 12.4 / 19.8 against 15.6 / 25.1 us).  Split
 // bfloat16 reads both planes: its 64 x 16 and 64 x 8 tiles take 8 waves and a CU
-// each.  Any choice gives the same results.
+// each, for 2.0 and 1.1 units of time; 64 to 512 channels, us with 16 and with 8 rows:
+//   0.5 rounds of 16 rows (1 of 8)  256 x 256 x 64 channels     43.0 / 31.5
+//   1.0 (2)                         128 x 128 x 512             69.1 / 78.4
+//   1.25 (3)                        120 x 160 x 512            111.5 / 97.2
+//   2.3 (5)                         480 x 640 x 64             120.3 / 116.9
+//   2.7 (6)                         360 x 480 x 128             80.1 / 87.9
+//   7 (14), no longer counted whole 720 x 1280 x 64            331.9 / 363.8
+// (of 168 layers, 0.02 to 16 rounds, the choice was the faster one in all but one,
+// 64.0 / 63.1).  Any choice gives the same results.
 template <int MODE>
 hipError_t dispatch(const ConvCall &c, hipStream_t s) {
   const bool wide = c.layer->cout_pad % 64 == 0;
