@@ -27,14 +27,14 @@ struct Buf {
   size_t cap = 0;
 };
 
-// Scratch of the tiled splat (see tiled_bufs): one allocation up to kOneAllocation
-// bytes, above it the records and the segments in allocations of their own.
-// hipMalloc takes about 60 us for sizes up to 1.5 GB and 320 from 2 GB on: the
-// first call of a new context, 8 views of 20M points at 1080p, took 905 us with
-// one allocation of 2.5 GB, 720 with three.  Below, every allocation more only costs: the first frame
-// of 20M points at 1080p took 1080 us with one per array and 1020 in one, the first
-// soft z-buffer of 5M points 290 and 245.
-constexpr size_t kOneAllocation = 3ull << 29;
+// Scratch of the tiled splat (see tiled_bufs): one allocation, or the records, the
+// segments and the rest each in one of its own.  hipMalloc serves up to about 2 MB
+// from memory that the runtime holds (1 us); more takes 60 us where a freed range
+// fits and 300 to 800 where none does, and from 2 GB on 320 and more.  First calls on new
+// contexts, us, in one allocation / in three: projection of 100K points 210 / 136, 250K
+// 645 / 171, 1M (28 MB) 646 / 170, 5M 230 / 518, 20M 315 / 416; 8 views of 20M points
+// at 1080p (2.5 GB) 905 / 720.  (Several views' parts are seldom small: one below.)
+constexpr size_t kSmallAllocations = 24u << 20, kOneAllocation = 3ull << 29;
 constexpr size_t kTiledPad = 8 * 256;  // beyond the arrays' own bytes, for their alignment
 struct TiledNeed {
   size_t recs = 0, segs = 0, rest = 0;
@@ -236,13 +236,14 @@ lnr_status ensure(lnr_context *ctx, Buf &b, size_t bytes) {
   if (st == LNR_OK) b.cap = bytes;
   return st;
 }
-lnr_status ensure(lnr_context *ctx, TiledBuf &b, const TiledNeed &need) {
+// small: up to this size in three allocations
+lnr_status ensure(lnr_context *ctx, TiledBuf &b, const TiledNeed &need, size_t small = kSmallAllocations) {
   if (b.holds(need)) return LNR_OK;
   if (b.cap()) {
     LNR_HIP(ctx, hipDeviceSynchronize());
     drop(ctx, b);
   }
-  const bool one = need.sum() <= kOneAllocation;
+  const bool one = need.sum() > small && need.sum() <= kOneAllocation;
   for (const auto &[buf, bytes] : {std::make_pair(&b.recs, one ? 0 : need.recs), std::make_pair(&b.segs, one ? 0 : need.segs),
                                    std::make_pair(&b.main, one ? need.sum() : need.rest)}) {
     if (!bytes) continue;
@@ -939,13 +940,13 @@ static int views_at_once(lnr_context *ctx, const TiledSplatGrid &g, uint32_t n_p
       size_t sum = held.cap() + need.sum();
       for (const TiledBuf &b : ctx->views_kept) sum += b.cap();
       TiledBuf larger;
-      if (sum <= kViewsScratch && ensure(ctx, larger, need) == LNR_OK) {
+      if (sum <= kViewsScratch && ensure(ctx, larger, need, 0) == LNR_OK) {
         ctx->views_kept.push_back(held);
         held = larger;
         ctx->views_captured = false;
         break;
       }
-    } else if (ensure(ctx, held, need) == LNR_OK) {
+    } else if (ensure(ctx, held, need, 0) == LNR_OK) {
       break;
     }
     ctx->err = err;
