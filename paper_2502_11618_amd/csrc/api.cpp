@@ -244,16 +244,18 @@ lnr_status ensure(lnr_context *ctx, TiledBuf &b, const TiledNeed &need, size_t s
     drop(ctx, b);
   }
   const bool one = need.sum() > small && need.sum() <= kOneAllocation;
-  for (const auto &[buf, bytes] : {std::make_pair(&b.recs, one ? 0 : need.recs), std::make_pair(&b.segs, one ? 0 : need.segs),
-                                   std::make_pair(&b.main, one ? need.sum() : need.rest)}) {
+  TiledBuf all;  // (b only once it is whole: an allocation on the way may release it)
+  for (const auto &[buf, bytes] : {std::make_pair(&all.recs, one ? 0 : need.recs), std::make_pair(&all.segs, one ? 0 : need.segs),
+                                   std::make_pair(&all.main, one ? need.sum() : need.rest)}) {
     if (!bytes) continue;
     const lnr_status st = dalloc(ctx, &buf->p, bytes, bytes + kTiledPad);
     if (st != LNR_OK) {
-      drop(ctx, b);
+      drop(ctx, all);
       return st;
     }
     buf->cap = bytes;
   }
+  b = all;
   return LNR_OK;
 }
 
@@ -1140,10 +1142,12 @@ lnr_status lnr_render_views(lnr_context *ctx, const lnr_cloud *c, const lnr_came
   const TiledSplatGrid grid = largest_grid(c, cams, n_views);
   uint64_t npix = 0;
   for (int v = 0; v < n_views; ++v) npix = std::max(npix, (uint64_t)cams[v].width * (uint64_t)cams[v].height);
-  const int at_once = key_buffers_faster(c->d, n_views, npix)
-                          ? 0
-                          : views_at_once(ctx, grid, c->d.n, std::min(n_views, kViewsPerPass), s);
+  int at_once = key_buffers_faster(c->d, n_views, npix)
+                    ? 0
+                    : views_at_once(ctx, grid, c->d.n, std::min(n_views, kViewsPerPass), s);
   if ((st = ensure(ctx, scr.counters, 4 * kCounterWords)) != LNR_OK) return st;
+  // (which the views' scratch may have given way to)
+  if (at_once > 0 && !ctx->views_tiled.holds(tiled_need(grid, c->d.n, at_once))) at_once = 0;
   uint32_t *counters = static_cast<uint32_t *>(scr.counters.p);
   uint4 *items = static_cast<uint4 *>(scr.views.p);
   const bool no_cull = (flags & LNR_RENDER_NO_CULL) != 0;

@@ -322,3 +322,21 @@ def test_views_by_either_splat(lnr, ctx, room_cloud, per_cell, n_views, W, H, ti
     names = {name for name, _ in lnr.lnr_profile_read(c)}
     assert ("bin" in names, "splat_views" in names) == (tiled, not tiled)
     _assert_views(lnr, ctx, cloud, cams, imgs, "views")
+
+
+@pytest.mark.parametrize("n", [1, 8])
+def test_views_give_way_to_their_own_counters(lnr, ctx, room_cloud, room_cams, n):
+    """Budgets around what the tiled splat of n views takes: where it fits but
+    the last thing that the call allocates, its counters, does not fit beside
+    it, the views go to the key buffers."""
+    cams = list(room_cams[:n])
+    full = lnr.lnr_context_create(0)
+    _views(lnr, full, room_cloud, cams)
+    need = lnr.lnr_allocated_bytes(full)  # with 92 bytes of counters
+    for budget in (need - 93, need - 92, need - 1, need):
+        c = lnr.lnr_context_create(0, budget)
+        for _ in range(2):
+            imgs = _views(lnr, c, room_cloud, cams)
+            _assert_views(lnr, ctx, room_cloud, cams, imgs, f"budget {budget - need}")
+        assert lnr.lnr_allocated_bytes(c) <= budget
+        assert (lnr.lnr_allocated_bytes(c) == need) == (budget == need)
