@@ -79,14 +79,14 @@ typedef struct {
  *   LNR_FP32     : float32 activations, float32 matrix-core products.
  *   LNR_BF16     : bfloat16 activations and weights, float32 accumulation.
  *   LNR_FP8_E4M3 : OCP e4m3 matrix-core operands, float32 accumulation:
- *                  float16 activations rounded to e4m3 (to nearest even,
- *                  saturating at 448) as they are multiplied, e4m3 weights
- *                  with one scale per output channel (its largest weight maps
- *                  to 448).
+ *                  activations rounded to float16 and that to e4m3 (to nearest
+ *                  even, saturating at 448) where they are produced, e4m3
+ *                  weights with one scale per output channel (its largest
+ *                  weight maps to 448).
  *   LNR_FP8_E4M3X3 : as LNR_FP8_E4M3 with each operand split into e4m3 high
  *                  + low parts (low = e4m3 of the remainder), multiplied as
  *                  lo*hi + hi*lo + hi*hi.
- *   LNR_BF16X3   : float32 activations; each operand split into bfloat16
+ *   LNR_BF16X3   : each float32 activation and weight split into bfloat16
  *                  high + low parts and multiplied as hi*hi + hi*lo + lo*hi
  *                  with float32 accumulation (near-float32 accuracy on
  *                  bfloat16 matrix cores).
@@ -168,8 +168,8 @@ void lnr_cloud_destroy(lnr_cloud *c);
  * culling never changes the image.  out->key, depth and rgba must all be
  * non-NULL with out->width/height equal to the camera's.  flags: 0 or any of
  * LNR_RENDER_NO_CULL, LNR_RENDER_ATOMIC_SPLAT, LNR_RENDER_COUNT_ATOMICS (see
- * above; the image is the same).  The tiled splat takes up to 28 bytes of
- * context scratch per point of the cloud. */
+ * above; the image is the same).  The tiled splat takes 28 1/4 bytes of context
+ * scratch per point of the cloud and 28 per tile of 32 x 32 pixels. */
 lnr_status lnr_render(lnr_context *ctx, const lnr_cloud *c, const lnr_camera *cam, lnr_image *out, uint32_t flags,
                       void *hip_stream);
 /* Render with the soft z-buffer of Method, "Point Cloud Projection" (colours of
@@ -324,10 +324,10 @@ lnr_status lnr_profile_read(lnr_context *ctx, lnr_kernel_time *out, int32_t max,
  * Each submitted camera becomes a request.  lnr_server_step takes a free lane
  * (a HIP stream with its own scratch and an RGBDA image per batch slot) and
  * the oldest pending request, joins it with up to max_batch - 1 other pending
- * requests of the same resolution, and enqueues for them: render (or soft
- * render), depth filter and input pack per request, and one batched U-Net
- * over all of them (each convolution processes the whole batch in one
- * launch).  With use_graphs, the whole launch sequence of every (resolution,
+ * requests of the same resolution, and enqueues for them: render and depth
+ * filter, several requests in each launch where the lane has scratch for it
+ * (soft render: one by one), and one batched U-Net over all of them (each
+ * convolution processes the whole batch in one launch).  With use_graphs, the whole launch sequence of every (resolution,
  * batch size) is captured once as a HIP graph and replayed: the kernels read
  * the batch's cameras and output pointers from device arrays that each step
  * writes before the replay.  Lanes run concurrently, so batches
