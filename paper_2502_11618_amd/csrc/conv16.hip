@@ -872,14 +872,21 @@ __global__ __launch_bounds__(64 * NW, 2) void enc0_kernel(Args a0, Args a1) {
 
 // 1x1 head of a layer too wide to fuse it: float32 weights [3][C], one thread
 // per pixel, planar float32 output.  x: blocks of 8 16-bit channels (MODE 1, 3)
-// or 4 float32 channels (MODE 2, and the float32 network).
-template <int MODE>
+// or 4 float32 channels (MODE 2, and the float32 network).  Bound by the pixels'
+// loads: U of them in flight per thread.  Four (16 channels) hide their latency
+// where one leaves it open (192 channels, us with one / four: fp16 64 x 64 14.9 /
+// 8.4, 1280 x 720 82.8 / 70.8; float32 64 x 64 16.9 / 8.7, 256 x 256 17.9 / 10.7);
+// float32 pixels, whole cache lines each, are read at full rate by four waves per
+// SIMD and more, and one then keeps the accesses in order (640 x 480 43.4 / 40.8,
+// 800 x 600 66.5 / 72.5, 1920 x 1080 289 / 300).  The sums' order is the same.
+template <int MODE, int U>
 __global__ __launch_bounds__(256) void head_kernel(const char *__restrict__ x, int C, size_t npix,
                                                    const float *__restrict__ w, const float *__restrict__ b,
                                                    float *__restrict__ out) {
   const size_t p = (size_t)blockIdx.x * 256 + threadIdx.x;
   if (p >= npix) return;
   float y0 = b[0], y1 = b[1], y2 = b[2];
+#pragma unroll U
   for (int c = 0; c < C; c += 4) {
     float v[4];
     if constexpr (MODE == 2) {
@@ -1061,11 +1068,13 @@ hipError_t launch_head16(const void *x, int C, int H, int W, const ConvLayer &he
   const float *w = static_cast<const float *>(head.w);
   const char *xc = static_cast<const char *>(x);
   if (p == Prec::BF16)
-    head_kernel<1><<<nb, 256, 0, s>>>(xc, C, npix, w, head.bias, out);
-  else if (p == Prec::BF16X3 || p == Prec::F32)  // float32 activations
-    head_kernel<2><<<nb, 256, 0, s>>>(xc, C, npix, w, head.bias, out);
+    head_kernel<1, 4><<<nb, 256, 0, s>>>(xc, C, npix, w, head.bias, out);
+  else if ((p == Prec::BF16X3 || p == Prec::F32) && nb <= 5 * kCUs)  // float32 activations
+    head_kernel<2, 4><<<nb, 256, 0, s>>>(xc, C, npix, w, head.bias, out);
+  else if (p == Prec::BF16X3 || p == Prec::F32)
+    head_kernel<2, 1><<<nb, 256, 0, s>>>(xc, C, npix, w, head.bias, out);
   else
-    head_kernel<3><<<nb, 256, 0, s>>>(xc, C, npix, w, head.bias, out);
+    head_kernel<3, 4><<<nb, 256, 0, s>>>(xc, C, npix, w, head.bias, out);
   return hipGetLastError();
 }
 
