@@ -420,9 +420,10 @@ struct ConvLds {
   // runs of two tiles, or where every tile has the same ones (launch() sees to it).
   static constexpr int kHead = kBias + 2 * 2 * CT * 32 * 4;
   static constexpr int kBytes = kHead + (HEAD ? (3 * 32 * CT + 4) * 4 : 0);
+  static constexpr int kWaves = NW == 8 || 2 * kBytes <= 160 * 1024 ? 2 : 1;  // per SIMD, as LDS has room
 };
 template <int MODE, int MB, int R, int NW, int CW, int DI, int DW, bool HEAD>
-__global__ __launch_bounds__(64 * NW, 2) void conv_kernel(Args a) {
+__global__ __launch_bounds__(64 * NW, (ConvLds<MODE, MB, R, NW, CW, DI, DW, HEAD>::kWaves)) void conv_kernel(Args a) {
   using S = ConvLds<MODE, MB, R, NW, CW, DI, DW, HEAD>;
   static_assert(!HEAD || CW == 1, "the head sums over all channels in one wave");
   static_assert(DI == DW || (DI == 2 && DW == 1), "the loads counted by wait_for");
@@ -974,13 +975,27 @@ inline double rounds(const ConvCall &c, int rows, int channels) {
 //   2.7 (6)                         360 x 480 x 128             80.1 / 87.9
 //   7 (14), no longer counted whole 720 x 1280 x 64            331.9 / 363.8
 // (of 168 layers, 0.02 to 16 rounds, the choice was the faster one in all but one,
-// 64.0 / 63.1).  Any choice gives the same results.
+// 64.0 / 63.1).  Layers of an odd number of 32-channel tiles take tiles of 32
+// channels x 16 rows where those are fewer rounds by the ratio of the two tiles'
+// times, which grows with the matrix work per byte; split bfloat16's are 8 waves
+// and 4, a CU each.  96 output channels of 16-channel steps, us with 16 / 8 rows
+// (32 -> 96 channels; rounds of 16 rows):
+//            60 x 80 (0.2)   150 x 200 (0.8)  240 x 320 (1.8)  540 x 960 (12)
+//   fp16       8.4 / 7.4        9.4 / 9.6       12.4 / 14.8      49.2 / 65.0
+//   fp8        9.2 / 7.8        9.9 / 9.5       12.3 / 12.4      36.6 / 46.3
+//   fp8x3     12.5 / 9.5       13.8 / 12.6      19.4 / 20.4      81.0 / 92.1
+//   bf16x3    11.8 / 9.4       13.8 / 16.9      22.4 / 29.2     117.6 / 134.7
+// (308 layers each, 64 x 64 to 2560 x 1440, against the faster of the two: always
+// 16 rows 5, 6, 11 and 6% slower, always 8 rows 10, 6, 3 and 13%, the choice under
+// 1%).  Any choice gives the same results.
 template <int MODE>
 hipError_t dispatch(const ConvCall &c, hipStream_t s) {
   const bool wide = c.layer->cout_pad % 64 == 0;
   const bool head = c.head_out || c.head_outs;
   if constexpr (MODE == 2) {
-    if (!wide) return launch<MODE, 1, 2, 8, 1, 1, 1>(c, s);
+    if (!wide)
+      return rounds(c, 16, 32) * 1.3 <= rounds(c, 8, 32) ? launch<MODE, 1, 2, 8, 1, 1, 1>(c, s)
+                                                         : launch<MODE, 1, 2, 4, 1, 1, 1>(c, s);
     if (!head && rounds(c, 16, 64) * 2.0 > rounds(c, 8, 64) * 1.1) return launch<MODE, 1, 2, 8, 2, 1, 1>(c, s);
     return launch<MODE, 2, 2, 8, 1, 1, 1>(c, s);
   } else {
@@ -993,8 +1008,9 @@ hipError_t dispatch(const ConvCall &c, hipStream_t s) {
       if (t64x16 <= t64x8 && t64x16 <= t32x8) return launch<MODE, 2, 4, 4, 1, 1, 1>(c, s);
       return t64x8 <= t32x8 ? launch<MODE, 2, 2, 4, 1, 1, 1>(c, s) : launch<MODE, 1, 2, 4, 1, 2, 2>(c, s);
     }
-    return cost(16, 32, 1.8) <= cost(8, 32, 1.0) ? launch<MODE, 1, 4, 4, 1, 2, 1>(c, s)
-                                                  : launch<MODE, 1, 2, 4, 1, 2, 2>(c, s);
+    constexpr double t32x16 = MODE == 5 ? 1.8 : (MODE == 4 ? 1.6 : 1.5);
+    return cost(16, 32, t32x16) <= cost(8, 32, 1.0) ? launch<MODE, 1, 4, 4, 1, 2, 1>(c, s)
+                                                     : launch<MODE, 1, 2, 4, 1, 2, 2>(c, s);
   }
 }
 
