@@ -945,7 +945,8 @@ def main():
         return dom, {"kernel": dom, "bound": "mfma", "achieved": round(ex, 2), "peak": peak, "unit": "TFLOP/s",
                      "frac": round(ex / peak, 4), "flops_per_launch": executed[dom],
                      "avg_launch_ms": round(conv_ms[dom], 4),
-                     "algorithm": "winograd F(2x2,3x3)" if executed[dom] != flops[dom] else "direct",
+                     "algorithm": ("direct" if executed[dom] == flops[dom] else "direct, split operands"
+                                   if executed[dom] > flops[dom] else "winograd F(2x2,3x3)"),
                      "algorithmic_flops_per_launch": flops[dom], "effective_tflops": round(eff, 2)}
 
     exec_fp32 = mfma_flops if p0 == "fp32" else flops
